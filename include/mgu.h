@@ -355,7 +355,7 @@ typedef struct mg_query_options {
  *   normal    [3][nq] unit normal of the face, zero if degenerate or none
  * point, bary, dist2, normal may each be NULL to skip.  max_dist2 >= 0
  * (+inf allowed).  bvh must be a MG_PRIM_TRIANGLES BVH built/refit on verts
- * (leaf triangles are read from the BVH, the winner's from verts).  opts: host
+ * (triangles are read from the BVH's records, or from verts).  opts: host
  * pointer or NULL.
  * ---------------------------------------------------------------------- */
 mg_status mg_closest_point_query(const void *bvh, size_t bvh_bytes, int32_t n_prims,

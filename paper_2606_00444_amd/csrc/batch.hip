@@ -209,6 +209,7 @@ __device__ QueryArgs query_args(const PlanScene &P, int64_t t, const RefitArgs &
     a.leaf_faces = P.leaf_faces;
     a.prim = P.prim;
     a.inv_prim = P.inv_prim;
+    a.leaf_parent = P.leaf_parent;
     a.status = r.status;
     a.verts = r.verts;
     a.nv = s.n_verts;

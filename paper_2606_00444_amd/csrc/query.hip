@@ -16,14 +16,15 @@
 //  * lane:  one query per lane, depth-first, nearer child first; stack in LDS
 //           for the first 32 entries and in a private array beyond (Karras trees
 //           over 30-bit codes with index tie-break are at most 62 levels deep).
-//  * batch: one wave owns M queries and a shared LDS stack of (query, node, box
-//           distance) entries; each round the wave pops up to 64 entries, one per
-//           lane, expands them and pushes the surviving children with ballots.
+//  * batch: one wave owns M queries and a shared LDS stack of (lower bound,
+//           query, node) entries; each round the wave pops up to 32 nodes, bounds
+//           each child in a lane of its own, pushes the surviving nodes with
+//           ballots and queues the leaves, which are tested exactly together.
 //           A query's best is a 64-bit LDS atomic min over (float bits of d^2,
 //           original id): non-negative floats order like their bit patterns, so
 //           this is the lexicographic (d^2, id) minimum.  A query near the middle
 //           of a closed surface has thousands of near-equidistant faces; here they
-//           are expanded 64 at a time instead of one lane walking them serially.
+//           are expanded by the whole wave instead of one lane walking them serially.
 #include "traverse.hpp"
 
 #include <atomic>
@@ -423,6 +424,7 @@ extern "C" mg_status mg_closest_point_query(const void *bvh, size_t bvh_bytes, i
     a.leaf_faces = cat<int32_t>(bvh, L.off_leaf_faces);
     a.prim = cat<int32_t>(bvh, L.off_prim);
     a.inv_prim = cat<int32_t>(bvh, L.off_inv_prim);
+    a.leaf_parent = cat<int32_t>(bvh, L.off_leaf_parent);
     a.status = &const_cast<mg_lbvh_header *>(cat<mg_lbvh_header>(bvh, L.off_header))->status;
     a.hdr_nv = &cat<mg_lbvh_header>(bvh, L.off_header)->n_verts;
     a.verts = verts; a.nv = n_verts; a.n = n_prims;
@@ -448,6 +450,7 @@ extern "C" mg_status mg_nearest_point_query(const void *bvh, size_t bvh_bytes, i
     a.leaf_faces = nullptr;
     a.prim = cat<int32_t>(bvh, L.off_prim);
     a.inv_prim = cat<int32_t>(bvh, L.off_inv_prim);
+    a.leaf_parent = cat<int32_t>(bvh, L.off_leaf_parent);
     a.status = &const_cast<mg_lbvh_header *>(cat<mg_lbvh_header>(bvh, L.off_header))->status;
     a.hdr_nv = &cat<mg_lbvh_header>(bvh, L.off_header)->n_verts;
     a.verts = points; a.nv = n_prims; a.n = n_prims;
@@ -489,6 +492,7 @@ extern "C" mg_status mg_knn_surface_query(const void *bvh, size_t bvh_bytes, int
     a.leaf_faces = cat<int32_t>(bvh, L.off_leaf_faces);
     a.prim = cat<int32_t>(bvh, L.off_prim);
     a.inv_prim = cat<int32_t>(bvh, L.off_inv_prim);
+    a.leaf_parent = cat<int32_t>(bvh, L.off_leaf_parent);
     a.status = &const_cast<mg_lbvh_header *>(cat<mg_lbvh_header>(bvh, L.off_header))->status;
     a.hdr_nv = &cat<mg_lbvh_header>(bvh, L.off_header)->n_verts;
     a.verts = verts; a.nv = n_verts; a.n = n_prims;

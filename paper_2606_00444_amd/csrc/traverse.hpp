@@ -38,8 +38,10 @@ __device__ __forceinline__ float prune_bound(float best, float qm) {
 __device__ __forceinline__ float qnorm1(f3 q) { return (fabsf(q.x) + fabsf(q.y)) + fabsf(q.z); }
 
 constexpr int kBatchWaves = 4;          // waves per workgroup of the batch kernel
-constexpr int kBatchCap = 512;          // stack entries before the pop width shrinks
+constexpr int kBatchCap = 320;          // stack entries before the pop width shrinks
+constexpr int kPopNodes = 32;           // nodes a round pops: a pair of lanes each
 constexpr int kBatchAlloc = kBatchCap + 64;
+constexpr int kLeafNarrow = 8;         // stack entries below which waiting leaves are tested at once
 
 struct QueryArgs {
     const float4 *nodes;                // [n-1][6]
@@ -57,6 +59,7 @@ struct QueryArgs {
     const int32_t *order;               // processing order (permutation) or nullptr
     unsigned long long *counters;       // [4] statistics or nullptr
     const int32_t *inv_prim;            // [n] leaf of each original id (id -> position in leaf order)
+    const int32_t *leaf_parent;         // [n] record slot of each leaf: 2 x its parent node + the slot
     int32_t *status;                    // error word of the BVH header
     const int32_t *hdr_nv;              // vertex count of the build (header), or nullptr
     uint32_t *queue;                    // batch kernel: dynamic batch counter (zeroed before launch) or nullptr
@@ -166,32 +169,38 @@ __device__ __forceinline__ unsigned long long pack_best(float d2, int32_t id) {
     return (static_cast<unsigned long long>(__float_as_uint(d2)) << 32) | static_cast<uint32_t>(id);
 }
 
+// Final record of query q when no face qualifies.
+__device__ __forceinline__ void write_none(const QueryArgs &a, int64_t q, f3 p) {
+    store_face(a, q, -1);
+    if (a.point) store3(a.point, a.nq, q, p);
+    if (a.bary) { a.bary[q] = 0.0f; a.bary[a.nq + q] = 0.0f; }
+    if (a.dist2) a.dist2[q] = INFINITY;
+    if (a.normal) store3(a.normal, a.nq, q, f3{0.0f, 0.0f, 0.0f});
+}
+
+// Final record of query q on face `id`, the triangle ABC.
+__device__ __forceinline__ void write_face(const QueryArgs &a, int64_t q, f3 p, int32_t id, f3 A, f3 B, f3 C) {
+    float w1, w2;
+    const float dd = tri_closest(p, A, B, C, w1, w2);
+    store_face(a, q, id);
+    if (a.point) store3(a.point, a.nq, q, tri_point(A, B, C, w1, w2));
+    if (a.bary) { a.bary[q] = w1; a.bary[a.nq + q] = w2; }
+    if (a.dist2) a.dist2[q] = dd;
+    if (a.normal) store3(a.normal, a.nq, q, tri_normal(A, B, C));
+}
+
 // Final record of query q: recomputed from the winning leaf's face (triangles)
 // or point, which the BVH stores bit-identically.
 template <bool kTri>
 __device__ void write_result(const QueryArgs &a, int64_t q, f3 p, int32_t leaf, int32_t id, float d2) {
-    if (kTri) {
-        if (leaf >= 0 && leaf < a.n) {
-            const f3 A = vload(a.verts, a.nv, a.leaf_faces[leaf]);
-            const f3 B = vload(a.verts, a.nv, a.leaf_faces[a.n + leaf]);
-            const f3 C = vload(a.verts, a.nv, a.leaf_faces[2 * a.n + leaf]);
-            float w1, w2;
-            const float dd = tri_closest(p, A, B, C, w1, w2);
-            store_face(a, q, id);
-            if (a.point) store3(a.point, a.nq, q, tri_point(A, B, C, w1, w2));
-            if (a.bary) { a.bary[q] = w1; a.bary[a.nq + q] = w2; }
-            if (a.dist2) a.dist2[q] = dd;
-            if (a.normal) store3(a.normal, a.nq, q, tri_normal(A, B, C));
-        } else {
-            store_face(a, q, -1);
-            if (a.point) store3(a.point, a.nq, q, p);
-            if (a.bary) { a.bary[q] = 0.0f; a.bary[a.nq + q] = 0.0f; }
-            if (a.dist2) a.dist2[q] = INFINITY;
-            if (a.normal) store3(a.normal, a.nq, q, f3{0.0f, 0.0f, 0.0f});
-        }
-    } else {
+    if (!kTri) {
         store_face(a, q, leaf >= 0 ? id : -1);
         if (a.dist2) a.dist2[q] = leaf >= 0 ? d2 : INFINITY;
+    } else if (leaf >= 0 && leaf < a.n) {
+        write_face(a, q, p, id, vload(a.verts, a.nv, a.leaf_faces[leaf]), vload(a.verts, a.nv, a.leaf_faces[a.n + leaf]),
+                   vload(a.verts, a.nv, a.leaf_faces[2 * a.n + leaf]));
+    } else {
+        write_none(a, q, p);
     }
 }
 
@@ -259,19 +268,28 @@ __device__ __forceinline__ float single_leaf_dist2(const QueryArgs &a, f3 p) {
 constexpr int kDonateMin = 128;          // a wave keeps at least 64 entries after giving 64
 constexpr int kIdleSpinLimit = 1 << 22;  // bounded waits: error word instead of a hang
 
+// A stack entry: high word, the node's lower bound with its low five bits
+// replaced by the query's slot in the batch (rounding the bound down, so it
+// stays a bound); low word, the node.  A waiting leaf: its parent's high word,
+// and 2 x the parent node + the child slot that holds it.  The stack grows from
+// the front of e, the waiting leaves from its end.
+typedef unsigned long long StackEntry;
+constexpr uint32_t kSlotMask = 31u;
+__device__ __forceinline__ StackEntry make_entry(float bound, uint32_t slot, uint32_t node) {
+    return (static_cast<StackEntry>((__float_as_uint(bound) & ~kSlotMask) | slot) << 32) | node;
+}
+
 template <int M>
 struct WaveStack {
-    int32_t node[kBatchAlloc];
-    float dist[kBatchAlloc];
-    uint8_t slot[kBatchAlloc];
-    unsigned long long best[M];         // per query of the batch: (d^2 bits, original id)
-    float q[3][M];
+    static_assert(M <= kSlotMask + 1, "an entry holds its query's slot in five bits");
+    StackEntry e[kBatchAlloc];
+    float4 q[M];                        // per query of the batch: the point, and prune_bound of its best
+    unsigned long long best[M];         // (d^2 bits, original id)
+    uint32_t code[M];                   // where the best face lies (a record slot); only a guess, see leaf_of
 };
 
 struct WaveMail {
-    int32_t node[64];
-    float dist[64];
-    uint8_t slot[64];
+    StackEntry e[64];
     int32_t count;                      // entries in the chunk
     int32_t owner;                      // wave whose batch the entries belong to
     int32_t state;                      // 0 empty, 1 full, 2 being taken, 3 being filled
@@ -312,6 +330,12 @@ __device__ __forceinline__ bool lds_cas(int32_t *p, int expect, int v) {
 // nearest).
 __device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
 
+// Set bits of a ballot below this lane.
+__device__ __forceinline__ int rank_below(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(m >> 32),
+                                     __builtin_amdgcn_mbcnt_lo(static_cast<uint32_t>(m), 0u));
+}
+
 // The lanes of a wave hand stack entries to each other through LDS (a lane
 // pops what another lane pushed, copied or donated).  The hardware keeps a
 // wave's LDS operations in order, but the compiler only orders each lane's own
@@ -323,30 +347,79 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Exact tests of the last `cnt` (<= 64) of wave `self`'s lc waiting leaves, one
+// per lane.  A face at most as far as its query's best lowers the best and the
+// prune bound (both by LDS atomics: other waves may hold chunks of the batch).
+template <bool kTri, int M>
+__device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<M> &S, WaveStack<M> &O, int lc, int cnt,
+                                           BatchStats &stats) {
+    const int lane = threadIdx.x % 64;
+    bool act = lane < cnt;
+    const StackEntry en = S.e[kBatchAlloc - lc + (act ? lane : 0)];
+    const uint32_t hi = static_cast<uint32_t>(en >> 32), code = static_cast<uint32_t>(en), slot = hi & kSlotMask;
+    const float4 q = O.q[slot];
+    act = act && __uint_as_float(hi & ~kSlotMask) <= q.w;   // its parent may have fallen behind by now
+    if (a.counters) stats.lex += __popcll(__ballot(act));
+    if (act) {
+        const float4 *rec = a.nodes + 3 * static_cast<uint64_t>(code);
+        const f3 p = f3{q.x, q.y, q.z};
+        const float4 f0 = rec[0], f1 = rec[1], f2 = kTri ? rec[2] : f1;
+        const float d2 = leaf_dist2<kTri>(p, f0, f1, f2);
+        if (d2 <= q.w) {
+            const unsigned long long cand = pack_best(d2, __float_as_int(f1.w));
+            if (cand < atomicMin(&O.best[slot], cand)) {
+                atomicMin(reinterpret_cast<uint32_t *>(&O.q[slot].w), __float_as_uint(prune_bound(d2, qnorm1(p))));
+                O.code[slot] = code;
+            }
+        }
+    }
+    return lc - cnt;
+}
+
 // Rounds over wave `self`'s stack (sp entries) until it is empty.  Entries
-// belong to the batch of wave `owner`: its query positions and bests.
+// belong to the batch of wave `owner`: its query points and bests.
+//
+// A round pops up to 32 nodes and gives each child to a lane of its own.  Every
+// lane bounds its child without a branch; internal children that survive are
+// pushed, the nearer of a pair on top, and leaf children are queued.  Queued
+// leaves are tested exactly together, once 32 wait or the stack runs low: tested
+// inside the round they left most lanes idle (18 of 64 needed an exact test, in
+// two divergent passes, and 26 a bound test of the leaf's box, with two children
+// to a lane); with 64 waiting, cold queries' bests came late (299 nodes a query
+// instead of 283 on 1,000,000 faces).  Waiting leaves are not tested against
+// their box, which costs about what it drops.  A child to a lane halves what a
+// lone wave issues in a round, its cost on small launches.
+//
+// 50,000 hinted queries on 40,000 faces (batches of 16): 117 -> 62 us with the
+// joint bound of child_bound, 55% of the time issuing VALU; 1M on 500,000 faces:
+// 5,980 -> 1,340 us, 80% issuing and 6.6 TB/s of cache-line misses.
 template <bool kTri, int M>
 __device__ void run_stack(const QueryArgs &a, BatchLds<M> &L, int self, int owner, int sp, BatchStats &stats) {
     const int lane = threadIdx.x % 64;
-    const uint64_t lt = lanemask_lt();
+    const uint32_t n_nodes = static_cast<uint32_t>(a.n - 1), odd = lane & 1;
     WaveStack<M> &S = L.st[self];
     WaveStack<M> &O = L.st[owner];
     WaveMail &mail = L.mail;
+    int lc = 0;                               // waiting leaves
     // the stack never exceeds kBatchCap + 62: a round of width k pushes at most
-    // 2k entries, widths are cut to (kBatchCap - sp) / 2, and width-1 rounds are
+    // 2k entries (nodes and leaves together), widths are cut to half the room
+    // left, the leaves are tested whenever room runs out, and width-1 rounds are
     // a plain depth-first walk whose growth is bounded by the tree depth; each
     // query expands each internal node at most once, so the round cap only stops
     // a corrupted buffer from looping
-    for (int64_t round = 0; sp > 0 && round < static_cast<int64_t>(M + 1) * a.n + 64; ++round) {
+    const int64_t max_rounds = 2 * static_cast<int64_t>(M + 1) * a.n + 64;
+    for (int64_t round = 0; sp + lc > 0 && round < max_rounds; ++round) {
         wave_sync();                          // the previous round's pushes, or the entries handed in
+        if (lc >= kLeafWait || (lc > 0 && (sp < kLeafNarrow || sp + lc > kBatchCap - 2 * kPopNodes))) {
+            lc = test_leaves<kTri, M>(a, S, O, lc, lc < 64 ? lc : 64, stats);
+            wave_sync();
+            if (sp == 0) continue;
+        }
         if (sp >= kDonateMin) {
             int give = 0;
             if (lane == 0 && lds_load(&mail.state) == 0 && lds_cas(&mail.state, 0, 3)) give = 1;
             if (uniform(give)) {
-                const int i = sp - 64 + lane;
-                mail.node[lane] = S.node[i];
-                mail.dist[lane] = S.dist[i];
-                mail.slot[lane] = S.slot[i];
+                mail.e[lane] = S.e[sp - 64 + lane];
                 wave_sync();
                 sp -= 64;
                 if (lane == 0) {
@@ -357,147 +430,291 @@ __device__ void run_stack(const QueryArgs &a, BatchLds<M> &L, int self, int owne
                 }
             }
         }
-        int take = sp < 64 ? sp : 64;
-        const int room = (kBatchCap - sp) / 2;
+        int take = sp < kPopNodes ? sp : kPopNodes;
+        const int room = (kBatchCap - sp - lc) / 2;
         if (take > room) take = room > 1 ? room : 1;
-        const bool pop = lane < take;
-        const int idx = sp - 1 - lane;
-        int32_t node = 0, slot = 0;
-        float nd = INFINITY;
-        if (pop) {
-            node = S.node[idx];
-            nd = S.dist[idx];
-            slot = S.slot[idx];
-            if (slot >= M) { node = -1; slot = 0; }
-        }
-        sp -= take;
-        bool act = pop && node >= 0 && node < a.n - 1;
-        unsigned long long best = act ? O.best[slot] : 0ull;
-        const f3 qp = act ? f3{O.q[0][slot], O.q[1][slot], O.q[2][slot]} : f3{0.0f, 0.0f, 0.0f};
-        const float qm = qnorm1(qp);
-        act = act && nd <= prune_bound(__uint_as_float(static_cast<uint32_t>(best >> 32)), qm);
-        float4 l0, l1, l2, r0, r1, r2;
-        int32_t lref = 0, rref = 0;
-        unsigned long long cand = ~0ull;
-        if (act) {
-            const float4 *rec = a.nodes + 6 * static_cast<int64_t>(node);
-            l0 = rec[0]; l1 = rec[1]; l2 = rec[2]; r0 = rec[3]; r1 = rec[4]; r2 = rec[5];
-            lref = __float_as_int(l0.w);
-            rref = __float_as_int(r0.w);
-            if (lref >= a.n - 1 || rref >= a.n - 1 || ~lref >= a.n || ~rref >= a.n) act = false;
-        }
-        const float pbound = prune_bound(__uint_as_float(static_cast<uint32_t>(best >> 32)), qm);
-        const bool tl = act && lref < 0 && leaf_box_dist2<kTri>(qp, l0, l1, l2) <= pbound;
-        const bool tr = act && rref < 0 && leaf_box_dist2<kTri>(qp, r0, r1, r2) <= pbound;
-        if (a.counters) {
-            stats.exp += __popcll(__ballot(act));
-            stats.lbox += __popcll(__ballot(act && lref < 0)) + __popcll(__ballot(act && rref < 0));
-            stats.lex += __popcll(__ballot(tl)) + __popcll(__ballot(tr));
-        }
-        if (tl) cand = pack_best(leaf_dist2<kTri>(qp, l0, l1, l2), __float_as_int(l1.w));
-        if (tr) {
-            const unsigned long long c = pack_best(leaf_dist2<kTri>(qp, r0, r1, r2), __float_as_int(r1.w));
-            if (c < cand) cand = c;
-        }
-        if (cand != ~0ull) atomicMin(&O.best[slot], cand);
-        best = act ? O.best[slot] : 0ull;
-        const float bound = prune_bound(__uint_as_float(static_cast<uint32_t>(best >> 32)), qm);
-        const float dq = 0x1p-20f * qm;
-        const float dl = (act && lref >= 0) ? child_bound<kTri>(qp, dq, l0, l1, l2) : INFINITY;
-        const float dr = (act && rref >= 0) ? child_bound<kTri>(qp, dq, r0, r1, r2) : INFINITY;
-        const bool pl = act && lref >= 0 && dl <= bound;
-        const bool pr = act && rref >= 0 && dr <= bound;
-        const uint64_t bl = __ballot(pl), br = __ballot(pr);
-        const int off = sp + __popcll(bl & lt) + __popcll(br & lt);
-        // The bound above only holds for a valid tree; the clamp keeps a
-        // corrupted buffer from writing past this wave's stack.
-        if (pl && pr) {
-            const bool left_near = dl <= dr;   // nearer child on top of the stack
-            if (off < kBatchAlloc) {
-                S.node[off] = left_near ? rref : lref;
-                S.dist[off] = left_near ? dr : dl;
-                S.slot[off] = static_cast<uint8_t>(slot);
-            }
-            if (off + 1 < kBatchAlloc) {
-                S.node[off + 1] = left_near ? lref : rref;
-                S.dist[off + 1] = left_near ? dl : dr;
-                S.slot[off + 1] = static_cast<uint8_t>(slot);
-            }
-        } else if ((pl || pr) && off < kBatchAlloc) {
-            S.node[off] = pl ? lref : rref;
-            S.dist[off] = pl ? dl : dr;
-            S.slot[off] = static_cast<uint8_t>(slot);
-        }
-        sp += __popcll(bl) + __popcll(br);
-        if (sp > kBatchAlloc) {              // past the bound of a valid tree
+        if (sp + lc + take > kBatchAlloc) {   // past the bound of a valid tree
             if (lane == 0) atomicOr(a.status, 64);
-            sp = kBatchAlloc;
+            break;
         }
+        const bool pop = lane < 2 * take;
+        const StackEntry en = S.e[pop ? sp - 1 - (lane >> 1) : 0];
+        sp -= take;
+        const uint32_t hi = static_cast<uint32_t>(en >> 32), node = static_cast<uint32_t>(en), slot = hi & kSlotMask;
+        const float4 q = O.q[slot];
+        const f3 qp = f3{q.x, q.y, q.z};
+        const bool act = pop && node < n_nodes && __uint_as_float(hi & ~kSlotMask) <= q.w;
+        float4 c0{}, c1{}, c2{};
+        if (act) {
+            const float4 *rec = a.nodes + 6 * static_cast<uint64_t>(node) + 3 * odd;
+            c0 = rec[0]; c1 = rec[1];
+            if (kTri) c2 = rec[2];
+        }
+        const int32_t ref = __float_as_int(c0.w);
+        const float d = child_bound<kTri>(qp, 0x1p-20f * qnorm1(qp), c0, c1, c2);
+        const bool push = act && ref >= 0 && d <= q.w, leaf = act && ref < 0;
+        const uint64_t pm = __ballot(push), lm = __ballot(leaf);
+        if (a.counters) {
+            stats.exp += __popcll(__ballot(act)) / 2;
+            stats.lbox += __popcll(lm);
+        }
+        // the other child's bound (infinite unless it is pushed too) decides which is on top
+        const float mine = push ? d : INFINITY;
+        const float other = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(mine), 0xb1, 0xf, 0xf, true));
+        const float even = odd ? other : mine, far = odd ? mine : other;
+        int pos = sp + rank_below(pm);
+        if (even <= far && far < INFINITY) pos += odd ? -1 : 1;      // the even lane's child is the nearer: swap
+        if (leaf) pos = kBatchAlloc - 1 - lc - rank_below(lm);
+        if (push || leaf)
+            S.e[pos] = leaf ? (static_cast<StackEntry>(hi) << 32) | (2 * node + odd)
+                            : make_entry(d, slot, static_cast<uint32_t>(ref));
+        sp += __popcll(pm);
+        lc += __popcll(lm);
     }
     wave_sync();                              // the last round's bests, before any lane reads them
 }
 
-// Takes the mailbox's chunk, if there is one, and runs it to the end.
-template <bool kTri, int M>
-__device__ bool help_once(const QueryArgs &a, BatchLds<M> &L, int self, BatchStats &stats) {
+// Takes the mailbox's chunk, if there is one, onto wave `self`'s (empty) stack:
+// its size, and the wave whose batch it belongs to; -1 if there is none.
+template <int M>
+__device__ __forceinline__ int take_chunk(const QueryArgs &a, BatchLds<M> &L, int self, int &owner) {
     const int lane = threadIdx.x % 64;
     WaveMail &mail = L.mail;
     int got = 0;
     if (lane == 0 && lds_load(&mail.state) == 1 && lds_cas(&mail.state, 1, 2)) got = 1;
-    if (!uniform(got)) return false;
+    if (!uniform(got)) return -1;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-    const int owner = uniform(mail.owner), n = uniform(mail.count);
+    owner = uniform(mail.owner);
+    int n = uniform(mail.count);
     if (owner < 0 || owner >= kBatchWaves || n < 0 || n > 64) {
-        if (lane == 0) { atomicOr(a.status, 16); lds_store(&mail.state, 0); }
-        return true;
+        if (lane == 0) atomicOr(a.status, 16);
+        owner = -1;
+        n = 0;
     }
-    WaveStack<M> &S = L.st[self];
-    if (lane < n) {
-        S.node[lane] = mail.node[lane];
-        S.dist[lane] = mail.dist[lane];
-        S.slot[lane] = mail.slot[lane];
-    }
+    if (lane < n) L.st[self].e[lane] = mail.e[lane];
     wave_sync();
     if (lane == 0) lds_store(&mail.state, 0);
-    run_stack<kTri, M>(a, L, self, owner, n, stats);
-    if (lane == 0) lds_add(&mail.outstanding[owner], -1);
-    return true;
+    return n;
 }
 
-// Helps other waves until cond() holds (cond is evaluated by every lane on
-// LDS words, so it is wave-uniform).
-template <bool kTri, int M, typename Cond>
-__device__ void wait_helping(const QueryArgs &a, BatchLds<M> &L, int self, BatchStats &stats, Cond cond) {
-    const int lane = threadIdx.x % 64;
-    for (int spin = 0; !cond();) {
-        if (help_once<kTri, M>(a, L, self, stats)) {
-            spin = 0;
-        } else if (++spin > kIdleSpinLimit) {
-            if (lane == 0) atomicOr(a.status, 16);
-            break;
+// The record slot of primitive `id` (original numbering), or -1 if it or its
+// leaf is out of range (n > 1).
+__device__ __forceinline__ int64_t slot_of(const QueryArgs &a, int32_t id) {
+    if (id < 0 || id >= a.n) return -1;
+    const int32_t leaf = a.inv_prim[id];
+    if (leaf < 0 || leaf >= a.n) return -1;
+    const int32_t code = a.leaf_parent[leaf];
+    return code >= 0 && (code >> 1) < a.n - 1 ? code : -1;
+}
+
+// Squared distance from p to the leaf in record slot `code`, and its id.
+template <bool kTri>
+__device__ __forceinline__ float slot_dist2(const QueryArgs &a, f3 p, int64_t code, int32_t &id) {
+    const float4 *rec = a.nodes + 3 * code;
+    const float4 f1 = rec[1];
+    id = __float_as_int(f1.w);
+    return kTri ? leaf_dist2<kTri>(p, rec[0], f1, rec[2]) : leaf_dist2<kTri>(p, f1, f1, f1);
+}
+
+// Another lane's value within each four lanes (mask 1, 2 or 3: the lane's
+// number in its four, xor mask).
+template <int kMask>
+__device__ __forceinline__ uint32_t quad_xor(uint32_t v) {
+    constexpr int kPerm = kMask == 1 ? 0xb1 : kMask == 2 ? 0x4e : 0x1b;
+    return static_cast<uint32_t>(__builtin_amdgcn_mov_dpp(static_cast<int>(v), kPerm, 0xf, 0xf, true));
+}
+template <int kMask>
+__device__ __forceinline__ unsigned long long quad_xor64(unsigned long long v) {
+    return (static_cast<unsigned long long>(quad_xor<kMask>(static_cast<uint32_t>(v >> 32))) << 32) |
+           quad_xor<kMask>(static_cast<uint32_t>(v));
+}
+
+// The seed descent of the batch's queries that `need` one: a walk from the root
+// to the leaves that keeps the kLanes / 2 nearest nodes of a level, each query
+// in kLanes (2 or 4) lanes, a child to a lane.  Returns, in every lane of the
+// query, the nearest of the leaves met on the way (the nearest by its box in
+// each lane), and its record slot in `code`.  With one node kept, both children
+// in a lane and every leaf on the way tested, 20,002 cold queries on 46,000 faces
+// took 58 us and expanded 52 nodes each, the walk included; now 41 us and 30.
+template <bool kTri, int kLanes>
+__device__ __forceinline__ unsigned long long seed_descent(const QueryArgs &a, f3 p, bool need, uint32_t &code) {
+    const uint32_t lane = threadIdx.x % 64, odd = lane & 1, pair = (lane >> 1) & (kLanes / 2 - 1);
+    const uint32_t n_nodes = static_cast<uint32_t>(a.n - 1);
+    const float dq = slab_query_margin(p);
+    uint32_t node = need && pair == 0 ? 0u : ~0u;
+    float leaf_key = INFINITY;
+    uint32_t leaf_code = ~0u;
+    for (int lvl = 0; lvl < 64; ++lvl) {
+        const bool act = node < n_nodes;
+        if (!__ballot(act)) break;
+        uint32_t key = ~0u, ref = ~0u;
+        if (act) {
+            const float4 *rec = a.nodes + 6 * static_cast<uint64_t>(node) + 3 * odd;
+            const float4 c0 = rec[0], c1 = rec[1], c2 = kTri ? rec[2] : c1;
+            const uint32_t r = static_cast<uint32_t>(__float_as_int(c0.w));
+            if (static_cast<int32_t>(r) < 0) {
+                const float b = leaf_box_dist2<kTri>(p, c0, c1, c2);
+                if (b <= leaf_key) {
+                    leaf_key = b;
+                    leaf_code = 2 * node + odd;
+                }
+            } else {
+                key = __float_as_uint(child_bound<kTri>(p, dq, c0, c1, c2));
+                ref = r;
+            }
+        }
+        // unique keys within the query's lanes, absent children last
+        key = (key & ~3u) | (lane & 3);
+        if (kLanes == 2) {
+            const uint32_t other = quad_xor<1>(key), other_ref = quad_xor<1>(ref);
+            node = other < key ? other_ref : ref;
         } else {
-            __builtin_amdgcn_s_sleep(2);
+            const uint32_t k1 = quad_xor<1>(key), k2 = quad_xor<2>(key), k3 = quad_xor<3>(key);
+            const uint32_t rank = (k1 < key) + (k2 < key) + (k3 < key);
+            // the nodes of the two lowest ranks, handed to the two pairs (0: none)
+            uint32_t x = rank == 0 ? ref + 1 : 0u, y = rank == 1 ? ref + 1 : 0u;
+            x |= quad_xor<1>(x);
+            y |= quad_xor<1>(y);
+            x |= quad_xor<2>(x);
+            y |= quad_xor<2>(y);
+            node = (pair ? y : x) - 1;
         }
     }
+    unsigned long long best = ~0ull;
+    if (leaf_code != ~0u) {
+        int32_t id;
+        const float d2 = slot_dist2<kTri>(a, p, leaf_code, id);
+        best = pack_best(d2, id);
+    }
+    code = leaf_code;
+    unsigned long long o = quad_xor64<1>(best);
+    uint32_t oc = quad_xor<1>(code);
+    if (o < best) { best = o; code = oc; }
+    if (kLanes == 4) {
+        o = quad_xor64<2>(best);
+        oc = quad_xor<2>(code);
+        if (o < best) { best = o; code = oc; }
+    }
+    return best;
+}
+
+// Starts a wave's batch [qb, qb + nb): points, starting bests (a hint's
+// distance, else the seed descent's, else max_dist2) and the root on the stack.
+// Returns the stack's size.
+template <bool kTri, int M>
+__device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M> &S, int64_t qb, int nb) {
+    constexpr int kLanes = M <= 16 ? 4 : 2;       // lanes of a query
+    const int lane = threadIdx.x % 64, i = lane / kLanes;
+    const unsigned long long none = pack_best(a.maxd2, INT_MAX);
+    const int64_t qid = i < nb ? query_at(a, qb + i) : -1;
+    const bool own = qid >= 0, lead = own && lane % kLanes == 0;
+    f3 p = f3{0.0f, 0.0f, 0.0f};
+    if (own) p = load3(a.queries, a.nq, qid);
+    unsigned long long best = none;
+    uint32_t code = ~0u;
+    float pb = 0.0f;
+    bool push = false;
+    float rd = 0.0f;
+    if (a.n == 1) {
+        if (lead) {
+            const unsigned long long c = pack_best(single_leaf_dist2<kTri>(a, p), a.prim[0]);
+            if (c < none) best = c;
+        }
+    } else if (a.n > 1) {
+        // a hinted primitive's distance starts the query; without one, the seed descent
+        bool hinted = false;
+        if (a.hint) {
+            if (own) {
+                const int32_t h = a.coherent ? __hip_atomic_load(a.hint + qid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                             : a.hint[qid];
+                const int64_t at = slot_of(a, h);
+                if (at >= 0) {
+                    int32_t id;
+                    const float d2 = slot_dist2<kTri>(a, p, at, id);
+                    const unsigned long long c = pack_best(d2, id);
+                    if (id == h && d2 < INFINITY && c < none) {
+                        best = c;
+                        code = static_cast<uint32_t>(at);
+                        hinted = true;
+                    }
+                }
+            }
+        }
+        const bool need = a.seed && own && !hinted;
+        if (__ballot(need)) {
+            uint32_t at;
+            const unsigned long long c = seed_descent<kTri, kLanes>(a, p, need, at);
+            if (need && c < best) {
+                best = c;
+                code = at;
+            }
+        }
+        rd = box_dist2(p, f3{a.root[0], a.root[1], a.root[2]}, f3{a.root[4], a.root[5], a.root[6]});
+        pb = prune_bound(best < none ? __uint_as_float(static_cast<uint32_t>(best >> 32)) : a.maxd2, qnorm1(p));
+        push = lead && rd <= pb;
+    }
+    if (lead) {
+        S.q[i] = make_float4(p.x, p.y, p.z, pb);
+        S.best[i] = best;
+        S.code[i] = code;
+    }
+    const uint64_t bm = __ballot(push);
+    if (push) S.e[rank_below(bm)] = make_entry(rd, static_cast<uint32_t>(i), 0u);
+    return __popcll(bm);
+}
+
+// Final record of the query in slot `lane` of the batch, its index qid: the
+// face's triangle is read again from its record slot.  The slot noted beside
+// the best may be another face's (two waves lowering one best race on it), so
+// its id is checked, and the face's slot is looked up where they differ.
+template <bool kTri, int M>
+__device__ __forceinline__ void finish_query(const QueryArgs &a, const WaveStack<M> &S, int lane, int64_t qid) {
+    const unsigned long long b = S.best[lane];
+    const float4 q = S.q[lane];
+    const f3 p = f3{q.x, q.y, q.z};
+    const int32_t id = static_cast<int32_t>(b & 0xffffffffull);
+    const float d2 = __uint_as_float(static_cast<uint32_t>(b >> 32));
+    if (!kTri || a.n == 1 || id < 0 || id >= a.n) {
+        write_result_id<kTri>(a, qid, p, id, d2);
+        return;
+    }
+    int64_t code = S.code[lane];
+    if (code >= 2 * (a.n - 1)) code = slot_of(a, id);
+    float4 f0{}, f1{}, f2{};
+    if (code >= 0) {
+        const float4 *rec = a.nodes + 3 * code;
+        f0 = rec[0]; f1 = rec[1]; f2 = rec[2];
+        if (__float_as_int(f1.w) != id) {
+            code = slot_of(a, id);
+            if (code >= 0) {
+                rec = a.nodes + 3 * code;
+                f0 = rec[0]; f1 = rec[1]; f2 = rec[2];
+            }
+        }
+    }
+    if (code < 0) {
+        atomicOr(a.status, 16);
+        write_none(a, qid, p);
+        return;
+    }
+    write_face(a, qid, p, id, xyz(f0), xyz(f1), xyz(f2));
 }
 
 // The workgroup's kBatchWaves waves process the query batches [qb, qb + M)
 // below q_end (positions in the processing order): wave w takes qb = start +
 // w M, then steps by stride or, with a queue, M times the batch numbers it
-// takes from the queue.  Every wave of the workgroup calls this.  kHelpBetween:
-// a wave that has written a batch's results empties the mailbox before it
-// starts its next batch.  The batched persistent kernel leaves that out: there
-// the compiled form of that loop returned faces that were not the nearest for
-// queries of later batches (about one in ten at 100,000 queries without the
-// seed descent), while every other form of this loop, and the plain kernels
-// with it, matched the all-faces kernel exactly; its waves still help while
-// they wait for their own chunks and at the end.
+// takes from the queue.  Every wave of the workgroup calls this.  A wave whose
+// batch waits for chunks it gave away, or that has no batch left, empties the
+// mailbox; kHelpBetween: also before it starts its next batch.  The batched
+// persistent kernel leaves that out: there an earlier form of this loop with it
+// returned faces that were not the nearest for queries of later batches, while
+// every other form, and the plain kernels with it, matched the all-faces kernel
+// exactly.  Each turn of the loop runs one stack, the wave's own or a chunk, so
+// the rounds are compiled once.
 template <bool kTri, int M, bool kHelpBetween = true>
 __device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, int64_t q_end, BatchLds<M> &L) {
     const int lane = threadIdx.x % 64;
     const int self = uniform(static_cast<int>(threadIdx.x / 64));
-    const uint64_t lt = lanemask_lt();
-    const unsigned long long none = pack_best(a.maxd2, INT_MAX);
     WaveStack<M> &S = L.st[self];
     WaveMail &mail = L.mail;
     BatchStats stats;
@@ -514,83 +731,53 @@ __device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, in
         if (lane == 0) b = atomicAdd(a.queue, 1u);
         return static_cast<int64_t>(static_cast<uint32_t>(uniform(static_cast<int>(b)))) * M;
     };
-    for (int64_t qb = a.queue ? next(0) : start + static_cast<int64_t>(self) * M; qb < q_end; qb = next(qb)) {
+    int64_t qb = a.queue ? next(0) : start + static_cast<int64_t>(self) * M;
+    bool open = false;                        // batch qb is started and its results not yet written
+    bool between = false;                     // a batch was written: chunks go before the next
+    bool told = false;                        // this wave's last batch is counted in mail.done
+    for (int spin = 0;;) {
+        int owner = -1, sp = -1;
+        if (open || between || qb >= q_end) sp = take_chunk<M>(a, L, self, owner);
         const int nb = static_cast<int>(q_end - qb < M ? q_end - qb : M);
-        const int64_t qid = lane < nb ? query_at(a, qb + lane) : -1;
-        const bool own = qid >= 0;
-        f3 p = f3{0.0f, 0.0f, 0.0f};
-        if (own) {
-            p = load3(a.queries, a.nq, qid);
-            S.q[0][lane] = p.x; S.q[1][lane] = p.y; S.q[2][lane] = p.z;
-            S.best[lane] = none;
+        if (sp < 0 && !open && qb < q_end) {
+            sp = start_batch<kTri, M>(a, S, qb, nb);
+            owner = self;
+            open = true;
+            between = false;
+        } else if (sp >= 0) {
+            owner = owner < 0 ? -1 : owner | kBatchWaves;      // a chunk: counted when done
         }
-        int sp = 0;
-        if (a.n == 1) {
-            if (own) {
-                const unsigned long long c = pack_best(single_leaf_dist2<kTri>(a, p), a.prim[0]);
-                if (c < none) S.best[lane] = c;
-            }
-        } else if (a.n > 1) {
-            // a hinted primitive's distance starts the query; without one, the seed descent
-            unsigned long long seeded = own ? hint_best<kTri>(a, qid, p, none) : none;
-            if (a.seed && own && seeded == none) {
-                // one greedy root-to-leaf walk (nearer internal child first) gives an
-                // upper bound before the wide expansion starts
-                const float dq = slab_query_margin(p);
-                int32_t node = 0;
-                for (int lvl = 0; lvl < 64 && node >= 0 && node < a.n - 1; ++lvl) {
-                    const float4 *rec = a.nodes + 6 * static_cast<int64_t>(node);
-                    const float4 l0 = rec[0], l1 = rec[1], l2 = rec[2], r0 = rec[3], r1 = rec[4], r2 = rec[5];
-                    const int32_t lref = __float_as_int(l0.w), rref = __float_as_int(r0.w);
-                    if (lref >= a.n - 1 || rref >= a.n - 1 || ~lref >= a.n || ~rref >= a.n) break;
-                    if (a.counters) {   // per-lane path: count directly
-                        const unsigned long long nl = (lref < 0) + (rref < 0);
-                        add_counters(a, 1, nl, nl, 0);
-                    }
-                    if (lref < 0) {
-                        const unsigned long long c = pack_best(leaf_dist2<kTri>(p, l0, l1, l2), __float_as_int(l1.w));
-                        if (c < seeded) seeded = c;
-                    }
-                    if (rref < 0) {
-                        const unsigned long long c = pack_best(leaf_dist2<kTri>(p, r0, r1, r2), __float_as_int(r1.w));
-                        if (c < seeded) seeded = c;
-                    }
-                    const float dl = lref >= 0 ? child_bound<kTri>(p, dq, l0, l1, l2) : INFINITY;
-                    const float dr = rref >= 0 ? child_bound<kTri>(p, dq, r0, r1, r2) : INFINITY;
-                    node = (lref >= 0 && dl <= dr) ? lref : (rref >= 0 ? rref : -1);
-                }
-            }
-            if (own && seeded < none) S.best[lane] = seeded;
-            const f3 rlo = f3{a.root[0], a.root[1], a.root[2]};
-            const f3 rhi = f3{a.root[4], a.root[5], a.root[6]};
-            const float rd = own ? box_dist2(p, rlo, rhi) : INFINITY;
-            const float rb = (seeded < none ? __uint_as_float(static_cast<uint32_t>(seeded >> 32)) : a.maxd2);
-            const bool push = own && rd <= prune_bound(rb, qnorm1(p));
-            const uint64_t bm = __ballot(push);
-            if (push) {
-                const int pos = __popcll(bm & lt);
-                S.node[pos] = 0;
-                S.dist[pos] = rd;
-                S.slot[pos] = static_cast<uint8_t>(lane);
-            }
-            sp = __popcll(bm);
+        if (sp >= 0) {
+            spin = 0;
+            if (sp > 0) run_stack<kTri, M>(a, L, self, owner & (kBatchWaves - 1), sp, stats);
+            if (owner >= kBatchWaves && lane == 0) lds_add(&mail.outstanding[owner & (kBatchWaves - 1)], -1);
         }
-        run_stack<kTri, M>(a, L, self, self, sp, stats);
         // chunks given away must be finished before the results are final
-        wait_helping<kTri, M>(a, L, self, stats, [&]() { return uniform(lds_load(&mail.outstanding[self])) == 0; });
-        if (own) {
-            const unsigned long long b = S.best[lane];
-            write_result_id<kTri>(a, qid, p, static_cast<int32_t>(b & 0xffffffffull),
-                                  __uint_as_float(static_cast<uint32_t>(b >> 32)));
+        if (open && uniform(lds_load(&mail.outstanding[self])) == 0) {
+            const int64_t qid = lane < nb ? query_at(a, qb + lane) : -1;
+            if (qid >= 0) finish_query<kTri, M>(a, S, lane, qid);
+            if (a.counters) stats.nq += __popcll(__ballot(qid >= 0));
+            open = false;
+            between = kHelpBetween;
+            qb = next(qb);
+            continue;
         }
-        if (a.counters) stats.nq += __popcll(__ballot(own));
-        // work already started in the workgroup goes before a new batch
-        if (kHelpBetween)
-            while (help_once<kTri, M>(a, L, self, stats)) {
+        if (open || qb < q_end) {
+            if (sp >= 0) continue;
+        } else {
+            if (!told) {
+                if (lane == 0) lds_add(&mail.done, 1);
+                told = true;
             }
+            if (uniform(lds_load(&mail.done)) == kBatchWaves) break;
+            if (sp >= 0) continue;
+        }
+        if (++spin > kIdleSpinLimit) {
+            if (lane == 0) atomicOr(a.status, 16);
+            break;
+        }
+        __builtin_amdgcn_s_sleep(2);
     }
-    if (lane == 0) lds_add(&mail.done, 1);
-    wait_helping<kTri, M>(a, L, self, stats, [&]() { return uniform(lds_load(&mail.done)) == kBatchWaves; });
     if (a.counters && lane == 0) add_counters(a, stats.exp, stats.lbox, stats.lex, stats.nq);
 }
 
