@@ -41,7 +41,8 @@ constexpr int kBatchWaves = 4;          // waves per workgroup of the batch kern
 constexpr int kBatchCap = 320;          // stack entries before the pop width shrinks
 constexpr int kPopNodes = 32;           // nodes a round pops: a pair of lanes each
 constexpr int kBatchAlloc = kBatchCap + 64;
-constexpr int kLeafNarrow = 8;         // stack entries below which waiting leaves are tested at once
+constexpr int kLeafWait = 32;           // waiting leaves that are tested together
+constexpr int kLeafNarrow = 8;          // stack entries below which waiting leaves are tested at once
 
 struct QueryArgs {
     const float4 *nodes;                // [n-1][6]
