@@ -510,7 +510,7 @@ def run_track(args):
     ops = OPS_EXPANSION * n_exp + OPS_LEAF_BOUND * n_lbox + OPS_EXACT * n_lex
     if ph["query"] >= ph["rebuild"]:
         achieved = ops / (ph["query"] * 1e-3) / 1e12
-        kname = "knn_lane_kernel" if args.knn > 1 else "traverse_batch_kernel"
+        kname = "knn_batch_kernel" if args.knn > 1 else "traverse_batch_kernel"
         roofline = {"bound": "alu", "kernel": f"{kname} (tracked points onto the frame's mesh)",
                     "achieved": round(achieved, 4), "peak": FP32_VECTOR_NONPACKED_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(achieved / FP32_VECTOR_NONPACKED_TFLOPS, 5), "traffic": None,

@@ -383,7 +383,7 @@ mg_status mg_closest_point_bruteforce(const float *verts, int32_t n_verts, const
  * point [3][n_queries] or NULL (the query itself when no face qualifies).
  * counters: NULL or a device uint64 [4] accumulating node expansions, leaf
  * bound tests, exact leaf tests and queries (as mg_query_options.counters).
- * One query per lane; k = 1 gives the single closest point (unweighted). */
+ * k = 1 gives the single closest point (unweighted). */
 mg_status mg_knn_surface_query(const void *bvh, size_t bvh_bytes, int32_t n_prims, const float *verts,
                                int32_t n_verts, const float *queries, int32_t n_queries, int32_t k,
                                float eps, float max_dist2, int32_t *face_k, float *dist2_k, float *point,

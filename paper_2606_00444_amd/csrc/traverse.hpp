@@ -66,6 +66,8 @@ struct QueryArgs {
     uint32_t *queue;                    // batch kernel: dynamic batch counter (zeroed before launch) or nullptr
     const int32_t *hint;                // [nq] original id to start each query from, or nullptr
     int coherent;                       // face ids stored and hints loaded device-coherent (batched form)
+    int k;                              // faces kept per query (the k-nearest form; face and dist2 are then [k][nq])
+    float eps;                          // its weights are 1 / (distance + eps)
 };
 
 // The face id of a result: with `coherent`, a relaxed device-scope store, which the
@@ -280,12 +282,12 @@ __device__ __forceinline__ StackEntry make_entry(float bound, uint32_t slot, uin
     return (static_cast<StackEntry>((__float_as_uint(bound) & ~kSlotMask) | slot) << 32) | node;
 }
 
-template <int M>
+template <int M, int K>
 struct WaveStack {
     static_assert(M <= kSlotMask + 1, "an entry holds its query's slot in five bits");
     StackEntry e[kBatchAlloc];
     float4 q[M];                        // per query of the batch: the point, and prune_bound of its best
-    unsigned long long best[M];         // (d^2 bits, original id)
+    unsigned long long best[M][K];      // the nearest faces, sorted: (d^2 bits, original id)
     uint32_t code[M];                   // where the best face lies (a record slot); only a guess, see leaf_of
 };
 
@@ -298,9 +300,9 @@ struct WaveMail {
     int32_t outstanding[kBatchWaves];   // chunks of each wave's batch held elsewhere
 };
 
-template <int M>
+template <int M, int K = 1>
 struct BatchLds {
-    WaveStack<M> st[kBatchWaves];
+    WaveStack<M, K> st[kBatchWaves];
     WaveMail mail;
 };
 
@@ -348,11 +350,38 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_wave_barrier();
 }
 
+// Puts `cand` into a query's k nearest, sorted by (d^2, id): each place keeps the
+// smaller of its own and the one coming in and hands the larger on, so lanes and
+// waves may insert at once and every element but the dropped ones stays; a face
+// tested twice meets itself and stops.
+template <int K>
+__device__ __forceinline__ void insert_nearest(unsigned long long *best, int k, unsigned long long cand) {
+#pragma unroll
+    for (int j = 0; j < K; ++j) {
+        if (j >= k) break;
+        const unsigned long long old = atomicMin(best + j, cand);
+        if (old == cand) break;
+        if (old > cand) cand = old;
+    }
+}
+
+// Lowers the prune bounds of wave `O`'s M queries to their k-th nearest.
+template <int M, int K>
+__device__ __forceinline__ void lower_bounds(WaveStack<M, K> &O, int k, int lane) {
+    wave_sync();                              // the insertions of every lane
+    if (lane < M) {
+        const float4 q = O.q[lane];
+        const float d2 = __uint_as_float(static_cast<uint32_t>(O.best[lane][k - 1] >> 32));
+        atomicMin(reinterpret_cast<uint32_t *>(&O.q[lane].w),
+                  __float_as_uint(prune_bound(d2, qnorm1(f3{q.x, q.y, q.z}))));
+    }
+}
+
 // Exact tests of the last `cnt` (<= 64) of wave `self`'s lc waiting leaves, one
 // per lane.  A face at most as far as its query's best lowers the best and the
 // prune bound (both by LDS atomics: other waves may hold chunks of the batch).
-template <bool kTri, int M>
-__device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<M> &S, WaveStack<M> &O, int lc, int cnt,
+template <bool kTri, int M, int K>
+__device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<M, K> &S, WaveStack<M, K> &O, int lc, int cnt,
                                            BatchStats &stats) {
     const int lane = threadIdx.x % 64;
     bool act = lane < cnt;
@@ -368,12 +397,15 @@ __device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<M> &S, 
         const float d2 = leaf_dist2<kTri>(p, f0, f1, f2);
         if (d2 <= q.w) {
             const unsigned long long cand = pack_best(d2, __float_as_int(f1.w));
-            if (cand < atomicMin(&O.best[slot], cand)) {
+            if (K > 1) {
+                insert_nearest<K>(O.best[slot], a.k, cand);
+            } else if (cand < atomicMin(&O.best[slot][0], cand)) {
                 atomicMin(reinterpret_cast<uint32_t *>(&O.q[slot].w), __float_as_uint(prune_bound(d2, qnorm1(p))));
                 O.code[slot] = code;
             }
         }
     }
+    if (K > 1) lower_bounds<M, K>(O, a.k, lane);
     return lc - cnt;
 }
 
@@ -394,12 +426,12 @@ __device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<M> &S, 
 // 50,000 hinted queries on 40,000 faces (batches of 16): 117 -> 62 us with the
 // joint bound of child_bound, 55% of the time issuing VALU; 1M on 500,000 faces:
 // 5,980 -> 1,340 us, 80% issuing and 6.6 TB/s of cache-line misses.
-template <bool kTri, int M>
-__device__ void run_stack(const QueryArgs &a, BatchLds<M> &L, int self, int owner, int sp, BatchStats &stats) {
+template <bool kTri, int M, int K>
+__device__ void run_stack(const QueryArgs &a, BatchLds<M, K> &L, int self, int owner, int sp, BatchStats &stats) {
     const int lane = threadIdx.x % 64;
     const uint32_t n_nodes = static_cast<uint32_t>(a.n - 1), odd = lane & 1;
-    WaveStack<M> &S = L.st[self];
-    WaveStack<M> &O = L.st[owner];
+    WaveStack<M, K> &S = L.st[self];
+    WaveStack<M, K> &O = L.st[owner];
     WaveMail &mail = L.mail;
     int lc = 0;                               // waiting leaves
     // the stack never exceeds kBatchCap + 62: a round of width k pushes at most
@@ -412,7 +444,7 @@ __device__ void run_stack(const QueryArgs &a, BatchLds<M> &L, int self, int owne
     for (int64_t round = 0; sp + lc > 0 && round < max_rounds; ++round) {
         wave_sync();                          // the previous round's pushes, or the entries handed in
         if (lc >= kLeafWait || (lc > 0 && (sp < kLeafNarrow || sp + lc > kBatchCap - 2 * kPopNodes))) {
-            lc = test_leaves<kTri, M>(a, S, O, lc, lc < 64 ? lc : 64, stats);
+            lc = test_leaves<kTri, M, K>(a, S, O, lc, lc < 64 ? lc : 64, stats);
             wave_sync();
             if (sp == 0) continue;
         }
@@ -477,8 +509,8 @@ __device__ void run_stack(const QueryArgs &a, BatchLds<M> &L, int self, int owne
 
 // Takes the mailbox's chunk, if there is one, onto wave `self`'s (empty) stack:
 // its size, and the wave whose batch it belongs to; -1 if there is none.
-template <int M>
-__device__ __forceinline__ int take_chunk(const QueryArgs &a, BatchLds<M> &L, int self, int &owner) {
+template <int M, int K>
+__device__ __forceinline__ int take_chunk(const QueryArgs &a, BatchLds<M, K> &L, int self, int &owner) {
     const int lane = threadIdx.x % 64;
     WaveMail &mail = L.mail;
     int got = 0;
@@ -602,8 +634,8 @@ __device__ __forceinline__ unsigned long long seed_descent(const QueryArgs &a, f
 // Starts a wave's batch [qb, qb + nb): points, starting bests (a hint's
 // distance, else the seed descent's, else max_dist2) and the root on the stack.
 // Returns the stack's size.
-template <bool kTri, int M>
-__device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M> &S, int64_t qb, int nb) {
+template <bool kTri, int M, int K>
+__device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M, K> &S, int64_t qb, int nb) {
     constexpr int kLanes = M <= 16 ? 4 : 2;       // lanes of a query
     const int lane = threadIdx.x % 64, i = lane / kLanes;
     const unsigned long long none = pack_best(a.maxd2, INT_MAX);
@@ -621,6 +653,34 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M> &S, 
             const unsigned long long c = pack_best(single_leaf_dist2<kTri>(a, p), a.prim[0]);
             if (c < none) best = c;
         }
+    } else if (K > 1 && a.n > 1) {
+        // the seed descent's leaf and its neighbours along the leaf order: k faces,
+        // so the farthest bounds the k-th nearest from the start
+        if (lead)
+#pragma unroll
+            for (int j = 0; j < K; ++j) S.best[i][j] = none;
+        wave_sync();
+        uint32_t at;
+        (void)seed_descent<kTri, kLanes>(a, p, own, at);
+        if (own && at < 2 * static_cast<uint32_t>(a.n - 1)) {
+            const int64_t leaf = ~static_cast<int64_t>(__float_as_int(a.nodes[3 * static_cast<uint64_t>(at)].w));
+            int64_t first = leaf - K / 2 < a.n - K ? leaf - K / 2 : a.n - K;
+            if (first < 0) first = 0;
+#pragma unroll
+            for (int u = 0; u < (K + kLanes - 1) / kLanes; ++u) {
+                const int64_t l = first + lane % kLanes + u * kLanes;
+                if (l >= a.n || lane % kLanes + u * kLanes >= K) continue;
+                const int32_t code_l = a.leaf_parent[l];
+                if (code_l < 0 || (code_l >> 1) >= a.n - 1) continue;
+                int32_t id;
+                const float d2 = slot_dist2<kTri>(a, p, code_l, id);
+                insert_nearest<K>(S.best[i], a.k, pack_best(d2, id));
+            }
+        }
+        wave_sync();
+        rd = box_dist2(p, f3{a.root[0], a.root[1], a.root[2]}, f3{a.root[4], a.root[5], a.root[6]});
+        if (own) pb = prune_bound(__uint_as_float(static_cast<uint32_t>(S.best[i][a.k - 1] >> 32)), qnorm1(p));
+        push = lead && rd <= pb;
     } else if (a.n > 1) {
         // a hinted primitive's distance starts the query; without one, the seed descent
         bool hinted = false;
@@ -656,7 +716,10 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M> &S, 
     }
     if (lead) {
         S.q[i] = make_float4(p.x, p.y, p.z, pb);
-        S.best[i] = best;
+        if (K == 1 || a.n <= 1) S.best[i][0] = best;
+        if (a.n <= 1)
+#pragma unroll
+            for (int j = 1; j < K; ++j) S.best[i][j] = none;
         S.code[i] = code;
     }
     const uint64_t bm = __ballot(push);
@@ -669,8 +732,8 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M> &S, 
 // the best may be another face's (two waves lowering one best race on it), so
 // its id is checked, and the face's slot is looked up where they differ.
 template <bool kTri, int M>
-__device__ __forceinline__ void finish_query(const QueryArgs &a, const WaveStack<M> &S, int lane, int64_t qid) {
-    const unsigned long long b = S.best[lane];
+__device__ __forceinline__ void finish_query(const QueryArgs &a, const WaveStack<M, 1> &S, int lane, int64_t qid) {
+    const unsigned long long b = S.best[lane][0];
     const float4 q = S.q[lane];
     const f3 p = f3{q.x, q.y, q.z};
     const int32_t id = static_cast<int32_t>(b & 0xffffffffull);
@@ -701,6 +764,69 @@ __device__ __forceinline__ void finish_query(const QueryArgs &a, const WaveStack
     write_face(a, qid, p, id, xyz(f0), xyz(f1), xyz(f2));
 }
 
+// Final records of a batch of the k-nearest form, a lane per query and place:
+// the faces and distances, and the closest points combined with
+// inverse-distance weights 1 / (d + eps) (the weighted nearest-neighbour
+// NearestSurface of Sec. 3.3); a face at distance 0 gives its own point.
+template <int M, int K>
+__device__ __forceinline__ void finish_nearest(const QueryArgs &a, const WaveStack<M, K> &S, int64_t qb, int nb) {
+    static_assert(M * K <= 64, "a lane per query and place");
+    const int lane = threadIdx.x % 64, i = lane / K < M ? lane / K : 0, j = lane % K;
+    const bool own = lane < M * K && i < nb;
+    const int64_t qid = own ? query_at(a, qb + i) : -1;
+    const float4 q = S.q[i];
+    const f3 p = f3{q.x, q.y, q.z};
+    const unsigned long long b = S.best[i][j];
+    const int32_t id = static_cast<int32_t>(b & 0xffffffffull);
+    bool ok = qid >= 0 && j < a.k && id >= 0 && id < a.n;
+    f3 c = f3{0.0f, 0.0f, 0.0f};
+    float d2 = 0.0f;
+    if (ok) {
+        f3 A = c, B = c, C = c;
+        if (a.n == 1) {
+            A = vload(a.verts, a.nv, a.leaf_faces[0]);
+            B = vload(a.verts, a.nv, a.leaf_faces[1]);
+            C = vload(a.verts, a.nv, a.leaf_faces[2]);
+        } else {
+            const int64_t code = slot_of(a, id);
+            ok = code >= 0;
+            if (ok) {
+                const float4 *rec = a.nodes + 3 * code;
+                A = xyz(rec[0]); B = xyz(rec[1]); C = xyz(rec[2]);
+            } else {
+                atomicOr(a.status, 16);
+            }
+        }
+        float w1, w2;
+        d2 = tri_closest(p, A, B, C, w1, w2);
+        c = tri_point(A, B, C, w1, w2);
+    }
+    if (qid >= 0 && j < a.k) {
+        a.face[j * a.nq + qid] = ok ? id : -1;
+        if (a.dist2) a.dist2[j * a.nq + qid] = ok ? __uint_as_float(static_cast<uint32_t>(b >> 32)) : INFINITY;
+    }
+    if (!a.point) return;
+    const float w = 1.0f / (sqrtf(d2) + a.eps);
+    f3 num = f3{0.0f, 0.0f, 0.0f}, on = p;
+    float den = 0.0f;
+    bool hit = false;                         // a face at distance 0: its point, unweighted
+#pragma unroll
+    for (int u = 0; u < K; ++u) {             // in the order of the places, in every lane of the query
+        const int from = lane - j + u;
+        const f3 cu = f3{__shfl(c.x, from), __shfl(c.y, from), __shfl(c.z, from)};
+        const float wu = __shfl(w, from), d2u = __shfl(d2, from);
+        if (__shfl(static_cast<int>(ok), from)) {
+            if (d2u == 0.0f && !hit) {
+                hit = true;
+                on = cu;
+            }
+            num = num + wu * cu;
+            den += wu;
+        }
+    }
+    if (qid >= 0 && j == 0) store3(a.point, a.nq, qid, hit ? on : (den > 0.0f ? (1.0f / den) * num : p));
+}
+
 // The workgroup's kBatchWaves waves process the query batches [qb, qb + M)
 // below q_end (positions in the processing order): wave w takes qb = start +
 // w M, then steps by stride or, with a queue, M times the batch numbers it
@@ -712,11 +838,11 @@ __device__ __forceinline__ void finish_query(const QueryArgs &a, const WaveStack
 // every other form, and the plain kernels with it, matched the all-faces kernel
 // exactly.  Each turn of the loop runs one stack, the wave's own or a chunk, so
 // the rounds are compiled once.
-template <bool kTri, int M, bool kHelpBetween = true>
-__device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, int64_t q_end, BatchLds<M> &L) {
+template <bool kTri, int M, bool kHelpBetween = true, int K = 1>
+__device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, int64_t q_end, BatchLds<M, K> &L) {
     const int lane = threadIdx.x % 64;
     const int self = uniform(static_cast<int>(threadIdx.x / 64));
-    WaveStack<M> &S = L.st[self];
+    WaveStack<M, K> &S = L.st[self];
     WaveMail &mail = L.mail;
     BatchStats stats;
     if (threadIdx.x == 0) {
@@ -738,10 +864,10 @@ __device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, in
     bool told = false;                        // this wave's last batch is counted in mail.done
     for (int spin = 0;;) {
         int owner = -1, sp = -1;
-        if (open || between || qb >= q_end) sp = take_chunk<M>(a, L, self, owner);
+        if (open || between || qb >= q_end) sp = take_chunk<M, K>(a, L, self, owner);
         const int nb = static_cast<int>(q_end - qb < M ? q_end - qb : M);
         if (sp < 0 && !open && qb < q_end) {
-            sp = start_batch<kTri, M>(a, S, qb, nb);
+            sp = start_batch<kTri, M, K>(a, S, qb, nb);
             owner = self;
             open = true;
             between = false;
@@ -750,13 +876,14 @@ __device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, in
         }
         if (sp >= 0) {
             spin = 0;
-            if (sp > 0) run_stack<kTri, M>(a, L, self, owner & (kBatchWaves - 1), sp, stats);
+            if (sp > 0) run_stack<kTri, M, K>(a, L, self, owner & (kBatchWaves - 1), sp, stats);
             if (owner >= kBatchWaves && lane == 0) lds_add(&mail.outstanding[owner & (kBatchWaves - 1)], -1);
         }
         // chunks given away must be finished before the results are final
         if (open && uniform(lds_load(&mail.outstanding[self])) == 0) {
             const int64_t qid = lane < nb ? query_at(a, qb + lane) : -1;
-            if (qid >= 0) finish_query<kTri, M>(a, S, lane, qid);
+            if constexpr (K > 1) finish_nearest<M, K>(a, S, qb, nb);
+            else if (qid >= 0) finish_query<kTri, M>(a, S, lane, qid);
             if (a.counters) stats.nq += __popcll(__ballot(qid >= 0));
             open = false;
             between = kHelpBetween;

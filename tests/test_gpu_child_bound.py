@@ -1,0 +1,84 @@
+"""The traversals against the all-faces kernel where their lower bounds, batches and
+k-nearest lists can go wrong: meshes far from the origin and at extreme scales (the
+rounding margins of the slab and ball bound), needle and flat boxes, face and query
+counts at the edges of the batches, and lists longer than the mesh."""
+
+import numpy as np
+import pytest
+import torch
+
+from gpu_helpers import need_gpu, dev, check_knn_result
+from synth.meshes import icosphere, uv_sphere
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def device():
+    return need_gpu()
+
+
+def _mesh(shape, scale, offset, rng):
+    v, f = uv_sphere(24, 17) if shape != "needle" else icosphere(3)
+    v = v + 0.02 * rng.normal(size=v.shape)
+    v = v * {"ball": (1, 1, 1), "flat": (1, 1, 1e-4), "needle": (1, 1e-3, 1e-3)}[shape]
+    V = (scale * (v + offset)).astype(np.float32).T
+    lo, hi = V.min(1, keepdims=True), V.max(1, keepdims=True)
+    mid = 0.5 * (lo + hi)
+    near = V[:, ::7] + (1e-3 * (hi - lo)) * rng.normal(size=(3, V[:, ::7].shape[1]))
+    Q = np.concatenate([mid + 1e-3 * (hi - lo) * rng.normal(size=(3, 40)),        # nearly equidistant from many faces
+                        rng.uniform(lo - (hi - lo), hi + (hi - lo), size=(3, 400)), near], axis=1)
+    return np.ascontiguousarray(V), np.ascontiguousarray(f.T.astype(np.int32)), Q.astype(np.float32)
+
+
+@pytest.mark.parametrize("shape", ["ball", "flat", "needle"])
+@pytest.mark.parametrize("scale,offset", [(1.0, 0.0), (1.0, 200.0), (1e-6, 3.0), (1e6, 0.0), (1.0, 5000.0)])
+def test_traversals_match_all_faces(device, shape, scale, offset):
+    """Faces equal, distances bitwise: the bound may never drop a face that the all-faces
+    kernel finds nearest (ties of the float32 distance to the lowest id in both)."""
+    import paper_2606_00444_amd as mg
+    rng = np.random.default_rng(7)
+    V, F, Q = (dev(x, device) for x in _mesh(shape, scale, offset, rng))
+    ref = mg.closest_point_bruteforce(V, F, Q, normal=True)
+    bvh = mg.lbvh_build(V, F)
+    for kw in ({}, {"kernel": "lane"}, {"kernel": "batch", "batch": 16, "seed": True},
+               {"kernel": "batch", "batch": 32, "seed": True}, {"kernel": "batch", "batch": 16},
+               {"hint": ref["face"].roll(1)}, {"hint": ref["face"]}):
+        r = mg.closest_point_query(bvh, V, Q, normal=True, **kw)
+        assert torch.equal(r["dist2"], ref["dist2"]), kw
+        assert torch.equal(r["face"], ref["face"]), kw
+        for key in ("point", "bary", "normal"):
+            assert torch.equal(r[key], ref[key]), (kw, key)
+
+
+@pytest.mark.parametrize("nf", [1, 2, 3, 7, 9, 64, 65])
+@pytest.mark.parametrize("k", [2, 3, 5, 8])
+def test_knn_small_meshes_and_ragged_counts(device, nf, k):
+    """Fewer faces than places, one to two wave-fulls of faces, 1 to 70 queries."""
+    import paper_2606_00444_amd as mg
+    rng = np.random.default_rng(100 * nf + k)
+    c = rng.uniform(-1, 1, size=(nf, 1, 3))
+    V = (c + 0.2 * rng.normal(size=(nf, 3, 3))).reshape(-1, 3).T.astype(np.float32)
+    F = np.arange(3 * nf, dtype=np.int32).reshape(nf, 3).T.copy()
+    Vd, Fd = dev(np.ascontiguousarray(V), device), dev(F, device)
+    bvh = mg.lbvh_build(Vd, Fd)
+    for nq in (1, 5, 70):
+        Q = rng.uniform(-1.5, 1.5, size=(3, nq)).astype(np.float32)
+        r = mg.knn_surface_query(bvh, Vd, dev(Q, device), k=k, eps=1e-6)
+        check_knn_result(r, V, F, Q, k, 1e-6, float("inf"))
+
+
+@pytest.mark.parametrize("k", [1, 2, 4, 8])
+def test_knn_does_not_depend_on_the_batch(device, k):
+    """The queries per wave follow the query count: the same queries alone and among 33,000."""
+    import paper_2606_00444_amd as mg
+    rng = np.random.default_rng(5)
+    V, F, _ = _mesh("ball", 1.0, 0.0, rng)
+    Q = rng.uniform(-1.2, 1.2, size=(3, 33000)).astype(np.float32)
+    Vd, Fd, Qd = dev(V, device), dev(F, device), dev(Q, device)
+    bvh = mg.lbvh_build(Vd, Fd)
+    whole = mg.knn_surface_query(bvh, Vd, Qd, k=k, eps=1e-6, max_dist2=0.3)
+    for n in (333, 4100, 8200, 16400):
+        part = mg.knn_surface_query(bvh, Vd, Qd[:, :n].contiguous(), k=k, eps=1e-6, max_dist2=0.3)
+        for key in ("face", "dist2", "point"):
+            assert torch.equal(part[key], whole[key][:, :n]), (n, key)
