@@ -7,6 +7,7 @@ arithmetic happens in the HIP kernels; nothing here computes on the host.
 """
 
 import ctypes
+import functools
 import math
 
 import torch
@@ -22,8 +23,15 @@ __all__ = [
 ]
 
 
+# Marshalling is on every call's path: 20 arguments checked and passed to two library
+# calls took longer than the kernels of a 500-face frame.  Addresses and the stream are
+# passed as plain integers (ctypes converts them to pointers, 0 to NULL), and functions
+# are looked up in the library once.
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The handle of torch's current stream on the current device."""
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
 
 def _ptr(t):
@@ -33,13 +41,13 @@ def _ptr(t):
         raise ValueError("expected a device tensor")
     if not t.is_contiguous():
         raise ValueError("expected a contiguous tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _f32(t, shape0=None, name="tensor"):
     if t is None:
         return None
-    if t.dtype != torch.float32:
+    if t.dtype is not torch.float32:
         raise TypeError(f"{name} must be float32")
     if shape0 is not None and (t.dim() != 2 or t.shape[0] != shape0):
         raise ValueError(f"{name} must be [{shape0}][n], got {tuple(t.shape)}")
@@ -49,7 +57,7 @@ def _f32(t, shape0=None, name="tensor"):
 def _i32(t, name="tensor"):
     if t is None:
         return None
-    if t.dtype != torch.int32:
+    if t.dtype is not torch.int32:
         raise TypeError(f"{name} must be int32")
     return t
 
@@ -57,14 +65,20 @@ def _i32(t, name="tensor"):
 def _f64(t, name="tensor"):
     if t is None:
         return None
-    if t.dtype != torch.float64:
+    if t.dtype is not torch.float64:
         raise TypeError(f"{name} must be float64")
     return t
 
 
+@functools.lru_cache(maxsize=None)          # one entry per library function
+def _fn(name):
+    return getattr(_lib.load(), name)
+
+
 def _call(name, *args):
-    lib = _lib.load()
-    _lib.check(name, getattr(lib, name)(*args))
+    code = _fn(name)(*args)
+    if code:
+        _lib.check(name, code)
 
 
 def version():
@@ -143,16 +157,22 @@ def mesh_gaussian_update_backward(verts, faces, gface, bary, q_local, log_scale,
     return g_verts
 
 
+@functools.lru_cache(maxsize=64)            # pure functions of two integers
 def _layout(n, kind):
     L = LbvhLayout()
     _call("mg_lbvh_layout_query", n, kind, ctypes.byref(L))
     return L
 
 
-def lbvh_workspace_bytes(n_prims, kind=MG_PRIM_TRIANGLES):
+@functools.lru_cache(maxsize=64)
+def _workspace(n, kind):
     ws = ctypes.c_size_t()
-    _call("mg_lbvh_workspace_size", int(n_prims), int(kind), ctypes.byref(ws))
+    _call("mg_lbvh_workspace_size", n, kind, ctypes.byref(ws))
     return ws.value
+
+
+def lbvh_workspace_bytes(n_prims, kind=MG_PRIM_TRIANGLES):
+    return _workspace(int(n_prims), int(kind))
 
 
 def lbvh_bytes(n_prims, kind=MG_PRIM_TRIANGLES):
@@ -404,7 +424,7 @@ _reduce_ws = {}
 
 
 def _rws(device):
-    key = str(device)
+    key = device
     if key not in _reduce_ws:
         sz = ctypes.c_size_t()
         _call("mg_reduce_workspace_size", 0, ctypes.byref(sz))
