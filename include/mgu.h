@@ -531,7 +531,8 @@ typedef struct mg_batch_scene {
     const float *log_scale;     /* [3][n_gauss] */
     const float *queries;       /* [3][n_queries] */
     int32_t n_queries;
-    int32_t batch;              /* this scene's queries per wave (1, 2, 4, 8, 16); 0: the plan's */
+    int32_t batch;              /* this scene's queries per wave at least (1, 2, 4, 8, 16; raised while
+                                   a tile still gives each of four waves a batch); 0: the plan's */
     int32_t seed;               /* this scene's seed descent: 0 off, 1 on, -1: the plan's */
     int32_t query_tile;         /* this scene's queries per work item, a multiple of 4 * its
                                    batch; 0: the plan's */
@@ -553,7 +554,7 @@ typedef struct mg_batch_scene {
 /* Plan-wide defaults; a scene's own batch / seed / query_tile fields override
  * them (the autotuner picks the traversal per scene). */
 typedef struct mg_batch_options {
-    int32_t batch;              /* queries per wave of the batch traversal: 1, 2, 4, 8, 16 (0: 4) */
+    int32_t batch;              /* least queries per wave of the batch traversal: 1, 2, 4, 8, 16 (0: 4) */
     int32_t seed;               /* greedy seed descent: 0 off, otherwise on */
     int32_t gauss_tile;         /* Gaussians per work item, multiple of 256 (0: 2048) */
     int32_t query_tile;         /* queries per work item, multiple of 4 * batch (0: 256) */
