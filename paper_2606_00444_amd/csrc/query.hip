@@ -130,7 +130,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_e
 
 // ----------------------------------------------------------------- k nearest
 // The batch kernel with the K best per query (k <= K kept), the children pruned
-// against the k-th.  20,002 queries, k = 4, on 46,000 faces: 268 -> 70 us
+// against the k-th.  20,002 queries, k = 4, on 46,000 faces: 268 -> 84 us
 // against one query per lane, depth-first, where a wave waits for its longest walk.
 template <int M, int K>
 __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_eu(4))) void knn_batch_kernel(QueryArgs a) {

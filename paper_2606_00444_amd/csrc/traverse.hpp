@@ -39,7 +39,7 @@ __device__ __forceinline__ float qnorm1(f3 q) { return (fabsf(q.x) + fabsf(q.y))
 
 constexpr int kBatchWaves = 4;          // waves per workgroup of the batch kernel
 constexpr int kBatchCap = 320;          // stack entries before the pop width shrinks
-constexpr int kPopNodes = 32;           // nodes a round pops: a pair of lanes each
+constexpr int kPopNodes = 32;           // nodes a triangle round pops: a pair of lanes each
 constexpr int kBatchAlloc = kBatchCap + 64;
 constexpr int kLeafWait = 32;           // waiting leaves that are tested together
 constexpr int kLeafNarrow = 8;          // stack entries below which waiting leaves are tested at once
@@ -154,7 +154,7 @@ __device__ __forceinline__ float child_bound(f3 q, float dq, float4 c0, float4 c
     const float dx = q.x - __builtin_amdgcn_fmed3f(q.x, c0.x, c1.x);
     const float dy = q.y - __builtin_amdgcn_fmed3f(q.y, c0.y, c1.y);
     const float dz = q.z - __builtin_amdgcn_fmed3f(q.z, c0.z, c1.z);
-    const float bd = dx * dx + dy * dy + dz * dz;
+    const float bd = fdot(f3{dx, dy, dz}, f3{dx, dy, dz});
     if (!kTri) return bd;
     const float s = c2.x * q.x + c2.y * q.y + c2.z * q.z;
     const float g = fmaxf(fmaxf(c1.w - s, s - c2.w) - dq, 0.0f);
@@ -409,6 +409,55 @@ __device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<M, K> &
     return lc - cnt;
 }
 
+// A round over a point BVH: up to 64 nodes, one per lane with both children.  A
+// leaf's box is its point, so its bound is its exact squared distance and the
+// round settles it; with a box test this cheap, a child per lane only doubles
+// the rest of the round (100,000 nearest points of 100,000: 75-87 -> 54-70 us).
+template <int M, int K>
+__device__ __forceinline__ void point_round(const QueryArgs &a, WaveStack<M, K> &S, WaveStack<M, K> &O, uint32_t n_nodes,
+                                            int take, int &sp, BatchStats &stats) {
+    const int lane = threadIdx.x % 64;
+    const bool pop = lane < take;
+    const StackEntry en = S.e[pop ? sp - 1 - lane : 0];
+    sp -= take;
+    const uint32_t hi = static_cast<uint32_t>(en >> 32), node = static_cast<uint32_t>(en), slot = hi & kSlotMask;
+    const float4 q = O.q[slot];
+    const f3 p = f3{q.x, q.y, q.z};
+    const bool act = pop && node < n_nodes && __uint_as_float(hi & ~kSlotMask) <= q.w;
+    float4 l0{}, l1{}, r0{}, r1{};
+    if (act) {
+        const float4 *rec = a.nodes + 6 * static_cast<uint64_t>(node);
+        l0 = rec[0]; l1 = rec[1]; r0 = rec[3]; r1 = rec[4];
+    }
+    const int32_t lref = __float_as_int(l0.w), rref = __float_as_int(r0.w);
+    const float dl = child_bound<false>(p, 0.0f, l0, l1, l1), dr = child_bound<false>(p, 0.0f, r0, r1, r1);
+    const bool il = act && dl <= q.w, ir = act && dr <= q.w;
+    const bool pl = il && lref >= 0, pr = ir && rref >= 0;
+    unsigned long long cand = ~0ull;
+    if (il && lref < 0) cand = pack_best(dl, __float_as_int(l1.w));
+    if (ir && rref < 0) {
+        const unsigned long long c = pack_best(dr, __float_as_int(r1.w));
+        if (c < cand) cand = c;
+    }
+    if (cand != ~0ull && cand < atomicMin(&O.best[slot][0], cand))
+        atomicMin(reinterpret_cast<uint32_t *>(&O.q[slot].w),
+                  __float_as_uint(prune_bound(__uint_as_float(static_cast<uint32_t>(cand >> 32)), qnorm1(p))));
+    const uint64_t bl = __ballot(pl), br = __ballot(pr);
+    if (a.counters) {
+        stats.exp += __popcll(__ballot(act));
+        stats.lbox += __popcll(__ballot(act && lref < 0)) + __popcll(__ballot(act && rref < 0));
+        stats.lex += __popcll(__ballot(il && lref < 0)) + __popcll(__ballot(ir && rref < 0));
+    }
+    if (pl || pr) {                           // nearer child on top of the stack
+        const int off = sp + rank_below(bl) + rank_below(br);
+        const bool left_near = dl <= dr, first_left = pl && !(pr && left_near);
+        S.e[off] = make_entry(first_left ? dl : dr, slot, static_cast<uint32_t>(first_left ? lref : rref));
+        if (pl && pr)
+            S.e[off + 1] = make_entry(left_near ? dl : dr, slot, static_cast<uint32_t>(left_near ? lref : rref));
+    }
+    sp += __popcll(bl) + __popcll(br);
+}
+
 // Rounds over wave `self`'s stack (sp entries) until it is empty.  Entries
 // belong to the batch of wave `owner`: its query points and bests.
 //
@@ -463,12 +512,17 @@ __device__ void run_stack(const QueryArgs &a, BatchLds<M, K> &L, int self, int o
                 }
             }
         }
-        int take = sp < kPopNodes ? sp : kPopNodes;
+        constexpr int kPop = kTri ? kPopNodes : 2 * kPopNodes;
+        int take = sp < kPop ? sp : kPop;
         const int room = (kBatchCap - sp - lc) / 2;
         if (take > room) take = room > 1 ? room : 1;
         if (sp + lc + take > kBatchAlloc) {   // past the bound of a valid tree
             if (lane == 0) atomicOr(a.status, 64);
             break;
+        }
+        if constexpr (!kTri) {
+            point_round<M, K>(a, S, O, n_nodes, take, sp, stats);
+            continue;
         }
         const bool pop = lane < 2 * take;
         const StackEntry en = S.e[pop ? sp - 1 - (lane >> 1) : 0];
