@@ -197,6 +197,7 @@ __device__ RefitArgs refit_args(const PlanScene &P, int64_t t, PlanHeader *h) {
     a.n = s.n_faces;
     a.chunk_log2 = P.chunk_log2;
     a.inf = INFINITY;
+    a.list_top = 0;
     return a;
 }
 

@@ -6,9 +6,9 @@
 // (Sec. 4.1).  The BVH kind is not named by the paper; this is a linear BVH
 // (Karras 2012) built entirely on the device:
 //
-//   init     clear build scratch (histograms, look-back words, counters)
-//   bounds   per-axis min/max of s = (v0 + v1) + v2, block reduce + one
-//            atomic per block on order-preserving uint encodings
+//   bounds   per-axis min/max of s = (v0 + v1) + v2 per workgroup, s kept for
+//            the next step; clears the build scratch (histograms, look-back
+//            words, counters) on the way
 //   morton   30-bit codes defined in IEEE binary32 (no contraction), fused
 //            with the four 8-bit digit histograms of the radix sort
 //   sort     4 passes of a stable LSD radix sort of (code, id): one kernel per
@@ -16,11 +16,12 @@
 //            digit bits), global digit offsets by decoupled look-back
 //   tree     Karras radix tree per internal node + leaf permutation of faces;
 //            lists the subtrees of at most C leaves that cut the tree and the
-//            "top" nodes above them, then lists each top node's two children
+//            "top" nodes above them
 //   refit    one kernel: a workgroup per subtree refits it level by level
-//            with summary slots in LDS, and the workgroup that finishes the
-//            last subtree refits the top nodes from the deposited subtree
-//            roots (see refit.hpp)
+//            with summary slots in LDS, another lists each top node's two
+//            children meanwhile, and the workgroup that finishes the last
+//            subtree refits the top nodes from the deposited subtree roots
+//            (see refit.hpp)
 //
 // Node records are child-centric (96 B: both children's boxes, or a leaf
 // child's triangle itself) so a traversal step reads one record and a leaf
@@ -33,19 +34,21 @@
 namespace mgu {
 namespace {
 
-constexpr int kSortThreads = 256;          // 4 waves
-
-// Keys per lane of a sort pass: about 256 tiles whatever the size (at least 2
-// and at most 16 keys per lane), so small sorts still spread over the chip.
-inline int sort_items_for(int64_t n) {
-    int items = 2;
-    while (items < 16 && int64_t(kSortThreads) * items * 256 < n) items <<= 1;
-    return items;
+// Keys of a sort tile: about 256 tiles whatever the size (at least 512 and at
+// most 4096 keys), so small sorts still spread over the chip.  Tiles of 512 keys
+// take 256 threads, larger ones 4 keys per thread: a tile is alone on its CU, and
+// ranking a thread's keys is a chain (1M keys: 23.5 us a pass with 16 keys in
+// each of 256 threads, 16.3 us with 4 in 1024 and 16 look-back words).
+inline int sort_tile_for(int64_t n) {
+    int tile = 512;
+    while (tile < 4096 && int64_t(tile) * 256 < n) tile <<= 1;
+    return tile;
 }
 constexpr uint32_t kFlagAgg = 1u << 30;    // look-back word: tile aggregate
 constexpr uint32_t kFlagPrefix = 2u << 30; //                 inclusive prefix
 constexpr uint32_t kValueMask = (1u << 30) - 1;
 constexpr int kSpinLimit = 1 << 24;        // bounded waits: error word instead of a hang
+constexpr int kLookback = 16;              // look-back words read at once
 
 constexpr int64_t align256(int64_t x) { return (x + 255) & ~int64_t(255); }
 
@@ -81,14 +84,17 @@ inline int chunk_log2_for(int64_t n) {
     return c;
 }
 
+constexpr int kBoundsBlocks = 1024;        // most workgroups of the bounds kernel
+constexpr int64_t kPartialBytes = int64_t(kBoundsBlocks) * 6 * 4;
+
 struct WsLayout {
-    int64_t keys_a, vals_a, keys_b, vals_b, hist, lookback, total;
+    int64_t keys_a, vals_a, keys_b, vals_b, hist, partial, lookback, total;
     int64_t tiles;
 };
 
 inline WsLayout make_ws(int64_t n) {
     WsLayout W{};
-    const int64_t tile = int64_t(kSortThreads) * sort_items_for(n);
+    const int64_t tile = sort_tile_for(n);
     W.tiles = (n + tile - 1) / tile;
     int64_t o = 0;
     W.keys_a = o;   o += align256(4 * n);
@@ -96,6 +102,7 @@ inline WsLayout make_ws(int64_t n) {
     W.keys_b = o;   o += align256(4 * n);
     W.vals_b = o;   o += align256(4 * n);
     W.hist = o;     o += align256(4 * 4 * 256);
+    W.partial = o;  o += kPartialBytes;
     W.lookback = o; o += align256(4 * 4 * 256 * W.tiles);
     W.total = o;
     return W;
@@ -107,31 +114,6 @@ inline T *at(void *base, int64_t off) {
 }
 
 // ------------------------------------------------------------------ kernels
-
-__global__ void build_init_kernel(mg_lbvh_header *hdr, uint32_t *hist, uint32_t *lookback,
-                                  int64_t n_lookback, int n, int nv, int kind, int chunk_log2) {
-    const int64_t tid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    if (hist != nullptr)          // no sort scratch when there are no primitives
-        for (int64_t i = tid; i < 4 * 256; i += stride) hist[i] = 0;
-    if (lookback != nullptr)
-        for (int64_t i = tid; i < n_lookback; i += stride) lookback[i] = 0;
-    if (tid == 0) {
-        hdr->n_prims = n;
-        hdr->n_verts = nv;
-        hdr->prim_kind = kind;
-        hdr->status = 0;
-        for (int k = 0; k < 3; ++k) {
-            hdr->bounds_enc[k] = 0xffffffffu;   // running min
-            hdr->bounds_enc[3 + k] = 0u;        // running max
-        }
-        for (int k = 0; k < 4; ++k) hdr->tile_counter[k] = 0;
-        hdr->refit_arrivals = 0u;
-        hdr->chunk_log2 = chunk_log2;
-        hdr->n_top = 0;
-        hdr->n_sub = 0;
-    }
-}
 
 // s = (v0 + v1) + v2 for face i (three times its centroid), or the point itself.
 // Every operation is a separately rounded binary32 add.
@@ -155,17 +137,9 @@ __device__ __forceinline__ float wave_max(float x) {
     return x;
 }
 
-__global__ __launch_bounds__(256) void bounds_kernel(const float *__restrict__ v, int64_t nv,
-                                                     const int32_t *__restrict__ faces, int64_t n,
-                                                     mg_lbvh_header *hdr) {
-    __shared__ float s_red[6][4];
-    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
-    for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const f3 s = centroid_sum(v, nv, faces, n, i);
-        mn[0] = fminf(mn[0], s.x); mn[1] = fminf(mn[1], s.y); mn[2] = fminf(mn[2], s.z);
-        mx[0] = fmaxf(mx[0], s.x); mx[1] = fmaxf(mx[1], s.y); mx[2] = fmaxf(mx[2], s.z);
-    }
+// Min and max over a block of kThreads of three values per thread, to every thread.
+template <int kThreads>
+__device__ __forceinline__ void block_bounds(float mn[3], float mx[3], float (*s_red)[kThreads / kWave], float out[6]) {
     const int wave = threadIdx.x / kWave, lane = threadIdx.x % kWave;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
@@ -175,13 +149,60 @@ __global__ __launch_bounds__(256) void bounds_kernel(const float *__restrict__ v
     if (lane == 0)
         for (int k = 0; k < 3; ++k) { s_red[k][wave] = mn[k]; s_red[3 + k][wave] = mx[k]; }
     __syncthreads();
-    if (threadIdx.x < 6) {
-        const int k = threadIdx.x;
-        float r = s_red[k][0];
-        for (int w = 1; w < 4; ++w) r = k < 3 ? fminf(r, s_red[k][w]) : fmaxf(r, s_red[k][w]);
-        if (k < 3) atomicMin(&hdr->bounds_enc[k], f2ord(r));
-        else atomicMax(&hdr->bounds_enc[k], f2ord(r));
+    // every wave reduces the waves' values again
+    constexpr int kWaves = kThreads / kWave;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        out[k] = s_red[k][lane % kWaves];
+        out[3 + k] = s_red[3 + k][lane % kWaves];
+#pragma unroll
+        for (int o = kWaves / 2; o >= 1; o >>= 1) {
+            out[k] = fminf(out[k], __shfl_xor(out[k], o));
+            out[3 + k] = fmaxf(out[3 + k], __shfl_xor(out[3 + k], o));
+        }
     }
+}
+
+// The workgroup's bounds of s into partial[blockIdx.x]; the next kernel reduces
+// them, so nothing has to be cleared before this one, which clears the scratch
+// of the rest of the build and writes the header instead of a launch of its own.
+// A face's s is stored (sx, sy, sz), so that its vertices are gathered once.
+__global__ __launch_bounds__(256) void bounds_kernel(const float *__restrict__ v, int64_t nv,
+                                                     const int32_t *__restrict__ faces, int64_t n,
+                                                     float *__restrict__ sx, float *__restrict__ sy,
+                                                     float *__restrict__ sz, float *__restrict__ partial,
+                                                     mg_lbvh_header *hdr, uint32_t *__restrict__ hist,
+                                                     uint32_t *__restrict__ lookback, int64_t n_lookback, int kind,
+                                                     int chunk_log2) {
+    __shared__ float s_red[6][4];
+    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
+    const int64_t tid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+    for (int64_t i = tid; i < n; i += stride) {
+        const f3 s = centroid_sum(v, nv, faces, n, i);
+        if (faces) { sx[i] = s.x; sy[i] = s.y; sz[i] = s.z; }
+        mn[0] = fminf(mn[0], s.x); mn[1] = fminf(mn[1], s.y); mn[2] = fminf(mn[2], s.z);
+        mx[0] = fmaxf(mx[0], s.x); mx[1] = fmaxf(mx[1], s.y); mx[2] = fmaxf(mx[2], s.z);
+    }
+    if (hist != nullptr)          // no sort scratch when there are no primitives
+        for (int64_t i = tid; i < 4 * 256; i += stride) hist[i] = 0;
+    if (lookback != nullptr)
+        for (int64_t i = tid; i < n_lookback; i += stride) lookback[i] = 0;
+    if (tid == 0) {
+        hdr->n_prims = static_cast<int32_t>(n);
+        hdr->n_verts = static_cast<int32_t>(nv);
+        hdr->prim_kind = kind;
+        hdr->status = 0;
+        for (int k = 0; k < 4; ++k) hdr->tile_counter[k] = 0;
+        hdr->refit_arrivals = 0u;
+        hdr->chunk_log2 = chunk_log2;
+        hdr->n_top = 0;
+        hdr->n_sub = 0;
+    }
+    if (partial == nullptr) return;
+    float out[6];
+    block_bounds<256>(mn, mx, s_red, out);
+    if (threadIdx.x < 6) partial[6 * static_cast<int64_t>(blockIdx.x) + threadIdx.x] = out[threadIdx.x];
 }
 
 // Put bit i of a 10-bit value at bit 3 i (magic-number spreading).
@@ -202,18 +223,31 @@ __device__ __forceinline__ uint32_t quant10(float s, float lo, float scale) {
     return q < 1023u ? q : 1023u;
 }
 
-__global__ __launch_bounds__(256) void morton_kernel(const float *__restrict__ v, int64_t nv,
-                                                     const int32_t *__restrict__ faces, int64_t n,
+// s: planes sx, sy, sz of n values (the bounds kernel's, or the points').
+constexpr int kMortonThreads = 1024;
+__global__ __launch_bounds__(kMortonThreads) __attribute__((amdgpu_waves_per_eu(8))) void morton_kernel(const float *__restrict__ sx, const float *__restrict__ sy,
+                                                     const float *__restrict__ sz, int64_t n,
+                                                     const float *__restrict__ partial, int n_partial,
                                                      mg_lbvh_header *hdr, uint32_t *__restrict__ keys,
                                                      uint32_t *__restrict__ hist) {
 #pragma clang fp contract(off)
     __shared__ uint32_t s_hist[4][256];
+    __shared__ float s_red[6][kMortonThreads / kWave];
     for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) (&s_hist[0][0])[i] = 0;
+    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (int b = threadIdx.x; b < n_partial; b += kMortonThreads)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            mn[k] = fminf(mn[k], partial[6 * b + k]);
+            mx[k] = fmaxf(mx[k], partial[6 * b + 3 + k]);
+        }
+    float bounds[6];
+    block_bounds<kMortonThreads>(mn, mx, s_red, bounds);
     float lo[3], scale[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        lo[k] = ord2f(hdr->bounds_enc[k]);
-        const float hi = ord2f(hdr->bounds_enc[3 + k]);
+        lo[k] = bounds[k];
+        const float hi = bounds[3 + k];
         // 1024 / (hi - lo) correctly rounded to binary32: the binary64 quotient of
         // two binary32 values rounds to the same binary32 as a direct division.
         const float ext = hi - lo[k];
@@ -221,17 +255,26 @@ __global__ __launch_bounds__(256) void morton_kernel(const float *__restrict__ v
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         for (int k = 0; k < 3; ++k) { hdr->quant_lo[k] = lo[k]; hdr->quant_scale[k] = scale[k]; }
+        for (int k = 0; k < 6; ++k) hdr->bounds_enc[k] = f2ord(bounds[k]);
     }
     __syncthreads();
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) {
-        const f3 s = centroid_sum(v, nv, faces, n, i);
+        const f3 s = f3{sx[i], sy[i], sz[i]};
         const uint32_t code = (spread10(quant10(s.x, lo[0], scale[0])) << 2) |
                               (spread10(quant10(s.y, lo[1], scale[1])) << 1) |
                               spread10(quant10(s.z, lo[2], scale[2]));
         keys[i] = code;
+        // neighbouring faces share their upper digits: the lanes with the first lane's
+        // digit add once together instead of queueing on one counter
 #pragma unroll
-        for (int p = 0; p < 4; ++p) atomicAdd(&s_hist[p][(code >> (8 * p)) & 0xffu], 1u);
+        for (int p = 0; p < 4; ++p) {
+            const uint32_t d = (code >> (8 * p)) & 0xffu;
+            const uint32_t d0 = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(d)));
+            const uint64_t same = __ballot(d == d0);
+            if (d != d0) atomicAdd(&s_hist[p][d], 1u);
+            else if ((same & lanemask_lt()) == 0) atomicAdd(&s_hist[p][d], static_cast<uint32_t>(__popcll(same)));
+        }
     }
     __syncthreads();
     for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) {
@@ -240,9 +283,9 @@ __global__ __launch_bounds__(256) void morton_kernel(const float *__restrict__ v
     }
 }
 
-// Exclusive scan of one value per thread over a 256-thread block.
-__device__ __forceinline__ uint32_t block_excl_scan256(uint32_t x, uint32_t *s_tmp /*[4]*/,
-                                                       uint32_t &total) {
+// Exclusive scan of one value per thread over a block of kThreads.
+template <int kThreads>
+__device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t *s_tmp /*[kThreads / 64]*/) {
     const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
     uint32_t inc = x;
 #pragma unroll
@@ -253,37 +296,39 @@ __device__ __forceinline__ uint32_t block_excl_scan256(uint32_t x, uint32_t *s_t
     if (lane == kWave - 1) s_tmp[wave] = inc;
     __syncthreads();
     uint32_t before = 0;
-    total = 0;
 #pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        const uint32_t t = s_tmp[w];
-        if (w < wave) before += t;
-        total += t;
-    }
+    for (int w = 0; w < 4; ++w)               // the digits lie in the first 256 threads
+        if (w < wave) before += s_tmp[w];
     __syncthreads();
     return before + inc - x;
 }
 
-// One stable LSD pass over digit (key >> shift) & 255 for tiles of
-// kSortThreads * kItems keys.  vals_in == nullptr means the values are the
-// input positions (first pass).
-template <int kItems>
-__global__ __launch_bounds__(kSortThreads) void radix_pass_kernel(
+// Threads of a sort tile of 256 kScale keys (sort_tile_for).
+constexpr int sort_threads(int scale) { return scale <= 4 ? 256 : 64 * scale; }
+
+// One stable LSD pass over digit (key >> shift) & 255 for tiles of 256 kScale
+// keys.  vals_in == nullptr means the values are the input positions (first
+// pass).  The first 256 threads own a digit each.
+template <int kScale>
+__global__ __launch_bounds__(sort_threads(kScale)) __attribute__((amdgpu_waves_per_eu(8))) void radix_pass_kernel(
     const uint32_t *__restrict__ keys_in, const int32_t *__restrict__ vals_in,
     uint32_t *__restrict__ keys_out, int32_t *__restrict__ vals_out, int64_t n, int shift,
     const uint32_t *__restrict__ hist, uint32_t *lookback, uint32_t *tile_counter, int32_t *status) {
-    constexpr int kTile = kSortThreads * kItems;
+    constexpr int kThreads = sort_threads(kScale), kTile = 256 * kScale, kItems = kTile / kThreads,
+                  kWaves = kThreads / kWave;
     __shared__ uint32_t s_tile;
-    __shared__ uint32_t s_wave_cnt[4][256];
+    __shared__ uint32_t s_wave_cnt[kWaves][256];
     __shared__ uint32_t s_digit_start[256];
     __shared__ uint32_t s_global[256];
-    __shared__ uint32_t s_tmp[4];
+    __shared__ uint32_t s_tmp[kWaves];
     __shared__ uint32_t s_keys[kTile];
     __shared__ int32_t s_vals[kTile];
 
     const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave;
     if (tid == 0) s_tile = atomicAdd(tile_counter, 1u);
-    for (int i = tid; i < 4 * 256; i += kSortThreads) (&s_wave_cnt[0][0])[i] = 0;
+    const bool digit = tid < 256;
+    const uint32_t hist_d = digit ? hist[tid] : 0u;
+    for (int i = tid; i < kWaves * 256; i += kThreads) (&s_wave_cnt[0][0])[i] = 0;
     __syncthreads();
     const int64_t tile = s_tile;
     const int64_t base = tile * kTile;
@@ -292,12 +337,18 @@ __global__ __launch_bounds__(kSortThreads) void radix_pass_kernel(
     int32_t val[kItems];
     uint32_t rank[kItems];
     const uint64_t lt = lanemask_lt();
+    // all of a thread's keys in flight before the first is ranked
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+        const int64_t idx = base + (static_cast<int64_t>(wave) * kItems + j) * kWave + lane;
+        const int64_t in = idx < n ? idx : n - 1;
+        key[j] = keys_in[in];
+        val[j] = vals_in ? vals_in[in] : static_cast<int32_t>(in);
+    }
 #pragma unroll
     for (int j = 0; j < kItems; ++j) {
         const int64_t idx = base + (static_cast<int64_t>(wave) * kItems + j) * kWave + lane;
         const bool valid = idx < n;
-        key[j] = valid ? keys_in[idx] : 0u;
-        val[j] = valid ? (vals_in ? vals_in[idx] : static_cast<int32_t>(idx)) : 0;
         const uint32_t d = (key[j] >> shift) & 0xffu;
         // lanes of this wave holding the same digit (match mask from 8 ballots)
         uint64_t m = __ballot(valid);
@@ -315,47 +366,67 @@ __global__ __launch_bounds__(kSortThreads) void radix_pass_kernel(
     __syncthreads();
 
     // per digit: counts of each wave -> exclusive offsets across waves
-    const int d = tid;
-    const uint32_t c0 = s_wave_cnt[0][d], c1 = s_wave_cnt[1][d], c2 = s_wave_cnt[2][d], c3 = s_wave_cnt[3][d];
-    const uint32_t tile_cnt = c0 + c1 + c2 + c3;
-    // publish this tile's aggregate as early as possible
+    const int d = digit ? tid : 0;
+    uint32_t tile_cnt = 0;
     uint32_t *my_word = lookback + tile * 256 + d;
-    __hip_atomic_store(my_word, (tile == 0 ? kFlagPrefix : kFlagAgg) | tile_cnt, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-    __syncthreads();   // every wave has read its counts before they are overwritten
-    s_wave_cnt[0][d] = 0;
-    s_wave_cnt[1][d] = c0;
-    s_wave_cnt[2][d] = c0 + c1;
-    s_wave_cnt[3][d] = c0 + c1 + c2;
-    uint32_t tile_total;
-    const uint32_t dstart = block_excl_scan256(tile_cnt, s_tmp, tile_total);
-    s_digit_start[d] = dstart;
-    uint32_t hist_total;
-    const uint32_t dbase = block_excl_scan256(hist[d], s_tmp, hist_total);
+    if (digit) {
+        uint32_t c[kWaves];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) c[w] = s_wave_cnt[w][d];
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) tile_cnt += c[w];
+        // publish this tile's aggregate as early as possible
+        __hip_atomic_store(my_word, (tile == 0 ? kFlagPrefix : kFlagAgg) | tile_cnt, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t before = 0;                  // a digit's column is its thread's alone
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) {
+            s_wave_cnt[w][d] = before;
+            before += c[w];
+        }
+    }
+    const uint32_t dstart = block_excl_scan<kThreads>(tile_cnt, s_tmp);
+    if (digit) s_digit_start[d] = dstart;
+    const uint32_t dbase = block_excl_scan<kThreads>(hist_d, s_tmp);
 
-    // decoupled look-back: sum the counts of digit d over all earlier tiles
+    // decoupled look-back: sum the counts of digit d over all earlier tiles, the
+    // words of kLookback tiles read at once (a word is a round trip past the XCD's
+    // L2, and the tiles in flight together have only their aggregates published)
     uint32_t excl = 0;
-    if (tile > 0) {
+    if (tile > 0 && digit) {
         int64_t t = tile - 1;
         int spins = 0;
-        while (true) {
-            const uint32_t w = __hip_atomic_load(lookback + t * 256 + d, __ATOMIC_RELAXED,
-                                                 __HIP_MEMORY_SCOPE_AGENT);
-            if ((w & ~kValueMask) == 0) {
-                if (++spins > kSpinLimit) {   // never expected: report instead of hanging
-                    atomicOr(status, 1);
-                    break;
+        for (bool found = false; !found;) {
+            uint32_t w[kLookback];
+#pragma unroll
+            for (int u = 0; u < kLookback; ++u)
+                // (32-bit byte offsets: with a 64-bit address each, the loads reused each
+                // other's address registers and went one by one)
+                w[u] = __hip_atomic_load(
+                    reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(lookback) +
+                                                       ((t > u ? static_cast<uint32_t>(t) - u : 0u) * 1024u + 4u * d)),
+                    __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            int used = 0;
+            bool ready = true;
+#pragma unroll
+            for (int u = 0; u < kLookback; ++u) {
+                ready = ready && !found && (w[u] & ~kValueMask) != 0;
+                if (ready) {
+                    excl += w[u] & kValueMask;
+                    ++used;
+                    found = (w[u] & kFlagPrefix) != 0;
                 }
-                continue;
             }
-            excl += w & kValueMask;
-            if (w & kFlagPrefix) break;
-            --t;
+            t -= used;
+            if (used == 0 && ++spins > kSpinLimit) {   // never expected: report instead of hanging
+                atomicOr(status, 1);
+                break;
+            }
         }
         __hip_atomic_store(my_word, kFlagPrefix | (excl + tile_cnt), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
-    s_global[d] = dbase + excl - dstart;
+    if (digit) s_global[d] = dbase + excl - dstart;
     __syncthreads();
 
     // scatter into the tile in digit order (stable), then write out coalesced
@@ -371,7 +442,7 @@ __global__ __launch_bounds__(kSortThreads) void radix_pass_kernel(
     }
     __syncthreads();
     const int64_t count = (n - base) < kTile ? (n - base) : kTile;
-    for (int i = tid; i < count; i += kSortThreads) {
+    for (int i = tid; i < count; i += kThreads) {
         const uint32_t k = s_keys[i];
         const uint32_t out = s_global[(k >> shift) & 0xffu] + i;
         if (out < static_cast<uint64_t>(n)) {
@@ -384,8 +455,25 @@ __global__ __launch_bounds__(kSortThreads) void radix_pass_kernel(
 }
 
 // Internal node i (i < n - 1) and leaf i (i < n): Karras's range and split
-// search; children's parent tags; leaf face permutation; counter reset.
-__global__ __launch_bounds__(256) void hierarchy_kernel(const uint32_t *__restrict__ codes,
+// search; children's parent tags; leaf face permutation; subtree and top lists.
+//
+// A search step is a dependent read of a code, and there are three searches of
+// log2(range) steps, so the few nodes near the root set the time of one search
+// per thread (some 48 steps of 0.3 us on 46,000 leaves).  A thread therefore
+// searches only ranges that stay within kNear leaves, in a window of codes in
+// LDS; the workgroup's other nodes (about six in 256) go to groups of 16 lanes
+// that probe 16 places a step.  Hierarchies of 46,000 leaves:
+// 17.5 -> 12.3 us, of 1M: 49 -> 29 us (also by leaving the records to the refit).
+constexpr int kNear = 64;                  // longest range a thread searches alone
+constexpr int kHierThreads = 256;
+constexpr int kWindow = kHierThreads + 2 * kNear + 2;
+
+__device__ __forceinline__ int karras_delta(uint32_t ci, uint32_t cj, int i, int j) {
+    return ci != cj ? __clz(static_cast<int>(ci ^ cj))
+                    : 32 + __clz(static_cast<int>(static_cast<uint32_t>(i) ^ static_cast<uint32_t>(j)));
+}
+
+__global__ __launch_bounds__(kHierThreads) void hierarchy_kernel(const uint32_t *__restrict__ codes,
                                                         const int32_t *__restrict__ prim,
                                                         int32_t *__restrict__ inv_prim, int64_t n,
                                                         const int32_t *__restrict__ faces,
@@ -396,177 +484,255 @@ __global__ __launch_bounds__(256) void hierarchy_kernel(const uint32_t *__restri
                                                         int32_t *__restrict__ child,
                                                         int32_t *__restrict__ top_nodes,
                                                         int32_t *__restrict__ subtrees,
-                                                        float *__restrict__ nodes,
                                                         mg_lbvh_header *hdr, int chunk_log2) {
-    const int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    {
-        const int32_t p = prim[i];
-        if (p >= 0 && p < n) inv_prim[p] = static_cast<int32_t>(i);
-        else atomicOr(&hdr->status, 4);
+    __shared__ uint32_t s_code[kWindow];
+    __shared__ int2 s_long[kHierThreads];      // nodes left to the lane groups: local index and sign of d, delta past the near end
+    __shared__ int s_nlong;
+    const int tid = threadIdx.x;
+    const int ni = static_cast<int>(n);
+    const int base = static_cast<int>(blockIdx.x) * kHierThreads, w0 = base - kNear - 1;
+    const int i = base + tid;
+    for (int u = tid; u < kWindow; u += kHierThreads) {
+        const int j = w0 + u;
+        s_code[u] = j >= 0 && j < ni ? codes[j] : 0u;
     }
-    if (faces) {
+    if (tid == 0) s_nlong = 0;
+    // the leaf's face is gathered while the searches run
+    int32_t f0 = 0, f1 = 0, f2 = 0;
+    if (i < ni) {
         const int32_t p = prim[i];
-        leaf_faces[i] = faces[p];
-        leaf_faces[n + i] = faces[n + p];
-        leaf_faces[2 * n + i] = faces[2 * n + p];
+        if (p >= 0 && p < ni) {
+            inv_prim[p] = i;
+            if (faces) { f0 = faces[p]; f1 = faces[n + p]; f2 = faces[2 * n + p]; }
+        } else {
+            atomicOr(&hdr->status, 4);
+        }
     }
+    auto store_leaf = [&]() {
+        if (!faces || i >= ni) return;
+        leaf_faces[i] = f0;
+        leaf_faces[n + i] = f1;
+        leaf_faces[2 * n + i] = f2;
+    };
     if (n == 1) {
-        leaf_parent[0] = -1;
-        subtrees[0] = ~0;         // the one leaf is the one subtree
-        subtrees[1] = 0;
-        subtrees[2] = 0;
-        hdr->n_sub = 1;
+        if (i == 0) {
+            leaf_parent[0] = -1;
+            subtrees[0] = ~0;         // the one leaf is the one subtree
+            subtrees[1] = 0;
+            subtrees[2] = 0;
+            hdr->n_sub = 1;
+        }
+        store_leaf();
         return;
     }
-    if (i >= n - 1) return;
-    // The searches run in 32-bit indices (counts are below 2^30, so i + lmax d and
-    // 2 l stay below 2^31) with shifts for the halvings.  Each step is a dependent
-    // read of a code (about 0.3 us from L2 for the top nodes), which sets the
-    // kernel's time: the top nodes' threads finish last.
-    const int ni = static_cast<int>(n), ii = static_cast<int>(i);
-    const uint32_t ci = codes[i];
-    auto delta = [&](int jx) -> int {      // delta(i, jx) of Karras 2012; -1 outside [0, n)
-        if (static_cast<uint32_t>(jx) >= static_cast<uint32_t>(ni)) return -1;
-        const uint32_t cj = codes[jx];
-        if (ci != cj) return __clz(static_cast<int>(ci ^ cj));
-        return 32 + __clz(static_cast<int>(static_cast<uint32_t>(ii) ^ static_cast<uint32_t>(jx)));
+    __syncthreads();
+    // Writes node x over leaves x and x + l d, split after x + sp d (+ -1 for d < 0).
+    auto emit = [&](int x, int d, int l, int sp) {
+        const int64_t j = x + l * d;
+        const int64_t gamma = x + sp * d + (d < 0 ? -1 : 0);
+        const int64_t lo = x < j ? x : j, hi = x < j ? j : x;
+        const int32_t tag_l = static_cast<int32_t>(static_cast<uint32_t>(x) << 1), tag_r = tag_l | 1;
+        if (lo == gamma) leaf_parent[gamma] = tag_l; else node_parent[gamma] = tag_l;
+        if (hi == gamma + 1) leaf_parent[gamma + 1] = tag_r; else node_parent[gamma + 1] = tag_r;
+        if (x == 0) node_parent[0] = -1;
+        // (the records' own copies of these references are written by the refit)
+        child[x] = static_cast<int32_t>(lo == gamma ? ~gamma : gamma);
+        child[n - 1 + x] = static_cast<int32_t>(hi == gamma + 1 ? ~(gamma + 1) : gamma + 1);
+        // the cut: a node with more than C leaves is a top node, and each of its
+        // children with at most C leaves roots a subtree (list order is irrelevant)
+        const int64_t C = int64_t(1) << chunk_log2;
+        if (hi - lo + 1 > C) {
+            const bool s0 = gamma - lo + 1 <= C, s1 = hi - gamma <= C;
+            const int32_t t = static_cast<int32_t>(atomicAdd(reinterpret_cast<uint32_t *>(&hdr->n_top), 1u));
+            int32_t k = 0;
+            if (s0 || s1)
+                k = static_cast<int32_t>(atomicAdd(reinterpret_cast<uint32_t *>(&hdr->n_sub), (s0 ? 1u : 0u) + (s1 ? 1u : 0u)));
+            top_nodes[t] = x;
+            node_aux[x] = t;
+            if (s0) {
+                subtrees[k] = static_cast<int32_t>(lo == gamma ? ~lo : gamma);
+                subtrees[n + k] = static_cast<int32_t>(lo);
+                subtrees[2 * n + k] = static_cast<int32_t>(gamma);
+                ++k;
+            }
+            if (s1) {
+                subtrees[k] = static_cast<int32_t>(hi == gamma + 1 ? ~hi : gamma + 1);
+                subtrees[n + k] = static_cast<int32_t>(gamma + 1);
+                subtrees[2 * n + k] = static_cast<int32_t>(hi);
+            }
+        } else {
+            node_aux[x] = -1;
+            if (x == 0) {             // the whole tree is one subtree
+                atomicAdd(reinterpret_cast<uint32_t *>(&hdr->n_sub), 1u);
+                subtrees[0] = 0;
+                subtrees[n] = 0;
+                subtrees[2 * n] = static_cast<int32_t>(n - 1);
+            }
+        }
     };
-    const int d = (delta(ii + 1) - delta(ii - 1)) > 0 ? 1 : -1;
-    const int dmin = delta(ii - d);
-    int lmax = 2;
-    while (lmax <= ni && delta(ii + lmax * d) > dmin) lmax <<= 1;
-    int l = 0;
-    for (int t = lmax >> 1; t >= 1; t >>= 1)
-        if (delta(ii + (l + t) * d) > dmin) l += t;
-    const int dnode = delta(ii + l * d);
-    int sp = 0;
-    for (int k = 1;; ++k) {               // t = ceil(l / 2^k)
-        const int t = static_cast<int>((static_cast<uint32_t>(l) + (1u << k) - 1u) >> k);
-        if (delta(ii + (sp + t) * d) > dnode) sp += t;
-        if (t <= 1) break;
-    }
-    const int64_t j = ii + l * d;
-    const int64_t gamma = ii + sp * d + (d < 0 ? -1 : 0);
-    const int64_t lo = i < j ? i : j, hi = i < j ? j : i;
-    const int32_t tag_l = static_cast<int32_t>(i << 1), tag_r = static_cast<int32_t>((i << 1) | 1);
-    if (lo == gamma) leaf_parent[gamma] = tag_l; else node_parent[gamma] = tag_l;
-    if (hi == gamma + 1) leaf_parent[gamma + 1] = tag_r; else node_parent[gamma + 1] = tag_r;
-    if (i == 0) node_parent[0] = -1;
-    // child references live in the records' first .w word of each slot; the refit
-    // rewrites the same values, so they are valid before any box exists
-    const int32_t c0 = static_cast<int32_t>(lo == gamma ? ~gamma : gamma);
-    const int32_t c1 = static_cast<int32_t>(hi == gamma + 1 ? ~(gamma + 1) : gamma + 1);
-    nodes[24 * i + 3] = __int_as_float(c0);
-    nodes[24 * i + 15] = __int_as_float(c1);
-    child[i] = c0;
-    child[n - 1 + i] = c1;
-    // the cut: a node with more than C leaves is a top node, and each of its
-    // children with at most C leaves roots a subtree (list order is irrelevant)
-    const int64_t C = int64_t(1) << chunk_log2;
-    if (hi - lo + 1 > C) {
-        const int32_t t = static_cast<int32_t>(atomicAdd(reinterpret_cast<uint32_t *>(&hdr->n_top), 1u));
-        top_nodes[t] = static_cast<int32_t>(i);
-        node_aux[i] = t;
-        const int64_t cf[2] = {lo, gamma + 1}, cl[2] = {gamma, hi};
-        for (int c = 0; c < 2; ++c) {
-            if (cl[c] - cf[c] + 1 > C) continue;
-            const int32_t k = static_cast<int32_t>(atomicAdd(reinterpret_cast<uint32_t *>(&hdr->n_sub), 1u));
-            const bool leaf = cl[c] == cf[c];
-            subtrees[k] = static_cast<int32_t>(leaf ? ~cf[c] : (c == 0 ? gamma : gamma + 1));
-            subtrees[n + k] = static_cast<int32_t>(cf[c]);
-            subtrees[2 * n + k] = static_cast<int32_t>(cl[c]);
-        }
-    } else {
-        node_aux[i] = -1;
-        if (i == 0) {             // the whole tree is one subtree
-            atomicAdd(reinterpret_cast<uint32_t *>(&hdr->n_sub), 1u);
-            subtrees[0] = 0;
-            subtrees[n] = 0;
-            subtrees[2 * n] = static_cast<int32_t>(n - 1);
+    if (i < ni - 1) {
+        const uint32_t ci = s_code[i - w0];
+        auto delta = [&](int jx) -> int {      // delta(i, jx) of Karras 2012 in the window; -1 outside [0, n)
+            if (static_cast<uint32_t>(jx) >= static_cast<uint32_t>(ni)) return -1;
+            return karras_delta(ci, s_code[jx - w0], i, jx);
+        };
+        const int d = (delta(i + 1) - delta(i - 1)) > 0 ? 1 : -1;
+        const int dmin = delta(i - d);
+        int lmax = 2;
+        while (lmax <= kNear && delta(i + lmax * d) > dmin) lmax <<= 1;
+        if (lmax > kNear) {                    // delta(i + kNear d) > dmin: the range is longer
+            s_long[atomicAdd(&s_nlong, 1)] = make_int2(2 * tid + (d > 0 ? 1 : 0), dmin);
+        } else {
+            int l = 0;
+            for (int t = lmax >> 1; t >= 1; t >>= 1)
+                if (delta(i + (l + t) * d) > dmin) l += t;
+            const int dnode = delta(i + l * d);
+            int sp = 0;
+            for (int k = 1;; ++k) {            // t = ceil(l / 2^k)
+                const int t = (l + (1 << k) - 1) >> k;
+                if (delta(i + (sp + t) * d) > dnode) sp += t;
+                if (t <= 1) break;
+            }
+            emit(i, d, l, sp);
         }
     }
+    __syncthreads();
+    // the long ranges: 16 lanes each, all groups of a wave in step
+    const int nlong = s_nlong, group = tid / 16, sub = tid % 16, shift = 16 * (group % 4);
+    for (int first = 0; first < nlong; first += kHierThreads / 16) {
+        const bool on = first + group < nlong;
+        const int2 item = s_long[on ? first + group : 0];
+        const int x = base + (item.x >> 1), d = (item.x & 1) ? 1 : -1, dmin = item.y;
+        const uint32_t cx = s_code[x - w0];
+        auto delta = [&](int64_t jx) -> int {
+            if (jx < 0 || jx >= ni) return -1;
+            return karras_delta(cx, codes[jx], x, static_cast<int>(jx));
+        };
+        auto votes = [&](bool yes) -> int {    // leading lanes of the group that say yes
+            const uint32_t m = static_cast<uint32_t>(__ballot(on && yes) >> shift) & 0xffffu;
+            return __builtin_ctz(~m);
+        };
+        // the largest e in [lo, hi) with ok(e), given ok(lo), not ok(hi), ok falling
+        auto search = [&](int64_t lo, int64_t hi, int above) -> int64_t {
+            while (__any(on && hi - lo > 1)) {
+                const int64_t step = (hi - lo + 16) / 17;
+                const int64_t at = lo + (sub + 1) * step;
+                const int yes = votes(at < hi && delta(x + at * d) > above);
+                if (hi - lo > 1) {
+                    const int64_t nlo = lo + yes * step, nhi = nlo + step;
+                    hi = nhi < hi ? nhi : hi;
+                    lo = nlo;
+                }
+            }
+            return lo;
+        };
+        int64_t lo = kNear, hi = 0;            // delta(x + kNear d) > dmin
+        for (bool more = on; __any(more);) {   // the first power of two past the range
+            const int64_t at = lo << (sub + 1);
+            const int yes = votes(at <= ni && delta(x + at * d) > dmin);
+            if (more) {
+                hi = lo << (yes + 1);
+                lo <<= yes;
+                more = yes == 16;
+            }
+        }
+        const int64_t l = search(lo, hi, dmin);
+        const int dnode = delta(x + l * d);
+        const int64_t sp = search(0, l, dnode);
+        if (on && sub == 0) emit(x, d, static_cast<int>(l), static_cast<int>(sp));
+    }
+    store_leaf();
 }
 
 // Subtrees largest first.  Phase 1 of the refit gives subtree k to workgroup k
 // (then k + grid, ...), and workgroups start in index order as compute units free
 // up; when more subtrees than resident workgroups exist (LDS allows two per CU at
 // 1024-leaf chunks, one at 2048), the late starters should be the small subtrees
-// (longest-first list scheduling).  One workgroup sorts by (size descending, first
-// leaf ascending), so the order is deterministic; more than kOrderMax subtrees keep
-// their order.  The refit's records do not depend on the order.
+// (longest-first list scheduling).  One workgroup deals them by size, a counting
+// sort in LDS (the bitonic sort it replaces took 16 us); equal sizes in any order,
+// and more than kOrderMax subtrees keep theirs.  The refit's records do not depend
+// on the order.
 constexpr int kOrderMax = 2048;
 __global__ __launch_bounds__(1024) void order_subtrees_kernel(int32_t *__restrict__ subtrees, int64_t n,
                                                               const mg_lbvh_header *__restrict__ hdr) {
-    __shared__ uint64_t s_key[kOrderMax];
-    __shared__ int32_t s_val[3][kOrderMax];
-    const int ns = hdr->n_sub;
+    __shared__ uint32_t s_start[2049];         // by 2048 - size: counts, then first places
+    __shared__ uint32_t s_wave[16];
+    const int ns = hdr->n_sub, tid = threadIdx.x;
     if (ns <= 1 || ns > kOrderMax) return;
-    int P = 1;
-    while (P < ns) P <<= 1;
-    for (int i = threadIdx.x; i < P; i += 1024) {
-        uint64_t key = ~0ull;                     // padding sorts last
-        if (i < ns) {
-            const int32_t r = subtrees[i], f = subtrees[n + i], l = subtrees[2 * n + i];
-            const uint32_t size = static_cast<uint32_t>(l - f + 1) & 0xfffu;   // <= 2048 leaves
-            key = (static_cast<uint64_t>(0xfffu - size) << 42) | (static_cast<uint64_t>(f & 0x3fffffff) << 11) |
-                  static_cast<uint64_t>(i);
-            s_val[0][i] = r; s_val[1][i] = f; s_val[2][i] = l;
-        }
-        s_key[i] = key;
-    }
-    for (int k = 2; k <= P; k <<= 1)
-        for (int j = k >> 1; j > 0; j >>= 1) {
-            __syncthreads();
-            for (int t = threadIdx.x; t < P; t += 1024) {
-                const int o = t ^ j;
-                if (o <= t) continue;
-                const uint64_t a = s_key[t], b = s_key[o];
-                if ((a > b) == ((t & k) == 0)) { s_key[t] = b; s_key[o] = a; }
-            }
-        }
+    for (int i = tid; i <= 2048; i += 1024) s_start[i] = 0u;
     __syncthreads();
-    for (int q = threadIdx.x; q < ns; q += 1024) {
-        const int i = static_cast<int>(s_key[q] & 0x7ffu);
-        subtrees[q] = s_val[0][i];
-        subtrees[n + q] = s_val[1][i];
-        subtrees[2 * n + q] = s_val[2][i];
+    int32_t r[2], f[2], l[2], bin[2];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        const int i = tid + 1024 * u;
+        bin[u] = -1;
+        if (i >= ns) continue;
+        r[u] = subtrees[i]; f[u] = subtrees[n + i]; l[u] = subtrees[2 * n + i];
+        const int size = l[u] - f[u] + 1;
+        bin[u] = size < 0 ? 2048 : size > 2048 ? 0 : 2048 - size;
+        atomicAdd(&s_start[bin[u]], 1u);
+    }
+    __syncthreads();
+    // exclusive scan of bins 2 tid and 2 tid + 1 (bin 2048, size 0, cannot occur in a valid list)
+    const uint32_t c0 = s_start[2 * tid], c1 = s_start[2 * tid + 1], total = c0 + c1;
+    uint32_t inc = total;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const uint32_t y = __shfl_up(inc, o);
+        if (tid % kWave >= o) inc += y;
+    }
+    if (tid % kWave == kWave - 1) s_wave[tid / kWave] = inc;
+    __syncthreads();
+    uint32_t before = inc - total;
+    for (int w = 0; w < tid / kWave; ++w) before += s_wave[w];
+    s_start[2 * tid] = before;
+    s_start[2 * tid + 1] = before + c0;
+    if (tid == 1023) s_start[2048] = before + total;
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        if (bin[u] < 0) continue;
+        const uint32_t q = atomicAdd(&s_start[bin[u]], 1u);
+        if (q >= static_cast<uint32_t>(ns)) continue;
+        subtrees[q] = r[u];
+        subtrees[n + q] = f[u];
+        subtrees[2 * n + q] = l[u];
     }
 }
 
 // The top children: per top node and slot, the child's top index, or ~k when
 // the child is the root of subtree k (every top node has two children of
 // these kinds), and in planes 2 and 3 a top child's node id (0 for a subtree).
-__global__ __launch_bounds__(256) void top_child_kernel(const int32_t *__restrict__ node_aux,
-                                                        const int32_t *__restrict__ top_nodes,
-                                                        const int32_t *__restrict__ node_parent,
-                                                        const int32_t *__restrict__ leaf_parent,
-                                                        const int32_t *__restrict__ subtrees, int64_t n,
-                                                        int32_t *__restrict__ top_child, mg_lbvh_header *hdr) {
-    const int T = hdr->n_top, NS = hdr->n_sub;
-    if (NS < 2) return;                       // a single subtree is the whole tree: no top
+// One workgroup of a build's refit lists them beside the subtrees; device-scope
+// stores, since the workgroup that refits the top may be on another XCD.
+template <int kThreads>
+__device__ void list_top_children(const RefitArgs &a, int T, int NS) {
+    const int64_t n = a.n;
+    int32_t *top_child = const_cast<int32_t *>(a.top_child);
     // the parent tag of a top node or subtree root names its slot in a top node
     auto put = [&](int32_t tag, int32_t v, int32_t node) {
         if (tag < 0) return;                  // the root
         const int32_t p = tag >> 1;
-        if (p >= n - 1) { atomicOr(&hdr->status, 8); return; }
-        const int32_t t = node_aux[p];
-        if (t < 0 || t >= T) { atomicOr(&hdr->status, 8); return; }
-        top_child[(tag & 1) * n + t] = v;
-        top_child[(2 + (tag & 1)) * n + t] = node;
+        if (p >= n - 1) { atomicOr(a.status, 8); return; }
+        const int32_t t = a.node_aux[p];
+        if (t < 0 || t >= T) { atomicOr(a.status, 8); return; }
+        __hip_atomic_store(top_child + (tag & 1) * n + t, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(top_child + (2 + (tag & 1)) * n + t, node, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     };
-    for (int t = blockIdx.x * blockDim.x + threadIdx.x; t < T; t += gridDim.x * blockDim.x) {
-        const int32_t p = top_nodes[t];
-        if (p < 0 || p >= n - 1) { atomicOr(&hdr->status, 8); continue; }
-        put(node_parent[p], t, p);
+    for (int t = threadIdx.x; t < T; t += kThreads) {
+        const int32_t p = a.top_nodes[t];
+        if (p < 0 || p >= n - 1) { atomicOr(a.status, 8); continue; }
+        put(a.node_parent[p], t, p);
     }
-    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < NS; k += gridDim.x * blockDim.x) {
-        const int32_t r = subtrees[k];
+    for (int k = threadIdx.x; k < NS; k += kThreads) {
+        const int32_t r = a.subtrees[k];
         const bool leaf = r < 0;
         const int64_t id = leaf ? ~static_cast<int64_t>(r) : r;
-        if (id >= (leaf ? n : n - 1)) { atomicOr(&hdr->status, 8); continue; }
-        put(leaf ? leaf_parent[id] : node_parent[id], ~k, 0);
+        if (id >= (leaf ? n : n - 1)) { atomicOr(a.status, 8); continue; }
+        put(leaf ? a.leaf_parent[id] : a.node_parent[id], ~k, 0);
     }
+    __builtin_amdgcn_s_waitcnt(0);            // this wave's stores have completed
+    __syncthreads();
 }
 
 // The refit over workgroups block, block + nblocks, ...: each takes subtrees
@@ -578,18 +744,27 @@ template <bool kTri, int kThreads, int kPer>
 __device__ void refit_blocks(const RefitArgs &a, int64_t block, int64_t nblocks, unsigned char *smem) {
     __shared__ int s_last;
     const int32_t ns = *a.n_sub;
+    const int T = *a.n_top;
     int mine = 0;
-    for (int64_t k = block; k < ns; k += nblocks) {
-        refit_subtree<kTri, kThreads, kPer>(a, k, smem);     // ends with a barrier
-        ++mine;
+    if (a.list_top) {                         // a build: the first workgroup lists the top children
+        if (block == 0) {
+            if (ns >= 2 && T >= 1 && T < a.n) list_top_children<kThreads>(a, T, ns);
+            ++mine;
+        }
+        --block;
+        --nblocks;
     }
+    if (block >= 0)
+        for (int64_t k = block; k < ns; k += nblocks) {
+            refit_subtree<kTri, kThreads, kPer>(a, k, smem);     // ends with a barrier
+            ++mine;
+        }
     if (ns < 2 || mine == 0) return;          // one subtree is the whole tree: its root is written
     if (threadIdx.x == 0)
         s_last = __hip_atomic_fetch_add(a.arrivals, static_cast<uint32_t>(mine), __ATOMIC_RELAXED,
-                                        __HIP_MEMORY_SCOPE_AGENT) + mine == static_cast<uint32_t>(ns);
+                                        __HIP_MEMORY_SCOPE_AGENT) + mine == static_cast<uint32_t>(ns + a.list_top);
     __syncthreads();
     if (!s_last) return;
-    const int T = *a.n_top;
     static_assert(kTopCap % kThreads == 0, "the top nodes kept in LDS are dealt evenly");
     if (T < 1 || T >= a.n) {
         if (threadIdx.x == 0) atomicOr(a.status, 8);
@@ -699,6 +874,7 @@ RefitArgs refit_args(const float *verts, int64_t nv, void *bvh, int64_t n, int k
     a.n = n;
     a.chunk_log2 = chunk_log2_for(n);
     a.inf = INFINITY;
+    a.list_top = 0;
     return a;
 }
 
@@ -713,10 +889,12 @@ mg_status launch_frame_t(const RefitArgs &a, const FrameWork &w, int64_t grid, h
     return launch_status();
 }
 
-mg_status launch_refit(const float *verts, int64_t nv, void *bvh, int64_t n, int kind, hipStream_t s) {
-    const RefitArgs a = refit_args(verts, nv, bvh, n, kind);
+// build: the tree is new, so the top children are listed too, by one workgroup more.
+mg_status launch_refit(const float *verts, int64_t nv, void *bvh, int64_t n, int kind, bool build, hipStream_t s) {
+    RefitArgs a = refit_args(verts, nv, bvh, n, kind);
+    a.list_top = build;
     const int64_t C = int64_t(1) << a.chunk_log2;
-    const int grid = static_cast<int>(std::min<int64_t>(2 * ((n + C - 1) / C), 65535));
+    const int grid = static_cast<int>(std::min<int64_t>(2 * ((n + C - 1) / C), 65535)) + a.list_top;
     return kind == MG_PRIM_TRIANGLES ? launch_refit_k<true>(a, grid, s) : launch_refit_k<false>(a, grid, s);
 }
 
@@ -760,17 +938,22 @@ mg_status build_into(const float *verts, int32_t n_verts, const int32_t *faces, 
     uint32_t *hist = n ? at<uint32_t>(ws, W.hist) : nullptr;
     uint32_t *lookback = n ? at<uint32_t>(ws, W.lookback) : nullptr;
     const int64_t n_lookback = 4 * 256 * W.tiles;
-    hipLaunchKernelGGL(build_init_kernel, dim3(n_lookback > 65536 ? 256 : 16), dim3(256), 0, s, hdr,
-                       hist, lookback, n_lookback, n_prims, n_verts, prim_kind, chunk_log2_for(n_prims));
+    const int32_t *fz = prim_kind == MG_PRIM_TRIANGLES ? faces : nullptr;
+    const int grid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(blocks_for(n, 256), kBoundsBlocks)));
+    uint32_t *ka = n ? at<uint32_t>(ws, W.keys_a) : nullptr, *kb = n ? at<uint32_t>(ws, W.keys_b) : nullptr;
+    int32_t *va = n ? at<int32_t>(ws, W.vals_a) : nullptr, *vb = n ? at<int32_t>(ws, W.vals_b) : nullptr;
+    // the sums of faces wait in the sort's planes that no pass has written yet
+    float *sx = reinterpret_cast<float *>(kb), *sy = reinterpret_cast<float *>(vb), *sz = reinterpret_cast<float *>(va);
+    float *partial = n ? at<float>(ws, W.partial) : nullptr;
+    hipLaunchKernelGGL(bounds_kernel, dim3(grid), dim3(256), 0, s, verts, (int64_t)n_verts, fz, n, sx, sy, sz, partial,
+                       hdr, hist, lookback, n_lookback, prim_kind, chunk_log2_for(n_prims));
     if (launch_status() != MG_OK) return MG_ERR_HIP;
     if (n == 0) return MG_OK;
-    const int32_t *fz = prim_kind == MG_PRIM_TRIANGLES ? faces : nullptr;
-    const int grid = static_cast<int>(std::min<int64_t>(blocks_for(n, 256), 1024));
-    hipLaunchKernelGGL(bounds_kernel, dim3(grid), dim3(256), 0, s, verts, (int64_t)n_verts, fz, n, hdr);
-    uint32_t *ka = at<uint32_t>(ws, W.keys_a), *kb = at<uint32_t>(ws, W.keys_b);
-    int32_t *va = at<int32_t>(ws, W.vals_a), *vb = at<int32_t>(ws, W.vals_b);
-    hipLaunchKernelGGL(morton_kernel, dim3(grid), dim3(256), 0, s, verts, (int64_t)n_verts, fz, n, hdr, ka,
-                       hist);
+    // at most one workgroup per CU: every one adds its digit counts to the same 1024
+    // words (1M faces: 26.8 us with 1024 workgroups of 256 threads, 13.5 us so)
+    const int mgrid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(blocks_for(n, kMortonThreads), 256)));
+    hipLaunchKernelGGL(morton_kernel, dim3(mgrid), dim3(kMortonThreads), 0, s, fz ? sx : verts, fz ? sy : verts + n_verts,
+                       fz ? sz : verts + 2 * static_cast<int64_t>(n_verts), n, partial, grid, hdr, ka, hist);
     uint32_t *codes = at<uint32_t>(bvh, L.off_codes);
     int32_t *prim = at<int32_t>(bvh, L.off_prim);
     // pass p reads (src) and writes (dst): A->B, B->A, A->B, B->final
@@ -778,33 +961,29 @@ mg_status build_into(const float *verts, int32_t n_verts, const int32_t *faces, 
     const int32_t *vsrc[4] = {nullptr, vb, va, vb};
     uint32_t *kdst[4] = {kb, ka, kb, codes};
     int32_t *vdst[4] = {vb, va, vb, prim};
-    const int items = sort_items_for(n);
+    const int tile = sort_tile_for(n);
     for (int p = 0; p < 4; ++p) {
-        auto pass = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(W.tiles)), dim3(kSortThreads), 0, s, ksrc[p],
+        auto pass = [&](auto kernel, int threads) {
+            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(W.tiles)), dim3(threads), 0, s, ksrc[p],
                                vsrc[p], kdst[p], vdst[p], n, 8 * p, hist + 256 * p,
                                lookback + static_cast<int64_t>(p) * 256 * W.tiles, &hdr->tile_counter[p],
                                &hdr->status);
         };
-        if (items <= 2) pass(radix_pass_kernel<2>);
-        else if (items <= 4) pass(radix_pass_kernel<4>);
-        else if (items <= 8) pass(radix_pass_kernel<8>);
-        else pass(radix_pass_kernel<16>);
+        if (tile <= 512) pass(radix_pass_kernel<2>, sort_threads(2));
+        else if (tile <= 1024) pass(radix_pass_kernel<4>, sort_threads(4));
+        else if (tile <= 2048) pass(radix_pass_kernel<8>, sort_threads(8));
+        else pass(radix_pass_kernel<16>, sort_threads(16));
     }
-    hipLaunchKernelGGL(hierarchy_kernel, dim3(blocks_for(n, 256)), dim3(256), 0, s, codes, prim,
+    hipLaunchKernelGGL(hierarchy_kernel, dim3(blocks_for(n, kHierThreads)), dim3(kHierThreads), 0, s, codes, prim,
                        at<int32_t>(bvh, L.off_inv_prim), n, fz,
                        fz ? at<int32_t>(bvh, L.off_leaf_faces) : nullptr, at<int32_t>(bvh, L.off_leaf_parent),
                        at<int32_t>(bvh, L.off_node_parent), at<int32_t>(bvh, L.off_node_aux),
                        at<int32_t>(bvh, L.off_child), at<int32_t>(bvh, L.off_top_nodes), at<int32_t>(bvh, L.off_subtrees),
-                       at<float>(bvh, L.off_nodes), hdr, chunk_log2_for(n));
+                       hdr, chunk_log2_for(n));
     if (chunk_log2_for(n) >= 10)      // subtrees may outnumber the resident refit workgroups
         hipLaunchKernelGGL(order_subtrees_kernel, dim3(1), dim3(1024), 0, s, at<int32_t>(bvh, L.off_subtrees), n, hdr);
-    hipLaunchKernelGGL(top_child_kernel, dim3(static_cast<unsigned>(std::min<int64_t>(blocks_for(n, 256), 64))),
-                       dim3(256), 0, s, at<int32_t>(bvh, L.off_node_aux), at<int32_t>(bvh, L.off_top_nodes),
-                       at<int32_t>(bvh, L.off_node_parent), at<int32_t>(bvh, L.off_leaf_parent),
-                       at<int32_t>(bvh, L.off_subtrees), n, at<int32_t>(bvh, L.off_top_child), hdr);
     if (launch_status() != MG_OK) return MG_ERR_HIP;
-    return launch_refit(verts, n_verts, bvh, n, prim_kind, s);
+    return launch_refit(verts, n_verts, bvh, n, prim_kind, true, s);
 }
 
 }  // namespace
@@ -823,11 +1002,11 @@ extern "C" mg_status mg_lbvh_build(const float *verts, int32_t n_verts, const in
 // symbol: kernels get the device address that hipGetSymbolAddress returns for
 // the current device.  Sized for the largest build accepted: four key/value
 // planes of 2^20 entries, the four digit histograms, and look-back words for at
-// most 256 tiles per pass (sort_items_for keeps the tile count at or below 256
+// most 256 tiles per pass (sort_tile_for keeps the tile count at or below 256
 // up to 2^20 keys).
 namespace {
 constexpr int64_t kStaticMaxPrims = MG_LBVH_STATIC_MAX_PRIMS;
-constexpr int64_t kStaticWsBytes = 4 * (4 * kStaticMaxPrims) + 4 * 4 * 256 + 4 * 4 * 256 * 256;
+constexpr int64_t kStaticWsBytes = 4 * (4 * kStaticMaxPrims) + 4 * 4 * 256 + kPartialBytes + 4 * 4 * 256 * 256;
 constexpr int kMaxDevices = 64;
 }  // namespace
 
@@ -911,5 +1090,5 @@ extern "C" mg_status mg_lbvh_refit(const float *verts, int32_t n_verts, void *bv
     if (prim_kind == MG_PRIM_POINTS && n_verts != n_prims) return MG_ERR_TOPOLOGY_MISMATCH;
     if (n_prims == 0) return MG_OK;
     if (!verts || n_verts == 0) return MG_ERR_INVALID_ARGUMENT;
-    return launch_refit(verts, n_verts, bvh, n_prims, prim_kind, as_stream(stream));
+    return launch_refit(verts, n_verts, bvh, n_prims, prim_kind, false, as_stream(stream));
 }

@@ -68,7 +68,13 @@ struct RefitArgs {
     int64_t n;
     int chunk_log2;
     float inf;                    // +infinity, set at run time (see box_min)
+    int list_top;                 // a build's refit: the top children are listed by the same launch
 };
+
+// A word of the top-children table: past the L2 when this launch writes it.
+__device__ __forceinline__ int32_t top_child_word(const RefitArgs &a, int64_t at) {
+    return a.list_top ? __hip_atomic_load(a.top_child + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : a.top_child[at];
+}
 
 // The summary a finished node hands to its parent.
 struct Sum {
@@ -538,10 +544,10 @@ __device__ void refit_top_lds_steps(const RefitArgs &a, int T, int NS, unsigned 
         pn[u] = -1;
         if (t >= a.n) continue;
         pn[u] = a.top_nodes[t];
-        ch[u][0] = a.top_child[t];
-        ch[u][1] = a.top_child[a.n + t];
-        cn[u][0] = a.top_child[2 * a.n + t];
-        cn[u][1] = a.top_child[3 * a.n + t];
+        ch[u][0] = top_child_word(a, t);
+        ch[u][1] = top_child_word(a, a.n + t);
+        cn[u][0] = top_child_word(a, 2 * a.n + t);
+        cn[u][1] = top_child_word(a, 3 * a.n + t);
     }
 #pragma unroll
     for (int u = 0; u < kTPer; ++u)
@@ -660,7 +666,7 @@ __device__ void refit_top_global_steps(const RefitArgs &a, int T, int NS, unsign
     for (int step = 0; step < kMaxSteps && *t_fin > step; ++step) {   // as in the subtree phase
         for (int t = threadIdx.x; t < T; t += kThreads) {
             if (__hip_atomic_load(g_done + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != ~0u) continue;
-            const int32_t c0 = a.top_child[t], c1 = a.top_child[a.n + t], p = a.top_nodes[t];
+            const int32_t c0 = top_child_word(a, t), c1 = top_child_word(a, a.n + t), p = a.top_nodes[t];
             if (c0 >= T || c1 >= T || (c0 < 0 && ~c0 >= NS) || (c1 < 0 && ~c1 >= NS) || p < 0 || p >= a.n - 1) {
                 atomicOr(a.status, 8);
                 continue;

@@ -1,0 +1,45 @@
+"""The build at the sizes and key distributions where its kernels change form: workgroup
+and search-window edges of the hierarchy, every tile shape of the sort, and skewed codes
+(few long ranges, or all of them), bitwise against the oracle's tree."""
+
+import numpy as np
+import pytest
+
+from gpu_helpers import need_gpu, dev
+from test_gpu_lbvh import _check_build
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def device():
+    return need_gpu()
+
+
+def _points(dist, n, rng):
+    if dist == "uniform":
+        P = rng.uniform(-1, 1, size=(3, n))
+    elif dist == "same":                       # one code: the tree follows the indices
+        P = np.full((3, n), 0.25)
+    else:                                      # one far point squeezes the others into a few codes
+        P = 1e-3 * rng.normal(size=(3, n))
+        P[:, n // 2] = 50.0
+    return P.astype(np.float32)
+
+
+@pytest.mark.parametrize("dist", ["uniform", "same", "outlier"])
+@pytest.mark.parametrize("n", [2, 63, 64, 65, 66, 129, 255, 256, 257, 258, 320, 511, 513, 1025, 5000])
+def test_build_window_edges(device, n, dist):
+    import paper_2606_00444_amd as mg
+    P = _points(dist, n, np.random.default_rng(n))
+    _check_build(mg.lbvh_build(dev(P, device), None), P, None)
+
+
+@pytest.mark.parametrize("dist", ["uniform", "outlier"])
+@pytest.mark.parametrize("n", [131072, 131073, 262145, 524289])
+def test_build_sort_tiles(device, n, dist):
+    """512-, 1024-, 2048- and 4096-key tiles, the last one nearly empty."""
+    import paper_2606_00444_amd as mg
+    P = _points(dist, n, np.random.default_rng(n))
+    print(f"build: {n} points, {dist}", flush=True)
+    _check_build(mg.lbvh_build(dev(P, device), None), P, None)
