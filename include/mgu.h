@@ -493,12 +493,29 @@ mg_status mg_point_mesh_backward(const float *verts, int32_t n_verts, const int3
                                  const int32_t *face, const float *point, const float *bary,
                                  float scale, const double *g_loss, float *g_verts, void *stream);
 
+/* mg_point_mesh_backward with the queries taken in the order order[0], order[1],
+ * ... (device int32 [n_queries] permutation, or NULL), e.g. the prim section of
+ * a MG_PRIM_POINTS BVH built over them: in Morton order neighbouring lanes add
+ * to the same faces and cache lines. */
+mg_status mg_point_mesh_backward_ordered(const float *verts, int32_t n_verts, const int32_t *faces,
+                                         int32_t n_faces, const float *queries, int32_t n_queries,
+                                         const int32_t *face, const float *point, const float *bary,
+                                         float scale, const double *g_loss, const int32_t *order,
+                                         float *g_verts, void *stream);
+
 /* g_a [3][na] += g * (2 scale_ab (a_i - b_nn_ab(i)) + 2 scale_ba sum_{j: nn_ba(j)=i} (a_i - b_j)),
  * g = *g_loss (device float64) or 1 when g_loss is NULL.  Swapping the roles
  * of a and b (and of the two maps and scales) gives the gradient w.r.t. b. */
 mg_status mg_chamfer_backward(const float *a, int32_t na, const float *b, int32_t nb,
                               const int32_t *nn_ab, const int32_t *nn_ba, float scale_ab,
                               float scale_ba, const double *g_loss, float *g_a, void *stream);
+
+/* mg_chamfer_backward with the b taken in the order order_b[0], order_b[1], ...
+ * (device int32 [nb] permutation, or NULL), as mg_point_mesh_backward_ordered. */
+mg_status mg_chamfer_backward_ordered(const float *a, int32_t na, const float *b, int32_t nb,
+                                      const int32_t *nn_ab, const int32_t *nn_ba, float scale_ab,
+                                      float scale_ba, const double *g_loss, const int32_t *order_b,
+                                      float *g_a, void *stream);
 
 /* Adam (Kingma & Ba 2015) in torch.optim.Adam's order, in place on param/m/v
  * [n] float32; step counts from 1. */

@@ -19,7 +19,7 @@ __all__ = [
     "frame_index", "vertex_buffer_update", "fill", "blend", "mesh_gaussian_update", "mesh_gaussian_update_backward",
     "LBVH", "query_order", "lbvh_bytes", "lbvh_workspace_bytes", "lbvh_build", "lbvh_build_static", "frame_update", "lbvh_refit", "closest_point_query", "closest_point_bruteforce",
     "nearest_point_query", "knn_surface_query", "mean", "chamfer", "point_mesh_backward", "chamfer_backward", "adam_step",
-    "validate_indices", "validate_finite", "version", "check_device",
+    "scatter_order", "validate_indices", "validate_finite", "version", "check_device",
 ]
 
 
@@ -466,23 +466,42 @@ def chamfer(a, bvh_a, b, bvh_b, *, out=None, add=None, kernel=None, batch=0, see
     return o
 
 
-def point_mesh_backward(verts, faces, queries, rec, scale, g_verts=None, g_loss=None):
+# Scatters of fewer items are latency bound whatever their order.
+_ORDER_MIN = 16384
+
+
+def scatter_order(bvh):
+    """The processing order for a scatter over the points of a point LBVH (a copy of its
+    Morton order, since the buffer may be rebuilt before a backward pass), or None where
+    the order does not matter."""
+    return bvh.section("prim", torch.int32, bvh.n).clone() if bvh.n >= _ORDER_MIN else None
+
+
+def _order(order, n):
+    if order is not None and _i32(order, "order").numel() != n:
+        raise ValueError(f"order has {order.numel()} entries for {n} items")
+    return order
+
+
+def point_mesh_backward(verts, faces, queries, rec, scale, g_verts=None, g_loss=None, order=None):
     """g_verts += scale * g * d(sum_q d^2_q)/dV from closest-point records rec (face, point, bary);
-    g = g_loss (a float64 device scalar) or 1."""
+    g = g_loss (a float64 device scalar) or 1.  order: an optional int32 permutation in which the
+    queries are processed."""
     if g_verts is None:
         g_verts = torch.zeros_like(verts)
-    _call("mg_point_mesh_backward", _ptr(verts), verts.shape[1], _ptr(faces), faces.shape[1], _ptr(queries),
+    _call("mg_point_mesh_backward_ordered", _ptr(verts), verts.shape[1], _ptr(faces), faces.shape[1], _ptr(queries),
           queries.shape[1], _ptr(rec["face"]), _ptr(rec["point"]), _ptr(rec["bary"]), float(scale),
-          _ptr(_f64(g_loss)), _ptr(g_verts), _stream())
+          _ptr(_f64(g_loss)), _ptr(_order(order, queries.shape[1])), _ptr(g_verts), _stream())
     return g_verts
 
 
-def chamfer_backward(a, b, nn_ab, nn_ba, scale_ab, scale_ba, g_a=None, g_loss=None):
-    """g_a += g * gradient of scale_ab * sum d_ab + scale_ba * sum d_ba w.r.t. a (g = g_loss or 1)."""
+def chamfer_backward(a, b, nn_ab, nn_ba, scale_ab, scale_ba, g_a=None, g_loss=None, order_b=None):
+    """g_a += g * gradient of scale_ab * sum d_ab + scale_ba * sum d_ba w.r.t. a (g = g_loss or 1).
+    order_b: an optional int32 permutation in which the b are processed."""
     if g_a is None:
         g_a = torch.zeros_like(a)
-    _call("mg_chamfer_backward", _ptr(a), a.shape[1], _ptr(b), b.shape[1], _ptr(nn_ab), _ptr(nn_ba),
-          float(scale_ab), float(scale_ba), _ptr(_f64(g_loss)), _ptr(g_a), _stream())
+    _call("mg_chamfer_backward_ordered", _ptr(a), a.shape[1], _ptr(b), b.shape[1], _ptr(nn_ab), _ptr(nn_ba),
+          float(scale_ab), float(scale_ba), _ptr(_f64(g_loss)), _ptr(_order(order_b, b.shape[1])), _ptr(g_a), _stream())
     return g_a
 
 

@@ -106,19 +106,21 @@ class ChamferLoss(torch.autograd.Function):
         if bvh_b is None:
             bvh_b = api.lbvh_build(b_, None)
         o = api.chamfer(a_, bvh_a, b_, bvh_b, **(query or {}))
-        ctx.save_for_backward(a_, b_, o["nn_ab"], o["nn_ba"])
+        ctx.save_for_backward(a_, b_, o["nn_ab"], o["nn_ba"], api.scatter_order(bvh_a), api.scatter_order(bvh_b))
         return o["total"].reshape(())
 
     @staticmethod
     def backward(ctx, g):
-        a, b, nn_ab, nn_ba = ctx.saved_tensors
+        a, b, nn_ab, nn_ba, order_a, order_b = ctx.saved_tensors
         na, nb = a.shape[1], b.shape[1]
         gl = g.detach().to(torch.float64).contiguous()
         ga = gb = None
         if ctx.needs_input_grad[0] and na:
-            ga = api.chamfer_backward(a, b, nn_ab, nn_ba, 1.0 / na, 1.0 / nb if nb else 0.0, _zeros(a), g_loss=gl)
+            ga = api.chamfer_backward(a, b, nn_ab, nn_ba, 1.0 / na, 1.0 / nb if nb else 0.0, _zeros(a), g_loss=gl,
+                                      order_b=order_b)
         if ctx.needs_input_grad[1] and nb:
-            gb = api.chamfer_backward(b, a, nn_ba, nn_ab, 1.0 / nb, 1.0 / na if na else 0.0, _zeros(b), g_loss=gl)
+            gb = api.chamfer_backward(b, a, nn_ba, nn_ab, 1.0 / nb, 1.0 / na if na else 0.0, _zeros(b), g_loss=gl,
+                                      order_b=order_a)
         return ga, gb, None, None
 
 
@@ -145,24 +147,24 @@ class TemplateProjectionLoss(torch.autograd.Function):
         bvh_y = targets_bvh if targets_bvh is not None else api.lbvh_build(targets, None)
         o = api.chamfer(mu, bvh_mu, targets, bvh_y, add=P, **(nn_query or {}))
         ctx.save_for_backward(v, faces, gface, bary, q_local, log_scale, offset, targets, rec["face"],
-                              rec["point"], rec["bary"], mu, o["nn_ab"], o["nn_ba"])
+                              rec["point"], rec["bary"], mu, o["nn_ab"], o["nn_ba"], api.scatter_order(bvh_y))
         return o["total"].reshape(())
 
     @staticmethod
     def backward(ctx, g):
         if not ctx.needs_input_grad[0]:
             return (None,) * 12
-        v, faces, gface, bary, q_local, log_scale, offset, targets, face, point, bq, mu, nn_ab, nn_ba = \
+        v, faces, gface, bary, q_local, log_scale, offset, targets, face, point, bq, mu, nn_ab, nn_ba, order_y = \
             ctx.saved_tensors
         gl = g.detach().to(torch.float64).contiguous()
         gv = _zeros(v)
         ny, G = targets.shape[1], mu.shape[1]
         if ny:
             api.point_mesh_backward(v, faces, targets, {"face": face, "point": point, "bary": bq}, 1.0 / ny, gv,
-                                    g_loss=gl)
+                                    g_loss=gl, order=order_y)
         if G:
             gmu = api.chamfer_backward(mu, targets, nn_ab, nn_ba, 1.0 / G, 1.0 / ny if ny else 0.0, _zeros(mu),
-                                       g_loss=gl)
+                                       g_loss=gl, order_b=order_y)
             api.mesh_gaussian_update_backward(v, faces, gface, bary, q_local, log_scale, offset, gmu, g_verts=gv)
         return (gv,) + (None,) * 11
 

@@ -66,6 +66,7 @@ class TemplateRefiner:
         self.max_steps = max_steps
         self.bvh = api.lbvh_build(verts0, faces)
         self.bvh_y = api.lbvh_build(targets, None)
+        self.order_y = api.scatter_order(self.bvh_y)
         mu0 = api.mesh_gaussian_update(verts0, faces, binding["face"], binding["bary"], binding["q_local"],
                                        binding["log_scale"], binding.get("offset"), quat=False, cov=False)["mean"]
         self.bvh_mu = api.lbvh_build(mu0, None)
@@ -101,10 +102,11 @@ class TemplateRefiner:
         api.chamfer(self.mu, self.bvh_mu, self.targets, self.bvh_y, out=dict(self.ch, loss=row[1:4]),
                     add=row[0:1], warm=True, **self.nn_query)
         if self.ny:
-            api.point_mesh_backward(self.V, self.faces, self.targets, self.rec, 1.0 / self.ny, self.gV)
+            api.point_mesh_backward(self.V, self.faces, self.targets, self.rec, 1.0 / self.ny, self.gV,
+                                    order=self.order_y)
         if self.G:
             api.chamfer_backward(self.mu, self.targets, self.ch["nn_ab"], self.ch["nn_ba"], 1.0 / self.G,
-                                 1.0 / self.ny if self.ny else 0.0, self.gmu)
+                                 1.0 / self.ny if self.ny else 0.0, self.gmu, order_b=self.order_y)
             api.mesh_gaussian_update_backward(self.V, self.faces, b["face"], b["bary"], b["q_local"],
                                               b["log_scale"], b.get("offset"), self.gmu, g_verts=self.gV)
         return row
