@@ -299,7 +299,8 @@ mg_status mg_frame_update(const float *frames, int32_t n_frames, int32_t n_verts
  *                   few queries or queries with many near-equidistant faces
  *   MG_QUERY_AUTO   BATCH with the default batch and seed on
  * batch == 0 means the default: the largest of 16, 8, 4, 2, 1 with
- * n_queries >= 2048 batch (at least 512 workgroups of four waves).  NULL
+ * n_queries >= 2048 batch (at least 512 workgroups of four waves), on triangles
+ * without hints with n_queries >= 1024 batch.  NULL
  * options also turn the seed on; with options given, seed is as set.  seed != 0 (BATCH only): each query first descends
  * greedily (nearer child first) to one leaf to start from a tight bound before
  * the wide expansion.  order (device int32 [n_queries] permutation, or NULL):

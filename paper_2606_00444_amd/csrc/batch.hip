@@ -236,7 +236,7 @@ static_assert(kBlock == 64 * kBatchWaves, "a query tile is run by the workgroup'
 
 constexpr size_t cmax(size_t a, size_t b) { return a > b ? a : b; }
 constexpr size_t kSmemBytes = cmax(cmax(refit_top_lds(kBatchTopLds), refit_sub_lds(int64_t(1) << kBatchMaxChunkLog2)),
-                                   sizeof(BatchLds<16>));
+                                   sizeof(BatchLds<true, 16>));
 static_assert(refit_sub_lds(int64_t(1) << kBatchMaxChunkLog2) <= kSmemBytes &&
                   (int64_t(1) << kBatchMaxChunkLog2) <= 2 * kBlock,
               "a subtree of the batched refit fits the workgroup's LDS and two leaves per thread");
@@ -311,7 +311,7 @@ __device__ __noinline__ void item_query(PlanHeader *h, int si, int64_t t, int64_
     const int64_t q0 = k * P.query_tile;
     const int64_t q1 = q0 + P.query_tile < q.nq ? q0 + P.query_tile : q.nq;
     batch_loop<true, M, false>(q, q0, static_cast<int64_t>(kBatchWaves) * M, q1,
-                               *reinterpret_cast<BatchLds<M> *>(smem));
+                               *reinterpret_cast<BatchLds<true, M> *>(smem));
     __builtin_amdgcn_s_waitcnt(0);          // this wave's stores have completed
     __syncthreads();
     if (threadIdx.x == 0) __hip_atomic_fetch_add(&query_done[qd], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);

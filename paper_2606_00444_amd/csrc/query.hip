@@ -121,7 +121,7 @@ __global__ __launch_bounds__(kLaneBlock) void traverse_lane_kernel(QueryArgs a) 
 // when the launch has more waves than four per SIMD hold).
 template <bool kTri, int M, int kMinWaves>
 __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_eu(kMinWaves))) void traverse_batch_kernel(QueryArgs a) {
-    __shared__ BatchLds<M> lds;
+    __shared__ BatchLds<kTri, M> lds;
     check_vertex_count(a);
     const int64_t per_block = static_cast<int64_t>(kBatchWaves) * M;
     batch_loop<kTri, M>(a, static_cast<int64_t>(blockIdx.x) * per_block, static_cast<int64_t>(gridDim.x) * per_block,
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_e
 // against one query per lane, depth-first, where a wave waits for its longest walk.
 template <int M, int K>
 __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_eu(4))) void knn_batch_kernel(QueryArgs a) {
-    __shared__ BatchLds<M, K> lds;
+    __shared__ BatchLds<true, M, K> lds;
     check_vertex_count(a);
     const int64_t per_block = static_cast<int64_t>(kBatchWaves) * M;
     batch_loop<true, M, true, K>(a, static_cast<int64_t>(blockIdx.x) * per_block,
@@ -187,18 +187,19 @@ inline const T *cat(const void *base, int64_t off) {
 }
 
 // Default traversal when the caller gives no options: the batch kernel with a
-// greedy seed descent and the largest batch (16, 8, 4, 2 or 1 queries per wave)
-// that leaves at least 512 workgroups of four waves (the autotuner's choice on
-// the workloads measured; it refines per workload).
-inline void resolve(const mg_query_options *o, int64_t nq, int &kernel, int &batch, int &seed) {
+// seed descent and the largest batch (16, 8, 4, 2 or 1 queries per wave) that
+// leaves enough workgroups of four waves: 512 where the queries start from hints
+// or search points, 256 where they start cold on triangles, whose descents fill
+// four lanes a query only with 16 (20,002 cold queries on 46,000 faces: 41 us in
+// batches of 8, 39 of 16; 10,000 hinted on 5,120 faces: 28 us of 4, 31 of 8).
+inline void resolve(const mg_query_options *o, bool cold, int64_t nq, int &kernel, int &batch, int &seed) {
     kernel = o ? o->kernel : MG_QUERY_AUTO;
     batch = o ? o->batch : 0;
     seed = o ? (o->seed != 0) : 1;
     if (kernel == MG_QUERY_AUTO) kernel = MG_QUERY_BATCH;
     if (batch <= 0) {
-        // the largest batch that still gives at least 512 workgroups (two per CU)
         batch = 16;
-        while (batch > 1 && nq < static_cast<int64_t>(2048) * batch) batch >>= 1;
+        while (batch > 1 && nq < static_cast<int64_t>(cold ? 1024 : 2048) * batch) batch >>= 1;
     }
 }
 
@@ -258,7 +259,7 @@ mg_status launch_batch(const QueryArgs &a, int waves, hipStream_t s) {
 template <bool kTri>
 mg_status launch_traverse(QueryArgs a, const mg_query_options *opts, hipStream_t s) {
     int kernel, batch;
-    resolve(opts, a.nq, kernel, batch, a.seed);
+    resolve(opts, kTri && !(opts && opts->hint), a.nq, kernel, batch, a.seed);
     const int waves = opts ? opts->waves : 0;
     a.order = opts ? opts->order : nullptr;
     a.counters = opts ? reinterpret_cast<unsigned long long *>(opts->counters) : nullptr;
@@ -291,7 +292,7 @@ mg_status launch_knn(const QueryArgs &a, hipStream_t s) {
 template <int K>
 mg_status launch_knn_k(const QueryArgs &a, hipStream_t s) {
     int kernel, batch, seed;
-    resolve(nullptr, a.nq, kernel, batch, seed);
+    resolve(nullptr, true, a.nq, kernel, batch, seed);
     if constexpr (K <= 4)
         if (batch >= 16) return launch_knn<16, K>(a, s);
     if (batch >= 8) return launch_knn<8, K>(a, s);

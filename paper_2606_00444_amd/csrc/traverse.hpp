@@ -38,9 +38,11 @@ __device__ __forceinline__ float prune_bound(float best, float qm) {
 __device__ __forceinline__ float qnorm1(f3 q) { return (fabsf(q.x) + fabsf(q.y)) + fabsf(q.z); }
 
 constexpr int kBatchWaves = 4;          // waves per workgroup of the batch kernel
-constexpr int kBatchCap = 320;          // stack entries before the pop width shrinks
+// Stack entries before the pop width shrinks, for batches of M queries: room for
+// what a triangle tree's seed descents pass by (about 38 entries each).
+constexpr int batch_cap(bool tri, int M) { return !tri || M > 16 ? 320 : M > 8 ? 704 : 448; }
 constexpr int kPopNodes = 32;           // nodes a triangle round pops: a pair of lanes each
-constexpr int kBatchAlloc = kBatchCap + 64;
+constexpr int batch_alloc(bool tri, int M) { return batch_cap(tri, M) + 64; }
 constexpr int kLeafWait = 32;           // waiting leaves that are tested together
 constexpr int kLeafNarrow = 8;          // stack entries below which waiting leaves are tested at once
 
@@ -282,10 +284,11 @@ __device__ __forceinline__ StackEntry make_entry(float bound, uint32_t slot, uin
     return (static_cast<StackEntry>((__float_as_uint(bound) & ~kSlotMask) | slot) << 32) | node;
 }
 
-template <int M, int K>
+template <bool kTri, int M, int K>
 struct WaveStack {
+    static constexpr int kCap = batch_cap(kTri, M), kAlloc = batch_alloc(kTri, M);
     static_assert(M <= kSlotMask + 1, "an entry holds its query's slot in five bits");
-    StackEntry e[kBatchAlloc];
+    StackEntry e[kAlloc];
     float4 q[M];                        // per query of the batch: the point, and prune_bound of its best
     unsigned long long best[M][K];      // the nearest faces, sorted: (d^2 bits, original id)
     uint32_t code[M];                   // where the best face lies (a record slot); only a guess, see leaf_of
@@ -300,9 +303,9 @@ struct WaveMail {
     int32_t outstanding[kBatchWaves];   // chunks of each wave's batch held elsewhere
 };
 
-template <int M, int K = 1>
+template <bool kTri, int M, int K = 1>
 struct BatchLds {
-    WaveStack<M, K> st[kBatchWaves];
+    WaveStack<kTri, M, K> st[kBatchWaves];
     WaveMail mail;
 };
 
@@ -366,8 +369,8 @@ __device__ __forceinline__ void insert_nearest(unsigned long long *best, int k, 
 }
 
 // Lowers the prune bounds of wave `O`'s M queries to their k-th nearest.
-template <int M, int K>
-__device__ __forceinline__ void lower_bounds(WaveStack<M, K> &O, int k, int lane) {
+template <bool kTri, int M, int K>
+__device__ __forceinline__ void lower_bounds(WaveStack<kTri, M, K> &O, int k, int lane) {
     wave_sync();                              // the insertions of every lane
     if (lane < M) {
         const float4 q = O.q[lane];
@@ -381,11 +384,11 @@ __device__ __forceinline__ void lower_bounds(WaveStack<M, K> &O, int k, int lane
 // per lane.  A face at most as far as its query's best lowers the best and the
 // prune bound (both by LDS atomics: other waves may hold chunks of the batch).
 template <bool kTri, int M, int K>
-__device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<M, K> &S, WaveStack<M, K> &O, int lc, int cnt,
+__device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<kTri, M, K> &S, WaveStack<kTri, M, K> &O, int lc, int cnt,
                                            BatchStats &stats) {
     const int lane = threadIdx.x % 64;
     bool act = lane < cnt;
-    const StackEntry en = S.e[kBatchAlloc - lc + (act ? lane : 0)];
+    const StackEntry en = S.e[S.kAlloc - lc + (act ? lane : 0)];
     const uint32_t hi = static_cast<uint32_t>(en >> 32), code = static_cast<uint32_t>(en), slot = hi & kSlotMask;
     const float4 q = O.q[slot];
     act = act && __uint_as_float(hi & ~kSlotMask) <= q.w;   // its parent may have fallen behind by now
@@ -405,7 +408,7 @@ __device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<M, K> &
             }
         }
     }
-    if (K > 1) lower_bounds<M, K>(O, a.k, lane);
+    if (K > 1) lower_bounds<kTri, M, K>(O, a.k, lane);
     return lc - cnt;
 }
 
@@ -414,7 +417,7 @@ __device__ __forceinline__ int test_leaves(const QueryArgs &a, WaveStack<M, K> &
 // round settles it; with a box test this cheap, a child per lane only doubles
 // the rest of the round (100,000 nearest points of 100,000: 75-87 -> 54-70 us).
 template <int M, int K>
-__device__ __forceinline__ void point_round(const QueryArgs &a, WaveStack<M, K> &S, WaveStack<M, K> &O, uint32_t n_nodes,
+__device__ __forceinline__ void point_round(const QueryArgs &a, WaveStack<false, M, K> &S, WaveStack<false, M, K> &O, uint32_t n_nodes,
                                             int take, int &sp, BatchStats &stats) {
     const int lane = threadIdx.x % 64;
     const bool pop = lane < take;
@@ -458,8 +461,8 @@ __device__ __forceinline__ void point_round(const QueryArgs &a, WaveStack<M, K> 
     sp += __popcll(bl) + __popcll(br);
 }
 
-// Rounds over wave `self`'s stack (sp entries) until it is empty.  Entries
-// belong to the batch of wave `owner`: its query points and bests.
+// Rounds over wave `self`'s stack (sp entries, and lc waiting leaves) until it is
+// empty.  Entries belong to the batch of wave `owner`: its query points and bests.
 //
 // A round pops up to 32 nodes and gives each child to a lane of its own.  Every
 // lane bounds its child without a branch; internal children that survive are
@@ -476,14 +479,14 @@ __device__ __forceinline__ void point_round(const QueryArgs &a, WaveStack<M, K> 
 // joint bound of child_bound, 55% of the time issuing VALU; 1M on 500,000 faces:
 // 5,980 -> 1,340 us, 80% issuing and 6.6 TB/s of cache-line misses.
 template <bool kTri, int M, int K>
-__device__ void run_stack(const QueryArgs &a, BatchLds<M, K> &L, int self, int owner, int sp, BatchStats &stats) {
+__device__ void run_stack(const QueryArgs &a, BatchLds<kTri, M, K> &L, int self, int owner, int sp, int lc,
+                          BatchStats &stats) {
     const int lane = threadIdx.x % 64;
     const uint32_t n_nodes = static_cast<uint32_t>(a.n - 1), odd = lane & 1;
-    WaveStack<M, K> &S = L.st[self];
-    WaveStack<M, K> &O = L.st[owner];
+    WaveStack<kTri, M, K> &S = L.st[self];
+    WaveStack<kTri, M, K> &O = L.st[owner];
     WaveMail &mail = L.mail;
-    int lc = 0;                               // waiting leaves
-    // the stack never exceeds kBatchCap + 62: a round of width k pushes at most
+    // the stack never exceeds kCap + 62: a round of width k pushes at most
     // 2k entries (nodes and leaves together), widths are cut to half the room
     // left, the leaves are tested whenever room runs out, and width-1 rounds are
     // a plain depth-first walk whose growth is bounded by the tree depth; each
@@ -492,7 +495,7 @@ __device__ void run_stack(const QueryArgs &a, BatchLds<M, K> &L, int self, int o
     const int64_t max_rounds = 2 * static_cast<int64_t>(M + 1) * a.n + 64;
     for (int64_t round = 0; sp + lc > 0 && round < max_rounds; ++round) {
         wave_sync();                          // the previous round's pushes, or the entries handed in
-        if (lc >= kLeafWait || (lc > 0 && (sp < kLeafNarrow || sp + lc > kBatchCap - 2 * kPopNodes))) {
+        if (lc >= kLeafWait || (lc > 0 && (sp < kLeafNarrow || sp + lc > S.kCap - 2 * kPopNodes))) {
             lc = test_leaves<kTri, M, K>(a, S, O, lc, lc < 64 ? lc : 64, stats);
             wave_sync();
             if (sp == 0) continue;
@@ -514,9 +517,9 @@ __device__ void run_stack(const QueryArgs &a, BatchLds<M, K> &L, int self, int o
         }
         constexpr int kPop = kTri ? kPopNodes : 2 * kPopNodes;
         int take = sp < kPop ? sp : kPop;
-        const int room = (kBatchCap - sp - lc) / 2;
+        const int room = (S.kCap - sp - lc) / 2;
         if (take > room) take = room > 1 ? room : 1;
-        if (sp + lc + take > kBatchAlloc) {   // past the bound of a valid tree
+        if (sp + lc + take > S.kAlloc) {   // past the bound of a valid tree
             if (lane == 0) atomicOr(a.status, 64);
             break;
         }
@@ -551,7 +554,7 @@ __device__ void run_stack(const QueryArgs &a, BatchLds<M, K> &L, int self, int o
         const float even = odd ? other : mine, far = odd ? mine : other;
         int pos = sp + rank_below(pm);
         if (even <= far && far < INFINITY) pos += odd ? -1 : 1;      // the even lane's child is the nearer: swap
-        if (leaf) pos = kBatchAlloc - 1 - lc - rank_below(lm);
+        if (leaf) pos = S.kAlloc - 1 - lc - rank_below(lm);
         if (push || leaf)
             S.e[pos] = leaf ? (static_cast<StackEntry>(hi) << 32) | (2 * node + odd)
                             : make_entry(d, slot, static_cast<uint32_t>(ref));
@@ -563,8 +566,8 @@ __device__ void run_stack(const QueryArgs &a, BatchLds<M, K> &L, int self, int o
 
 // Takes the mailbox's chunk, if there is one, onto wave `self`'s (empty) stack:
 // its size, and the wave whose batch it belongs to; -1 if there is none.
-template <int M, int K>
-__device__ __forceinline__ int take_chunk(const QueryArgs &a, BatchLds<M, K> &L, int self, int &owner) {
+template <bool kTri, int M, int K>
+__device__ __forceinline__ int take_chunk(const QueryArgs &a, BatchLds<kTri, M, K> &L, int self, int &owner) {
     const int lane = threadIdx.x % 64;
     WaveMail &mail = L.mail;
     int got = 0;
@@ -623,10 +626,22 @@ __device__ __forceinline__ unsigned long long quad_xor64(unsigned long long v) {
 // each lane), and its record slot in `code`.  With one node kept, both children
 // in a lane and every leaf on the way tested, 20,002 cold queries on 46,000 faces
 // took 58 us and expanded 52 nodes each, the walk included; now 41 us and 30.
-template <bool kTri, int kLanes>
-__device__ __forceinline__ unsigned long long seed_descent(const QueryArgs &a, f3 p, bool need, uint32_t &code) {
+//
+// kKeep: the children that the walk passes by go to the stack (K.nodes entries)
+// and the leaves it meets to the waiting leaves (K.leaves), with their bounds, so
+// that the rounds go on from them instead of walking from the root again.
+struct Kept {
+    StackEntry *e;
+    int cap, alloc;                     // of the stack
+    int nodes, leaves;
+    bool full;                          // they did not fit, or the walk ended early: start from the root
+};
+
+template <bool kTri, int kLanes, bool kKeep>
+__device__ __forceinline__ unsigned long long seed_descent(const QueryArgs &a, f3 p, bool need, uint32_t &code, Kept &K,
+                                                           BatchStats &stats) {
     const uint32_t lane = threadIdx.x % 64, odd = lane & 1, pair = (lane >> 1) & (kLanes / 2 - 1);
-    const uint32_t n_nodes = static_cast<uint32_t>(a.n - 1);
+    const uint32_t n_nodes = static_cast<uint32_t>(a.n - 1), slot = lane / kLanes;
     const float dq = slab_query_margin(p);
     uint32_t node = need && pair == 0 ? 0u : ~0u;
     float leaf_key = INFINITY;
@@ -635,24 +650,34 @@ __device__ __forceinline__ unsigned long long seed_descent(const QueryArgs &a, f
         const bool act = node < n_nodes;
         if (!__ballot(act)) break;
         uint32_t key = ~0u, ref = ~0u;
+        float bound = 0.0f;
+        bool leaf = false;
         if (act) {
             const float4 *rec = a.nodes + 6 * static_cast<uint64_t>(node) + 3 * odd;
             const float4 c0 = rec[0], c1 = rec[1], c2 = kTri ? rec[2] : c1;
             const uint32_t r = static_cast<uint32_t>(__float_as_int(c0.w));
             if (static_cast<int32_t>(r) < 0) {
-                const float b = leaf_box_dist2<kTri>(p, c0, c1, c2);
-                if (b <= leaf_key) {
-                    leaf_key = b;
+                leaf = true;
+                bound = leaf_box_dist2<kTri>(p, c0, c1, c2);
+                if (bound <= leaf_key) {
+                    leaf_key = bound;
                     leaf_code = 2 * node + odd;
                 }
             } else {
-                key = __float_as_uint(child_bound<kTri>(p, dq, c0, c1, c2));
+                bound = child_bound<kTri>(p, dq, c0, c1, c2);
+                key = __float_as_uint(bound);
                 ref = r;
             }
+        }
+        const uint32_t here = 2 * node + odd;
+        if (a.counters) {
+            stats.exp += __popcll(__ballot(act)) / 2;
+            stats.lbox += __popcll(__ballot(leaf));
         }
         // unique keys within the query's lanes, absent children last
         key = (key & ~3u) | (lane & 3);
         if (kLanes == 2) {
+            static_assert(!kKeep || kLanes == 4, "kept with two nodes a level");
             const uint32_t other = quad_xor<1>(key), other_ref = quad_xor<1>(ref);
             node = other < key ? other_ref : ref;
         } else {
@@ -665,9 +690,22 @@ __device__ __forceinline__ unsigned long long seed_descent(const QueryArgs &a, f
             x |= quad_xor<2>(x);
             y |= quad_xor<2>(y);
             node = (pair ? y : x) - 1;
+            if (kKeep) {
+                const bool by = ref != ~0u && rank >= 2;
+                const uint64_t bm = __ballot(by), lm = __ballot(leaf);
+                K.full = K.full || K.nodes + K.leaves + __popcll(bm) + __popcll(lm) > K.cap;
+                if (!K.full) {
+                    if (by) K.e[K.nodes + rank_below(bm)] = make_entry(bound, slot, ref);
+                    if (leaf) K.e[K.alloc - 1 - K.leaves - rank_below(lm)] = make_entry(bound, slot, here);
+                    K.nodes += __popcll(bm);
+                    K.leaves += __popcll(lm);
+                }
+            }
         }
     }
+    if (kKeep && __ballot(node < n_nodes)) K.full = true;     // deeper than the walk: nothing kept below its last level
     unsigned long long best = ~0ull;
+    if (a.counters && !kKeep) stats.lex += __popcll(__ballot(leaf_code != ~0u));   // kept leaves count when the rounds test them
     if (leaf_code != ~0u) {
         int32_t id;
         const float d2 = slot_dist2<kTri>(a, p, leaf_code, id);
@@ -686,11 +724,19 @@ __device__ __forceinline__ unsigned long long seed_descent(const QueryArgs &a, f
 }
 
 // Starts a wave's batch [qb, qb + nb): points, starting bests (a hint's
-// distance, else the seed descent's, else max_dist2) and the root on the stack.
-// Returns the stack's size.
+// distance, else the seed descent's, else max_dist2) and, on the stack, the root
+// or what the descent passed by.  Returns the stack's size, and the number of
+// waiting leaves in lc.
+//
+// Going on from the descents' paths took 50,000 cold queries on 40,000 faces from
+// 98 to 81 us, 20,002 on 46,000 faces from 43 to 39.
 template <bool kTri, int M, int K>
-__device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M, K> &S, int64_t qb, int nb) {
+__device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<kTri, M, K> &S, int64_t qb, int nb, int &lc,
+                                           BatchStats &stats) {
     constexpr int kLanes = M <= 16 ? 4 : 2;       // lanes of a query
+    constexpr bool kKeep = kTri && M <= 16;
+    Kept kept{S.e, S.kCap, S.kAlloc, 0, 0, false};
+    bool walked = false;                          // this lane's query was in the descent
     const int lane = threadIdx.x % 64, i = lane / kLanes;
     const unsigned long long none = pack_best(a.maxd2, INT_MAX);
     const int64_t qid = i < nb ? query_at(a, qb + i) : -1;
@@ -715,7 +761,8 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M, K> &
             for (int j = 0; j < K; ++j) S.best[i][j] = none;
         wave_sync();
         uint32_t at;
-        (void)seed_descent<kTri, kLanes>(a, p, own, at);
+        (void)seed_descent<kTri, kLanes, kKeep>(a, p, own, at, kept, stats);
+        walked = own;
         if (own && at < 2 * static_cast<uint32_t>(a.n - 1)) {
             const int64_t leaf = ~static_cast<int64_t>(__float_as_int(a.nodes[3 * static_cast<uint64_t>(at)].w));
             int64_t first = leaf - K / 2 < a.n - K ? leaf - K / 2 : a.n - K;
@@ -758,7 +805,8 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M, K> &
         const bool need = a.seed && own && !hinted;
         if (__ballot(need)) {
             uint32_t at;
-            const unsigned long long c = seed_descent<kTri, kLanes>(a, p, need, at);
+            const unsigned long long c = seed_descent<kTri, kLanes, kKeep>(a, p, need, at, kept, stats);
+            walked = need;
             if (need && c < best) {
                 best = c;
                 code = at;
@@ -776,9 +824,35 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M, K> &
             for (int j = 1; j < K; ++j) S.best[i][j] = none;
         S.code[i] = code;
     }
+    int sp = 0;
+    lc = 0;
+    if (kKeep && !kept.full) {
+        // of what the descent passed by, the entries that the starting bests leave
+        wave_sync();
+        for (int at = 0; at < kept.nodes; at += 64) {
+            const StackEntry en = S.e[at + lane < kept.nodes ? at + lane : 0];
+            const uint32_t hi = static_cast<uint32_t>(en >> 32);
+            const bool keep = at + lane < kept.nodes && __uint_as_float(hi & ~kSlotMask) <= S.q[hi & kSlotMask].w;
+            const uint64_t km = __ballot(keep);
+            wave_sync();                          // read before any lane writes
+            if (keep) S.e[sp + rank_below(km)] = en;
+            sp += __popcll(km);
+        }
+        for (int at = 0; at < kept.leaves; at += 64) {
+            const StackEntry en = S.e[S.kAlloc - 1 - (at + lane < kept.leaves ? at + lane : 0)];
+            const uint32_t hi = static_cast<uint32_t>(en >> 32);
+            const bool keep = at + lane < kept.leaves && __uint_as_float(hi & ~kSlotMask) <= S.q[hi & kSlotMask].w &&
+                              (K > 1 || static_cast<uint32_t>(en) != S.code[hi & kSlotMask]);   // not the start itself
+            const uint64_t km = __ballot(keep);
+            wave_sync();
+            if (keep) S.e[S.kAlloc - 1 - lc - rank_below(km)] = en;
+            lc += __popcll(km);
+        }
+        push = push && !walked;
+    }
     const uint64_t bm = __ballot(push);
-    if (push) S.e[rank_below(bm)] = make_entry(rd, static_cast<uint32_t>(i), 0u);
-    return __popcll(bm);
+    if (push) S.e[sp + rank_below(bm)] = make_entry(rd, static_cast<uint32_t>(i), 0u);
+    return sp + __popcll(bm);
 }
 
 // Final record of the query in slot `lane` of the batch, its index qid: the
@@ -786,7 +860,7 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<M, K> &
 // the best may be another face's (two waves lowering one best race on it), so
 // its id is checked, and the face's slot is looked up where they differ.
 template <bool kTri, int M>
-__device__ __forceinline__ void finish_query(const QueryArgs &a, const WaveStack<M, 1> &S, int lane, int64_t qid) {
+__device__ __forceinline__ void finish_query(const QueryArgs &a, const WaveStack<kTri, M, 1> &S, int lane, int64_t qid) {
     const unsigned long long b = S.best[lane][0];
     const float4 q = S.q[lane];
     const f3 p = f3{q.x, q.y, q.z};
@@ -823,7 +897,7 @@ __device__ __forceinline__ void finish_query(const QueryArgs &a, const WaveStack
 // inverse-distance weights 1 / (d + eps) (the weighted nearest-neighbour
 // NearestSurface of Sec. 3.3); a face at distance 0 gives its own point.
 template <int M, int K>
-__device__ __forceinline__ void finish_nearest(const QueryArgs &a, const WaveStack<M, K> &S, int64_t qb, int nb) {
+__device__ __forceinline__ void finish_nearest(const QueryArgs &a, const WaveStack<true, M, K> &S, int64_t qb, int nb) {
     static_assert(M * K <= 64, "a lane per query and place");
     const int lane = threadIdx.x % 64, i = lane / K < M ? lane / K : 0, j = lane % K;
     const bool own = lane < M * K && i < nb;
@@ -893,10 +967,10 @@ __device__ __forceinline__ void finish_nearest(const QueryArgs &a, const WaveSta
 // exactly.  Each turn of the loop runs one stack, the wave's own or a chunk, so
 // the rounds are compiled once.
 template <bool kTri, int M, bool kHelpBetween = true, int K = 1>
-__device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, int64_t q_end, BatchLds<M, K> &L) {
+__device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, int64_t q_end, BatchLds<kTri, M, K> &L) {
     const int lane = threadIdx.x % 64;
     const int self = uniform(static_cast<int>(threadIdx.x / 64));
-    WaveStack<M, K> &S = L.st[self];
+    WaveStack<kTri, M, K> &S = L.st[self];
     WaveMail &mail = L.mail;
     BatchStats stats;
     if (threadIdx.x == 0) {
@@ -917,11 +991,11 @@ __device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, in
     bool between = false;                     // a batch was written: chunks go before the next
     bool told = false;                        // this wave's last batch is counted in mail.done
     for (int spin = 0;;) {
-        int owner = -1, sp = -1;
-        if (open || between || qb >= q_end) sp = take_chunk<M, K>(a, L, self, owner);
+        int owner = -1, sp = -1, lc = 0;
+        if (open || between || qb >= q_end) sp = take_chunk<kTri, M, K>(a, L, self, owner);
         const int nb = static_cast<int>(q_end - qb < M ? q_end - qb : M);
         if (sp < 0 && !open && qb < q_end) {
-            sp = start_batch<kTri, M, K>(a, S, qb, nb);
+            sp = start_batch<kTri, M, K>(a, S, qb, nb, lc, stats);
             owner = self;
             open = true;
             between = false;
@@ -930,7 +1004,7 @@ __device__ void batch_loop(const QueryArgs &a, int64_t start, int64_t stride, in
         }
         if (sp >= 0) {
             spin = 0;
-            if (sp > 0) run_stack<kTri, M, K>(a, L, self, owner & (kBatchWaves - 1), sp, stats);
+            if (sp + lc > 0) run_stack<kTri, M, K>(a, L, self, owner & (kBatchWaves - 1), sp, lc, stats);
             if (owner >= kBatchWaves && lane == 0) lds_add(&mail.outstanding[owner & (kBatchWaves - 1)], -1);
         }
         // chunks given away must be finished before the results are final

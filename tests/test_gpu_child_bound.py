@@ -82,3 +82,31 @@ def test_knn_does_not_depend_on_the_batch(device, k):
         part = mg.knn_surface_query(bvh, Vd, Qd[:, :n].contiguous(), k=k, eps=1e-6, max_dist2=0.3)
         for key in ("face", "dist2", "point"):
             assert torch.equal(part[key], whole[key][:, :n]), (n, key)
+
+
+@pytest.mark.parametrize("nf", [2, 300, 5000])
+@pytest.mark.parametrize("kind", ["doubling", "same"])
+def test_cold_queries_on_deep_trees(device, nf, kind):
+    """A seed descent that passes by more than the stack holds starts from the root again:
+    sizes doubling from face to face, then coincident faces, both far deeper than a mesh."""
+    import paper_2606_00444_amd as mg
+    rng = np.random.default_rng(nf)
+    if kind == "doubling":
+        c = np.exp2(-(np.arange(nf) % 24)).reshape(nf, 1, 1) * np.ones((1, 1, 3))
+        V = c * (1 + 0.2 * rng.normal(size=(nf, 3, 3)))
+    else:
+        V = np.broadcast_to(rng.normal(size=(1, 3, 3)), (nf, 3, 3)) + np.zeros((nf, 1, 1))
+        V = np.concatenate([V, 5 + rng.normal(size=(3, 3, 3))])
+    V = np.ascontiguousarray(V.reshape(-1, 3).T.astype(np.float32))
+    F = np.ascontiguousarray(np.arange(V.shape[1], dtype=np.int32).reshape(-1, 3).T)
+    Q = np.concatenate([np.exp2(rng.uniform(-24, 1, size=(1, 500))) * rng.uniform(0.9, 1.1, size=(3, 500)),
+                        rng.uniform(-1, 6, size=(3, 500))], axis=1).astype(np.float32)
+    Vd, Fd, Qd = dev(V, device), dev(F, device), dev(Q, device)
+    ref = mg.closest_point_bruteforce(Vd, Fd, Qd)
+    bvh = mg.lbvh_build(Vd, Fd)
+    for batch in (1, 2, 4, 8, 16, 32):
+        r = mg.closest_point_query(bvh, Vd, Qd, kernel="batch", batch=batch, seed=True)
+        assert torch.equal(r["face"], ref["face"]) and torch.equal(r["dist2"], ref["dist2"]), batch
+    if kind == "doubling":
+        for k in (2, 4):
+            check_knn_result(mg.knn_surface_query(bvh, Vd, Qd, k=k, eps=1e-6), V, F, Q, k, 1e-6, float("inf"))
