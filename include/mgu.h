@@ -424,6 +424,14 @@ mg_status mg_sdf_update(const float *verts, int32_t n_verts, const int32_t *face
                         const int32_t *face_k, int32_t k, float lo_x, float lo_y, float lo_z, float h,
                         int32_t nx, int32_t ny, int32_t nz, float *sdf, int32_t *face, void *stream);
 
+/* mg_sdf_update with room for the faces' current corners: records (device, 16-byte
+ * aligned, 48 n_faces bytes), written by the call where that makes it faster, and not
+ * read by later ones.  Results are mg_sdf_update's; NULL or fewer bytes are allowed. */
+mg_status mg_sdf_update_records(const float *verts, int32_t n_verts, const int32_t *faces, int32_t n_faces,
+                                const int32_t *face_k, int32_t k, float lo_x, float lo_y, float lo_z, float h,
+                                int32_t nx, int32_t ny, int32_t nz, float *sdf, int32_t *face,
+                                void *records, size_t records_bytes, void *stream);
+
 /* out [n_queries] (device) <- trilinear interpolation of the node values sdf at
  * queries [3][n_queries]; +inf for a query outside the grid's box. */
 mg_status mg_sdf_sample(const float *sdf, float lo_x, float lo_y, float lo_z, float h, int32_t nx, int32_t ny,

@@ -62,14 +62,44 @@ __global__ __launch_bounds__(256) void sdf_update_kernel(const float *__restrict
     }
 }
 
+// The faces' current corners as records of three float4 (nine floats, 48 bytes):
+// written once per face, they leave a node three wide gathers per face where the
+// index and vertex arrays take twelve of four bytes.
+constexpr int kRecord = 3;
+
+// At 40,000 faces the pass costs about 4 us, a launch and one chain of loads; at
+// 500,000 about 12.
+__global__ __launch_bounds__(256) void face_record_kernel(const float *__restrict__ verts, int64_t nv,
+                                                          const int32_t *__restrict__ faces, int64_t nf,
+                                                          float4 *__restrict__ rec) {
+    const int64_t f = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (f >= nf) return;
+    f3 c[3];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+        const int64_t id = faces[j * nf + f];
+        c[j] = load3(verts, nv, id >= 0 && id < nv ? id : 0);   // a face no node stores may hold any ids
+    }
+    rec[kRecord * f] = make_float4(c[0].x, c[0].y, c[0].z, c[1].x);
+    rec[kRecord * f + 1] = make_float4(c[1].y, c[1].z, c[2].x, c[2].y);
+    rec[kRecord * f + 2] = make_float4(c[2].z, 0.0f, 0.0f, 0.0f);
+}
+
 // The values of sdf_update_kernel for a compile-time k: every face id and vertex of
 // a node is loaded before any distance is computed (ids outside the mesh read face 0
 // and do not count), so the gathers overlap instead of forming one chain per face,
 // and the winner's sign is taken once, after the minimum.  Node coordinates use
 // 32-bit index arithmetic (grids have fewer than 2^31 nodes).
-template <int K>
+//
+// Bound by the vector cache, which serves a lane's scattered load at a time: 4 faces
+// a node are 48 loads from the index and vertex arrays.  kPacked takes them from the
+// records of face_record_kernel, 12 loads: 262,144 nodes, k = 4, 40,000 faces
+// 17.1 -> 12.1 us with the pass that writes them; 128^3 nodes 84 -> 36 us.  Bricks
+// of 4^3, 8 x 8 or 16 x 4 nodes a wave gain the records nothing (12.2, 11.7, ~12 us).
+template <int K, bool kPacked>
 __global__ __launch_bounds__(256) void sdf_update_k_kernel(const float *__restrict__ verts, int64_t nv,
                                                            const int32_t *__restrict__ faces, int64_t nf,
+                                                           const float4 *__restrict__ rec,
                                                            const int32_t *__restrict__ face_k, Grid g, int64_t n,
                                                            float *__restrict__ sdf, int32_t *__restrict__ face_out) {
     const int64_t stride = static_cast<int64_t>(gridDim.x) * 256;
@@ -89,9 +119,17 @@ __global__ __launch_bounds__(256) void sdf_update_k_kernel(const float *__restri
         f3 A[K], B[K], C[K];
 #pragma unroll
         for (int s = 0; s < K; ++s) {
-            A[s] = load3(verts, nv, faces[fid[s]]);
-            B[s] = load3(verts, nv, faces[nf + fid[s]]);
-            C[s] = load3(verts, nv, faces[2 * nf + fid[s]]);
+            if (kPacked) {
+                const float4 *r = rec + kRecord * static_cast<int64_t>(fid[s]);
+                const float4 r0 = r[0], r1 = r[1];
+                A[s] = f3{r0.x, r0.y, r0.z};
+                B[s] = f3{r0.w, r1.x, r1.y};
+                C[s] = f3{r1.z, r1.w, r[2].x};
+            } else {
+                A[s] = load3(verts, nv, faces[fid[s]]);
+                B[s] = load3(verts, nv, faces[nf + fid[s]]);
+                C[s] = load3(verts, nv, faces[2 * nf + fid[s]]);
+            }
         }
         float best = INFINITY, bw1 = 0.0f, bw2 = 0.0f;
         int32_t win = -1;
@@ -113,6 +151,17 @@ __global__ __launch_bounds__(256) void sdf_update_k_kernel(const float *__restri
         sdf[v] = side * sqrtf(best);
         if (face_out) face_out[v] = win;
     }
+}
+
+template <int K>
+void launch_update_k(int grid, hipStream_t st, const float *verts, int64_t nv, const int32_t *faces, int64_t nf,
+                     const float4 *rec, const int32_t *face_k, const Grid &g, int64_t n, float *sdf, int32_t *face) {
+    if (rec)
+        hipLaunchKernelGGL((sdf_update_k_kernel<K, true>), dim3(grid), dim3(256), 0, st, verts, nv, faces, nf, rec,
+                           face_k, g, n, sdf, face);
+    else
+        hipLaunchKernelGGL((sdf_update_k_kernel<K, false>), dim3(grid), dim3(256), 0, st, verts, nv, faces, nf, rec,
+                           face_k, g, n, sdf, face);
 }
 
 __global__ __launch_bounds__(256) void sdf_sample_kernel(const float *__restrict__ sdf, Grid g,
@@ -162,29 +211,49 @@ extern "C" mg_status mg_grid_points(float lo_x, float lo_y, float lo_z, float h,
     return launch_status();
 }
 
-extern "C" mg_status mg_sdf_update(const float *verts, int32_t n_verts, const int32_t *faces, int32_t n_faces,
-                                   const int32_t *face_k, int32_t k, float lo_x, float lo_y, float lo_z, float h,
-                                   int32_t nx, int32_t ny, int32_t nz, float *sdf, int32_t *face, void *stream) {
+// The records pay from about half a million stored ids on, if they are at least as
+// many as the faces (us without and with records):
+//   40,000 faces: 64^3 nodes, k = 1 6.2 / 7.9; 48^3, k = 4 9.6 / 10.0; 64^3, k = 2 9.8 / 9.5; k = 4 17.1 / 12.1
+//   500,000 faces: 64^3, k = 1 13.4 / 19.0; k = 2 21.3 / 21.9; k = 4 36.0 / 26.7; k = 8 67.5 / 37.1
+static bool packs(int64_t n, int32_t k, int64_t nf, const void *records, size_t records_bytes) {
+    return records && records_bytes >= kRecord * sizeof(float4) * static_cast<size_t>(nf) && nf > 0 &&
+           (k == 1 || k == 2 || k == 4 || k == 8) && n * k >= (1 << 19) && n * k >= nf;
+}
+
+extern "C" mg_status mg_sdf_update_records(const float *verts, int32_t n_verts, const int32_t *faces, int32_t n_faces,
+                                           const int32_t *face_k, int32_t k, float lo_x, float lo_y, float lo_z,
+                                           float h, int32_t nx, int32_t ny, int32_t nz, float *sdf, int32_t *face,
+                                           void *records, size_t records_bytes, void *stream) {
     int64_t n = 0;
     if (bad_grid(h, nx, ny, nz, n) || bad_count(n_verts) || bad_count(n_faces) || k < 1 || k > 64 || !face_k ||
-        !sdf || (n_faces > 0 && (!verts || !faces)))
+        !sdf || (n_faces > 0 && (!verts || !faces)) || reinterpret_cast<uintptr_t>(records) % sizeof(float4))
         return MG_ERR_INVALID_ARGUMENT;
     const Grid g{lo_x, lo_y, lo_z, h, nx, ny, nz};
     const int grid = static_cast<int>(std::min<int64_t>(blocks_for(n, 256), 8192));
     hipStream_t st = as_stream(stream);
     const int64_t nv = n_verts, nf = n_faces;
+    float4 *rec = packs(n, k, nf, records, records_bytes) ? static_cast<float4 *>(records) : nullptr;
+    if (rec)
+        hipLaunchKernelGGL(face_record_kernel, dim3(blocks_for(nf, 256)), dim3(256), 0, st, verts, nv, faces, nf, rec);
     if (n_faces > 0 && k == 1)
-        hipLaunchKernelGGL(sdf_update_k_kernel<1>, dim3(grid), dim3(256), 0, st, verts, nv, faces, nf, face_k, g, n, sdf, face);
+        launch_update_k<1>(grid, st, verts, nv, faces, nf, rec, face_k, g, n, sdf, face);
     else if (n_faces > 0 && k == 2)
-        hipLaunchKernelGGL(sdf_update_k_kernel<2>, dim3(grid), dim3(256), 0, st, verts, nv, faces, nf, face_k, g, n, sdf, face);
+        launch_update_k<2>(grid, st, verts, nv, faces, nf, rec, face_k, g, n, sdf, face);
     else if (n_faces > 0 && k == 4)
-        hipLaunchKernelGGL(sdf_update_k_kernel<4>, dim3(grid), dim3(256), 0, st, verts, nv, faces, nf, face_k, g, n, sdf, face);
+        launch_update_k<4>(grid, st, verts, nv, faces, nf, rec, face_k, g, n, sdf, face);
     else if (n_faces > 0 && k == 8)
-        hipLaunchKernelGGL(sdf_update_k_kernel<8>, dim3(grid), dim3(256), 0, st, verts, nv, faces, nf, face_k, g, n, sdf, face);
+        launch_update_k<8>(grid, st, verts, nv, faces, nf, rec, face_k, g, n, sdf, face);
     else
         hipLaunchKernelGGL(sdf_update_kernel, dim3(grid), dim3(256), 0, st, verts, nv, faces, nf, face_k, k, g, n,
                            sdf, face);
     return launch_status();
+}
+
+extern "C" mg_status mg_sdf_update(const float *verts, int32_t n_verts, const int32_t *faces, int32_t n_faces,
+                                   const int32_t *face_k, int32_t k, float lo_x, float lo_y, float lo_z, float h,
+                                   int32_t nx, int32_t ny, int32_t nz, float *sdf, int32_t *face, void *stream) {
+    return mg_sdf_update_records(verts, n_verts, faces, n_faces, face_k, k, lo_x, lo_y, lo_z, h, nx, ny, nz, sdf,
+                                 face, nullptr, 0, stream);
 }
 
 extern "C" mg_status mg_sdf_sample(const float *sdf, float lo_x, float lo_y, float lo_z, float h, int32_t nx,

@@ -35,12 +35,13 @@ class IndexSDF:
         self.face_k = r["face"]                   # [k][n] int32: the indices kept across frames
         self.sdf = torch.empty(n, device=dev)
         self.face = torch.empty(n, dtype=torch.int32, device=dev)
+        self.records = torch.empty(12 * self.faces.shape[1], device=dev)   # the faces' corners during an update
 
     def update(self, verts):
         """Signed distances of every node for the vertex positions verts [3][V] (into self.sdf)."""
-        _call("mg_sdf_update", _ptr(_f32(verts, 3, "verts")), verts.shape[1], _ptr(_i32(self.faces)),
+        _call("mg_sdf_update_records", _ptr(_f32(verts, 3, "verts")), verts.shape[1], _ptr(_i32(self.faces)),
               self.faces.shape[1], _ptr(self.face_k), self.k, *self.lo, self.h, *self.dims, _ptr(self.sdf),
-              _ptr(self.face), _stream())
+              _ptr(self.face), _ptr(self.records), 4 * self.records.numel(), _stream())
         return self.sdf
 
     def sample(self, queries, out=None):

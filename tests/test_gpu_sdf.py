@@ -109,3 +109,33 @@ def test_sdf_ignores_invalid_face_ids(device):
     sdf = host(S.sdf)
     assert np.isinf(sdf[:5]).all() and np.isfinite(sdf[5:]).all()
     assert (host(S.face)[:5] == -1).all()
+
+
+@pytest.mark.parametrize("k", [1, 2, 4, 8])
+@pytest.mark.parametrize("short", [0, 1])
+def test_sdf_face_records_change_nothing(device, k, short):
+    """mg_sdf_update_records at the node count from which it writes the faces' corners
+    (2^19 stored ids, not a whole number of workgroups) and just below, with records that
+    are long enough or one float short: mg_sdf_update's values, and ids outside the mesh
+    ignored."""
+    import ctypes
+    from paper_2606_00444_amd import _lib
+    from paper_2606_00444_amd.api import _ptr, _stream
+    rng = np.random.default_rng(k)
+    nv, nf = 301, 599
+    V = dev(rng.normal(size=(3, nv)).astype(np.float32), device)
+    F = dev(rng.integers(0, nv, size=(3, nf)).astype(np.int32), device)
+    lib = _lib.load()
+    rec = torch.empty(12 * nf - short, device=device)
+    for nz in (2 ** 19 // k // 1024, 2 ** 19 // k // 1024 + 1):
+        dims = (31, 33, nz)                        # 1023 a layer: just below, and just above
+        n = dims[0] * dims[1] * dims[2]
+        face_k = torch.randint(-1, nf + 1, (k, n), dtype=torch.int32, device=device)
+        out = []
+        for records, size in ((None, 0), (_ptr(rec), 4 * rec.numel())):
+            d, w = torch.empty(n, device=device), torch.empty(n, dtype=torch.int32, device=device)
+            st = lib.mg_sdf_update_records(_ptr(V), nv, _ptr(F), nf, _ptr(face_k), k, -1.0, -1.0, -1.0, 0.05, *dims,
+                                           _ptr(d), _ptr(w), records, ctypes.c_size_t(size), _stream())
+            assert st == 0
+            out.append((d, w))
+        assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
