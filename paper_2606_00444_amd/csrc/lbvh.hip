@@ -11,6 +11,8 @@
 //            words, counters) on the way
 //   morton   30-bit codes defined in IEEE binary32 (no contraction), fused
 //            with the four 8-bit digit histograms of the radix sort
+//            (up to 4,096 primitives: one workgroup makes the codes and sorts them
+//            in LDS, instead of this and the next step's launches)
 //   sort     4 passes of a stable LSD radix sort of (code, id): one kernel per
 //            pass, tiles ranked with wave64 ballots (match masks over the 8
 //            digit bits), global digit offsets by decoupled look-back
@@ -223,27 +225,9 @@ __device__ __forceinline__ uint32_t quant10(float s, float lo, float scale) {
     return q < 1023u ? q : 1023u;
 }
 
-// s: planes sx, sy, sz of n values (the bounds kernel's, or the points').
-constexpr int kMortonThreads = 1024;
-__global__ __launch_bounds__(kMortonThreads) __attribute__((amdgpu_waves_per_eu(8))) void morton_kernel(const float *__restrict__ sx, const float *__restrict__ sy,
-                                                     const float *__restrict__ sz, int64_t n,
-                                                     const float *__restrict__ partial, int n_partial,
-                                                     mg_lbvh_header *hdr, uint32_t *__restrict__ keys,
-                                                     uint32_t *__restrict__ hist) {
+// The lower corner of the codes' cells and the cells per unit, from the bounds of s.
+__device__ __forceinline__ void quantisation(const float bounds[6], float lo[3], float scale[3]) {
 #pragma clang fp contract(off)
-    __shared__ uint32_t s_hist[4][256];
-    __shared__ float s_red[6][kMortonThreads / kWave];
-    for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) (&s_hist[0][0])[i] = 0;
-    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
-    for (int b = threadIdx.x; b < n_partial; b += kMortonThreads)
-#pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            mn[k] = fminf(mn[k], partial[6 * b + k]);
-            mx[k] = fmaxf(mx[k], partial[6 * b + 3 + k]);
-        }
-    float bounds[6];
-    block_bounds<kMortonThreads>(mn, mx, s_red, bounds);
-    float lo[3], scale[3];
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
         lo[k] = bounds[k];
@@ -253,6 +237,41 @@ __global__ __launch_bounds__(kMortonThreads) __attribute__((amdgpu_waves_per_eu(
         const float ext = hi - lo[k];
         scale[k] = hi > lo[k] ? static_cast<float>(1024.0 / static_cast<double>(ext)) : 0.0f;
     }
+}
+
+__device__ __forceinline__ uint32_t morton_code(f3 s, const float lo[3], const float scale[3]) {
+    return (spread10(quant10(s.x, lo[0], scale[0])) << 2) | (spread10(quant10(s.y, lo[1], scale[1])) << 1) |
+           spread10(quant10(s.z, lo[2], scale[2]));
+}
+
+// The bounds of s from the workgroups' partial ones, to every thread of 1024.
+constexpr int kMortonThreads = 1024;
+__device__ __forceinline__ void partial_bounds(const float *__restrict__ partial, int n_partial,
+                                               float (*s_red)[kMortonThreads / kWave], float bounds[6]) {
+    float mn[3] = {INFINITY, INFINITY, INFINITY}, mx[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (int b = threadIdx.x; b < n_partial; b += kMortonThreads)
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            mn[k] = fminf(mn[k], partial[6 * b + k]);
+            mx[k] = fmaxf(mx[k], partial[6 * b + 3 + k]);
+        }
+    block_bounds<kMortonThreads>(mn, mx, s_red, bounds);
+}
+
+// s: planes sx, sy, sz of n values (the bounds kernel's, or the points').
+__global__ __launch_bounds__(kMortonThreads) __attribute__((amdgpu_waves_per_eu(8))) void morton_kernel(const float *__restrict__ sx, const float *__restrict__ sy,
+                                                     const float *__restrict__ sz, int64_t n,
+                                                     const float *__restrict__ partial, int n_partial,
+                                                     mg_lbvh_header *hdr, uint32_t *__restrict__ keys,
+                                                     uint32_t *__restrict__ hist) {
+#pragma clang fp contract(off)
+    __shared__ uint32_t s_hist[4][256];
+    __shared__ float s_red[6][kMortonThreads / kWave];
+    for (int i = threadIdx.x; i < 4 * 256; i += blockDim.x) (&s_hist[0][0])[i] = 0;
+    float bounds[6];
+    partial_bounds(partial, n_partial, s_red, bounds);
+    float lo[3], scale[3];
+    quantisation(bounds, lo, scale);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         for (int k = 0; k < 3; ++k) { hdr->quant_lo[k] = lo[k]; hdr->quant_scale[k] = scale[k]; }
         for (int k = 0; k < 6; ++k) hdr->bounds_enc[k] = f2ord(bounds[k]);
@@ -261,9 +280,7 @@ __global__ __launch_bounds__(kMortonThreads) __attribute__((amdgpu_waves_per_eu(
     const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
     for (int64_t i = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x; i < n; i += stride) {
         const f3 s = f3{sx[i], sy[i], sz[i]};
-        const uint32_t code = (spread10(quant10(s.x, lo[0], scale[0])) << 2) |
-                              (spread10(quant10(s.y, lo[1], scale[1])) << 1) |
-                              spread10(quant10(s.z, lo[2], scale[2]));
+        const uint32_t code = morton_code(s, lo, scale);
         keys[i] = code;
         // neighbouring faces share their upper digits: the lanes with the first lane's
         // digit add once together instead of queueing on one counter
@@ -452,6 +469,112 @@ __global__ __launch_bounds__(sort_threads(kScale)) __attribute__((amdgpu_waves_p
             atomicOr(status, 2);   // inconsistent histogram: never expected
         }
     }
+}
+
+// Codes and the whole sort by one workgroup, keys and ids in LDS, for up to 1024
+// kItems primitives.  The tiled sort is five launches there, each a chain of a few
+// us over a handful of workgroups; here a pass is its ranking (the ballots of the
+// radix passes, kItems keys a thread) and four barriers.  It takes 9 us for up to 1024
+// primitives, 13 for 2048, 20 for 4096 and would take 32 for 8192, as the one compute
+// unit's ranking grows; builds of (tiled, small) 1,024 faces 54.7, 41.5 us; 2,048 56.5,
+// 46.2; 2,160 55.4, 50.5; 4,224 59.3, 66.4.
+constexpr int64_t kSmallSort = 4096;
+template <int kItems>
+__global__ __launch_bounds__(kMortonThreads) void small_sort_kernel(const float *__restrict__ sx,
+                                                                    const float *__restrict__ sy,
+                                                                    const float *__restrict__ sz, int64_t n,
+                                                                    const float *__restrict__ partial, int n_partial,
+                                                                    mg_lbvh_header *hdr, uint32_t *__restrict__ codes,
+                                                                    int32_t *__restrict__ prim) {
+    constexpr int kWaves = kMortonThreads / kWave;
+    static_assert(kItems * kMortonThreads <= 65536, "ids in 16 bits");
+    __shared__ uint32_t s_keys[kItems * kMortonThreads];
+    __shared__ uint16_t s_vals[kItems * kMortonThreads];
+    __shared__ uint32_t s_wave_cnt[kWaves][256];
+    __shared__ uint32_t s_tmp[kWaves];
+    __shared__ float s_red[6][kWaves];
+    const int tid = threadIdx.x, lane = tid % kWave, wave = tid / kWave, ni = static_cast<int>(n);
+    const int first = wave * kItems * kWave + lane;          // the thread's keys: first + 64 j
+    f3 s[kItems];                                            // in flight while the bounds are reduced
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+        const int i = first + j * kWave < ni ? first + j * kWave : ni - 1;
+        s[j] = f3{sx[i], sy[i], sz[i]};
+    }
+    float bounds[6], lo[3], scale[3];
+    partial_bounds(partial, n_partial, s_red, bounds);
+    quantisation(bounds, lo, scale);
+    if (tid == 0) {
+        for (int k = 0; k < 3; ++k) { hdr->quant_lo[k] = lo[k]; hdr->quant_scale[k] = scale[k]; }
+        for (int k = 0; k < 6; ++k) hdr->bounds_enc[k] = f2ord(bounds[k]);
+    }
+    uint32_t key[kItems], val[kItems], rank[kItems];
+#pragma unroll
+    for (int j = 0; j < kItems; ++j) {
+        key[j] = morton_code(s[j], lo, scale);
+        val[j] = first + j * kWave;
+    }
+    const uint64_t lt = lanemask_lt();
+    for (int shift = 0; shift < 32; shift += 8) {
+        for (int i = tid; i < kWaves * 256; i += kMortonThreads) (&s_wave_cnt[0][0])[i] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kItems; ++j) {
+            const bool valid = first + j * kWave < ni;       // a place holds a key in every pass, or in none
+            const uint32_t d = (key[j] >> shift) & 0xffu;
+            uint64_t m = __ballot(valid);
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                const bool bit = (d >> b) & 1u;
+                const uint64_t bb = __ballot(bit);
+                m &= bit ? bb : ~bb;
+            }
+            const uint64_t below = m & lt;
+            const uint32_t prev = valid ? s_wave_cnt[wave][d] : 0u;
+            rank[j] = prev + static_cast<uint32_t>(__popcll(below));
+            if (valid && below == 0) s_wave_cnt[wave][d] = prev + static_cast<uint32_t>(__popcll(m));
+        }
+        __syncthreads();
+        // the first 256 threads own a digit each: its keys before each wave's, from
+        // the digit's start
+        const int d = tid % 256;
+        uint32_t c[kWaves], total = 0;
+        if (tid < 256) {
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) c[w] = s_wave_cnt[w][d];
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) total += c[w];
+        }
+        uint32_t before = block_excl_scan<kMortonThreads>(total, s_tmp);
+        if (tid < 256) {
+#pragma unroll
+            for (int w = 0; w < kWaves; ++w) {
+                s_wave_cnt[w][d] = before;
+                before += c[w];
+            }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kItems; ++j)
+            if (first + j * kWave < ni) {
+                const uint32_t pos = s_wave_cnt[wave][(key[j] >> shift) & 0xffu] + rank[j];
+                s_keys[pos] = key[j];
+                s_vals[pos] = static_cast<uint16_t>(val[j]);
+            }
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < kItems; ++j)
+            if (first + j * kWave < ni) {
+                key[j] = s_keys[first + j * kWave];
+                val[j] = s_vals[first + j * kWave];
+            }
+    }
+#pragma unroll
+    for (int j = 0; j < kItems; ++j)
+        if (first + j * kWave < ni) {
+            codes[first + j * kWave] = key[j];
+            prim[first + j * kWave] = static_cast<int32_t>(val[j]);
+        }
 }
 
 // Internal node i (i < n - 1) and leaf i (i < n): Karras's range and split
@@ -940,39 +1063,51 @@ mg_status build_into(const float *verts, int32_t n_verts, const int32_t *faces, 
     const int64_t n_lookback = 4 * 256 * W.tiles;
     const int32_t *fz = prim_kind == MG_PRIM_TRIANGLES ? faces : nullptr;
     const int grid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(blocks_for(n, 256), kBoundsBlocks)));
+    const bool small = n <= kSmallSort;
     uint32_t *ka = n ? at<uint32_t>(ws, W.keys_a) : nullptr, *kb = n ? at<uint32_t>(ws, W.keys_b) : nullptr;
     int32_t *va = n ? at<int32_t>(ws, W.vals_a) : nullptr, *vb = n ? at<int32_t>(ws, W.vals_b) : nullptr;
     // the sums of faces wait in the sort's planes that no pass has written yet
     float *sx = reinterpret_cast<float *>(kb), *sy = reinterpret_cast<float *>(vb), *sz = reinterpret_cast<float *>(va);
     float *partial = n ? at<float>(ws, W.partial) : nullptr;
     hipLaunchKernelGGL(bounds_kernel, dim3(grid), dim3(256), 0, s, verts, (int64_t)n_verts, fz, n, sx, sy, sz, partial,
-                       hdr, hist, lookback, n_lookback, prim_kind, chunk_log2_for(n_prims));
+                       hdr, small ? nullptr : hist, small ? nullptr : lookback, n_lookback, prim_kind,
+                       chunk_log2_for(n_prims));
     if (launch_status() != MG_OK) return MG_ERR_HIP;
     if (n == 0) return MG_OK;
-    // at most one workgroup per CU: every one adds its digit counts to the same 1024
-    // words (1M faces: 26.8 us with 1024 workgroups of 256 threads, 13.5 us so)
-    const int mgrid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(blocks_for(n, kMortonThreads), 256)));
-    hipLaunchKernelGGL(morton_kernel, dim3(mgrid), dim3(kMortonThreads), 0, s, fz ? sx : verts, fz ? sy : verts + n_verts,
-                       fz ? sz : verts + 2 * static_cast<int64_t>(n_verts), n, partial, grid, hdr, ka, hist);
     uint32_t *codes = at<uint32_t>(bvh, L.off_codes);
     int32_t *prim = at<int32_t>(bvh, L.off_prim);
-    // pass p reads (src) and writes (dst): A->B, B->A, A->B, B->final
-    const uint32_t *ksrc[4] = {ka, kb, ka, kb};
-    const int32_t *vsrc[4] = {nullptr, vb, va, vb};
-    uint32_t *kdst[4] = {kb, ka, kb, codes};
-    int32_t *vdst[4] = {vb, va, vb, prim};
-    const int tile = sort_tile_for(n);
-    for (int p = 0; p < 4; ++p) {
-        auto pass = [&](auto kernel, int threads) {
-            hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(W.tiles)), dim3(threads), 0, s, ksrc[p],
-                               vsrc[p], kdst[p], vdst[p], n, 8 * p, hist + 256 * p,
-                               lookback + static_cast<int64_t>(p) * 256 * W.tiles, &hdr->tile_counter[p],
-                               &hdr->status);
+    const float *px = fz ? sx : verts, *py = fz ? sy : verts + n_verts,
+                *pz = fz ? sz : verts + 2 * static_cast<int64_t>(n_verts);
+    if (small) {
+        auto sort = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(1), dim3(kMortonThreads), 0, s, px, py, pz, n, partial, grid, hdr, codes, prim);
         };
-        if (tile <= 512) pass(radix_pass_kernel<2>, sort_threads(2));
-        else if (tile <= 1024) pass(radix_pass_kernel<4>, sort_threads(4));
-        else if (tile <= 2048) pass(radix_pass_kernel<8>, sort_threads(8));
-        else pass(radix_pass_kernel<16>, sort_threads(16));
+        if (n <= 1024) sort(small_sort_kernel<1>);
+        else if (n <= 2048) sort(small_sort_kernel<2>);
+        else sort(small_sort_kernel<4>);
+    } else {
+        // at most one workgroup per CU: every one adds its digit counts to the same 1024
+        // words (1M faces: 26.8 us with 1024 workgroups of 256 threads, 13.5 us so)
+        const int mgrid = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(blocks_for(n, kMortonThreads), 256)));
+        hipLaunchKernelGGL(morton_kernel, dim3(mgrid), dim3(kMortonThreads), 0, s, px, py, pz, n, partial, grid, hdr, ka, hist);
+        // pass p reads (src) and writes (dst): A->B, B->A, A->B, B->final
+        const uint32_t *ksrc[4] = {ka, kb, ka, kb};
+        const int32_t *vsrc[4] = {nullptr, vb, va, vb};
+        uint32_t *kdst[4] = {kb, ka, kb, codes};
+        int32_t *vdst[4] = {vb, va, vb, prim};
+        const int tile = sort_tile_for(n);
+        for (int p = 0; p < 4; ++p) {
+            auto pass = [&](auto kernel, int threads) {
+                hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>(W.tiles)), dim3(threads), 0, s, ksrc[p],
+                                   vsrc[p], kdst[p], vdst[p], n, 8 * p, hist + 256 * p,
+                                   lookback + static_cast<int64_t>(p) * 256 * W.tiles, &hdr->tile_counter[p],
+                                   &hdr->status);
+            };
+            if (tile <= 512) pass(radix_pass_kernel<2>, sort_threads(2));
+            else if (tile <= 1024) pass(radix_pass_kernel<4>, sort_threads(4));
+            else if (tile <= 2048) pass(radix_pass_kernel<8>, sort_threads(8));
+            else pass(radix_pass_kernel<16>, sort_threads(16));
+        }
     }
     hipLaunchKernelGGL(hierarchy_kernel, dim3(blocks_for(n, kHierThreads)), dim3(kHierThreads), 0, s, codes, prim,
                        at<int32_t>(bvh, L.off_inv_prim), n, fz,

@@ -43,3 +43,16 @@ def test_build_sort_tiles(device, n, dist):
     P = _points(dist, n, np.random.default_rng(n))
     print(f"build: {n} points, {dist}", flush=True)
     _check_build(mg.lbvh_build(dev(P, device), None), P, None)
+
+
+@pytest.mark.parametrize("faces", [False, True])
+@pytest.mark.parametrize("dist", ["uniform", "same", "outlier"])
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 2047, 2048, 2049, 4095, 4096, 4097])
+def test_build_one_workgroup_sort(device, n, dist, faces):
+    """One workgroup's sort of 1, 2 and 4 keys a thread, full and one off, and the first
+    size of the tiled sort."""
+    import paper_2606_00444_amd as mg
+    rng = np.random.default_rng(n)
+    P = _points(dist, n + 2 if faces else n, rng)
+    F = np.stack([np.arange(n), np.arange(n) + 1, np.arange(n) + 2]).astype(np.int32) if faces else None
+    _check_build(mg.lbvh_build(dev(P, device), None if F is None else dev(F, device)), P, F)
