@@ -79,9 +79,12 @@ inline mg_lbvh_layout make_layout(int64_t n, int kind) {
 
 // Largest subtree C = 2^chunk_log2 leaves: the smallest power of two >= 256
 // with n <= 512 C (a few hundred subtrees, so the top tree stays small),
-// capped at 2048 (the phase-1 LDS state is 52 B per leaf).
+// capped at 2048 (the phase-1 LDS state is 52 B per leaf).  A tree of 257 to 512
+// leaves is one subtree: a level more in it is less than a phase for the one
+// or two nodes above subtrees of 256 (refit of 500 faces: 15.2 us
+// in subtrees of 256, 13.8 of 512; of 1,120 16.2 and 17.7).
 inline int chunk_log2_for(int64_t n) {
-    int c = 8;
+    int c = n > 256 && n <= 512 ? 9 : 8;
     while ((int64_t(512) << c) < n && c < 11) ++c;
     return c;
 }
