@@ -390,6 +390,14 @@ mg_status mg_knn_surface_query(const void *bvh, size_t bvh_bytes, int32_t n_prim
                                float eps, float max_dist2, int32_t *face_k, float *dist2_k, float *point,
                                uint64_t *counters, void *stream);
 
+/* order [n_queries] (device) <- a permutation for mg_query_options.order that keeps
+ * each XCD of the card on one part of the tree and each batch's queries apart, by
+ * cells of the BVH's root box (any order among a cell's queries).  Worth its three
+ * launches where the tree is much larger than an L2 (4 MB).  ws: 4096 bytes. */
+mg_status mg_query_spread(const void *bvh, size_t bvh_bytes, int32_t n_prims, int32_t prim_kind,
+                          const float *queries, int32_t n_queries, int32_t *order, void *ws, size_t ws_bytes,
+                          void *stream);
+
 /* Nearest point of a MG_PRIM_POINTS BVH built over points [3][n_prims]:
  * index[q] (lowest index on exact ties, -1 if none within max_dist2) and
  * dist2[q] (+inf if none); dist2 may be NULL.  opts as for mg_closest_point_query. */

@@ -352,6 +352,26 @@ def _query_out(nq, device, point, bary, dist2, normal):
     }
 
 
+# From which tree bytes and query counts closest_point_query spreads its queries: cold
+# ones where the tree is twice an XCD's L2, hinted ones, which read far less of it,
+# where it is all eight.  us without and with, the three launches (12 us for 100,000
+# queries, 29 for 1M) included:
+#   cold    40,000 faces: 250,002 queries 440 / 424, 1M 1,484 / 1,525;  100,000 faces: 50,000 201 / 194,
+#           100,000 347 / 285;  1M faces: 100,000 852 / 626, 250,002 1,512 / 1,076
+#   hinted  200,000 faces: 100,000 152 / 162, 1M 1,007 / 995;  500,000 faces: 50,000 119 / 125,
+#           100,000 204 / 195, 1M 1,337 / 1,209;  1M faces: 1M 1,680 / 1,371
+_SPREAD_COLD = (8 << 20, 1 << 16)
+_SPREAD_HINTED = (32 << 20, 3 << 15)
+
+
+def _spread(bvh, queries, nq):
+    """Order [Q] of mg_query_spread (its 4096 bytes of scratch lie before it)."""
+    buf = torch.empty(1024 + nq, dtype=torch.int32, device=queries.device)
+    _call("mg_query_spread", _ptr(bvh.buf), bvh.nbytes, bvh.n, bvh.kind, _ptr(queries), nq, _ptr(buf[1024:]), _ptr(buf),
+          4096, _stream())
+    return buf[1024:]
+
+
 def closest_point_query(bvh, verts, queries, max_dist2=math.inf, *, point=True, bary=True, dist2=True,
                         normal=False, out=None, kernel=None, batch=0, seed=False, dynamic=False, order=None,
                         counters=None, hint=None, waves=0):
@@ -369,6 +389,11 @@ def closest_point_query(bvh, verts, queries, max_dist2=math.inf, *, point=True, 
     nq = _f32(queries, 3, "queries").shape[1]
     _same_verts(bvh, verts, "closest_point_query")
     o = out if out is not None else _query_out(nq, queries.device, point, bary, dist2, normal)
+    tree, count = _SPREAD_COLD if hint is None else _SPREAD_HINTED
+    if (nq >= count and 96 * bvh.n >= tree and order is None and counters is None and kernel in (None, "auto")
+            and not batch and not waves and not dynamic):
+        order = _spread(bvh, queries, nq)
+        seed = True                           # as the automatic choice without an order
     _call("mg_closest_point_query", _ptr(bvh.buf), bvh.nbytes, bvh.n, _ptr(verts), verts.shape[1],
           _ptr(queries), nq, float(max_dist2), _ptr(o["face"]), _ptr(o.get("point")), _ptr(o.get("bary")),
           _ptr(o.get("dist2")), _ptr(o.get("normal")),
