@@ -295,20 +295,21 @@ mg_status mg_frame_update(const float *frames, int32_t n_frames, int32_t n_verts
 /* Traversal choice for the query calls (NULL options = MG_QUERY_AUTO).
  *   MG_QUERY_LANE   one query per lane, depth-first, nearer child first
  *   MG_QUERY_BATCH  one wave per `batch` queries (1, 2, 4, 8, 16 or 32) sharing
- *                   an LDS work stack, up to 64 node expansions per step; suits
+ *                   an LDS work stack, 32 node expansions per step (64 on points); suits
  *                   few queries or queries with many near-equidistant faces
  *   MG_QUERY_AUTO   BATCH with the default batch and seed on
  * batch == 0 means the default: the largest of 16, 8, 4, 2, 1 with
  * n_queries >= 2048 batch (at least 512 workgroups of four waves), on triangles
- * without hints with n_queries >= 1024 batch.  NULL
- * options also turn the seed on; with options given, seed is as set.  seed != 0 (BATCH only): each query first descends
- * greedily (nearer child first) to one leaf to start from a tight bound before
- * the wide expansion.  order (device int32 [n_queries] permutation, or NULL):
+ * without hints with n_queries >= 1024 batch.  NULL options also turn the seed
+ * on; with options given, seed is as set.  seed != 0 (BATCH only): each query
+ * first walks down the two nearest nodes of a level to a few leaves, for a tight
+ * bound, and on triangles (batches up to 16) the wide expansion goes on from what
+ * the walk passed by.  order (device int32 [n_queries] permutation, or NULL):
  * queries are processed in the order order[0], order[1], ... - e.g. the prim
  * section of a MG_PRIM_POINTS BVH built over the queries, i.e. Morton order -
- * and every result is still written at the query's own index.  counters
- * (device uint64 [4], or NULL): += node expansions, leaf bound tests, exact
- * leaf tests, queries.  queue (device uint32 [1], or NULL; BATCH only): the
+ * or mg_query_spread's, and every result is still written at the query's own
+ * index.  counters (device uint64 [4], or NULL): += node expansions, leaves met,
+ * exact leaf tests, queries.  queue (device uint32 [1], or NULL; BATCH only): the
  * waves stay resident and take query batches one at a time from this counter,
  * which the call zeroes on its stream before the traversal (no initial value
  * needed); calls that may overlap in time must use different words.  Without a
@@ -382,8 +383,8 @@ mg_status mg_closest_point_bruteforce(const float *verts, int32_t n_verts, const
  * Outputs (device): face_k [k][n_queries] (-1 where fewer than k faces exist or
  * lie within max_dist2), dist2_k [k][n_queries] or NULL (+inf for -1 entries),
  * point [3][n_queries] or NULL (the query itself when no face qualifies).
- * counters: NULL or a device uint64 [4] accumulating node expansions, leaf
- * bound tests, exact leaf tests and queries (as mg_query_options.counters).
+ * counters: NULL or a device uint64 [4] accumulating node expansions, leaves
+ * met, exact leaf tests and queries (as mg_query_options.counters).
  * k = 1 gives the single closest point (unweighted). */
 mg_status mg_knn_surface_query(const void *bvh, size_t bvh_bytes, int32_t n_prims, const float *verts,
                                int32_t n_verts, const float *queries, int32_t n_queries, int32_t k,
@@ -589,7 +590,7 @@ typedef struct mg_batch_scene {
  * them (the autotuner picks the traversal per scene). */
 typedef struct mg_batch_options {
     int32_t batch;              /* least queries per wave of the batch traversal: 1, 2, 4, 8, 16 (0: 4) */
-    int32_t seed;               /* greedy seed descent: 0 off, otherwise on */
+    int32_t seed;               /* seed descent: 0 off, otherwise on */
     int32_t gauss_tile;         /* Gaussians per work item, multiple of 256 (0: 2048) */
     int32_t query_tile;         /* queries per work item, multiple of 4 * batch (0: 256) */
     int32_t reserved[4];        /* must be 0 */

@@ -58,7 +58,7 @@ struct QueryArgs {
     float maxd2;
     int32_t *face;
     float *point, *bary, *dist2, *normal;
-    int seed;                           // batch kernel: greedy descent first
+    int seed;                           // batch kernel: seed descent first
     const int32_t *order;               // processing order (permutation) or nullptr
     unsigned long long *counters;       // [4] statistics or nullptr
     const int32_t *inv_prim;            // [n] leaf of each original id (id -> position in leaf order)
@@ -261,8 +261,8 @@ __device__ __forceinline__ float single_leaf_dist2(const QueryArgs &a, f3 p) {
 
 // --------------------------------------------------------------- batch kernel
 // The waves of a workgroup each process batches of M queries with an LDS work
-// stack shared by the batch's queries; each round pops up to 64 entries (one
-// per lane).  A wave whose stack is deep puts its top 64 entries into the
+// stack shared by the batch's queries; each round pops up to 32 nodes (a lane per
+// child; 64 with a lane per node on points).  A wave whose stack is deep puts its top 64 entries into the
 // workgroup's one-chunk mailbox whenever it is empty, and a wave that has
 // finished a batch empties the mailbox before it starts another, so a batch
 // holding an expensive query (one nearly equidistant from many faces) is
@@ -625,7 +625,7 @@ __device__ __forceinline__ unsigned long long quad_xor64(unsigned long long v) {
 // query, the nearest of the leaves met on the way (the nearest by its box in
 // each lane), and its record slot in `code`.  With one node kept, both children
 // in a lane and every leaf on the way tested, 20,002 cold queries on 46,000 faces
-// took 58 us and expanded 52 nodes each, the walk included; now 41 us and 30.
+// took 58 us; in this form 41 us, and 39 us with kKeep (40 nodes each in all).
 //
 // kKeep: the children that the walk passes by go to the stack (K.nodes entries)
 // and the leaves it meets to the waiting leaves (K.leaves), with their bounds, so
