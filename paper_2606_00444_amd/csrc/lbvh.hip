@@ -891,11 +891,12 @@ __device__ void refit_blocks(const RefitArgs &a, int64_t block, int64_t nblocks,
                                         __HIP_MEMORY_SCOPE_AGENT) + mine == static_cast<uint32_t>(ns + a.list_top);
     __syncthreads();
     if (!s_last) return;
-    static_assert(kTopCap % kThreads == 0, "the top nodes kept in LDS are dealt evenly");
+    constexpr int kCap = refit_top_cap(kThreads);
+    static_assert(kCap % kThreads == 0, "the top nodes kept in LDS are dealt evenly");
     if (T < 1 || T >= a.n) {
         if (threadIdx.x == 0) atomicOr(a.status, 8);
-    } else if (T <= kTopCap) {
-        refit_top<kTri, kThreads, false, kTopCap / kThreads>(a, T, ns, smem);
+    } else if (T <= kCap) {
+        refit_top<kTri, kThreads, false, kCap / kThreads>(a, T, ns, smem);
     } else {
         refit_top<kTri, kThreads, true, 1>(a, T, ns, smem);
     }
@@ -955,18 +956,20 @@ mg_status launch_refit_t(const RefitArgs &a, int grid, hipStream_t s) {
 }
 
 // 512-thread workgroups: a thread per internal node of a subtree of up to 256
-// or 512 leaves, and 2 or 4 nodes per thread for 1024- and 2048-leaf subtrees.
+// or 512 leaves, and 2 nodes per thread for 1024-leaf subtrees.
 // Up to 1024 leaves three workgroups fit a CU beside each other (about 50 KB
 // of LDS each, six waves per SIMD), so a tree of 500,000 faces has nearly all
 // its subtrees resident at once.  256-leaf subtrees leave half the threads
 // idle in phase 1, but phase 2 then holds up to 512 top nodes at one node per
 // thread (a 40,000-face tree has 276: 24.5 us against 26.4 us with 256-thread
-// workgroups, whose phase 2 needs two nodes per thread there).
+// workgroups, whose phase 2 needs two nodes per thread there).  2048-leaf
+// subtrees take a CU's LDS for themselves, so 1024 threads: with 512, 4 nodes each,
+// a refit of 540,000 faces took 78 us, now 71, and of 1M 121, now 109.
 template <bool kTri>
 mg_status launch_refit_k(const RefitArgs &a, int grid, hipStream_t s) {
     if (a.chunk_log2 <= 9) return launch_refit_t<kTri, 512, 1, 6>(a, grid, s);
     if (a.chunk_log2 == 10) return launch_refit_t<kTri, 512, 2, 6>(a, grid, s);
-    return launch_refit_t<kTri, 512, 4, 2>(a, grid, s);
+    return launch_refit_t<kTri, 1024, 2, 4>(a, grid, s);
 }
 
 mg_status check_kind(int32_t kind) {
@@ -1216,7 +1219,7 @@ extern "C" mg_status mg_frame_update(const float *frames, int32_t n_frames, int3
     hipStream_t s = as_stream(stream);
     if (a.chunk_log2 <= 9) return launch_frame_t<512, 1, 6>(a, w, grid, s);
     if (a.chunk_log2 == 10) return launch_frame_t<512, 2, 6>(a, w, grid, s);
-    return launch_frame_t<512, 4, 2>(a, w, grid, s);
+    return launch_frame_t<1024, 2, 4>(a, w, grid, s);
 }
 
 extern "C" mg_status mg_lbvh_refit(const float *verts, int32_t n_verts, void *bvh, size_t bvh_bytes,

@@ -86,16 +86,19 @@ struct Sum {
 
 // LDS of the two phases: a 48-byte summary slot and a done byte per node, and
 // the step loop's finish word.
-constexpr int kTopCap = 1024;     // top nodes the plain refit keeps in LDS (more: global scratch)
+constexpr int kTopCap = 1024;     // top nodes the plain refit keeps in LDS (more: global scratch),
+                                  // twice as many with 2048-leaf subtrees, whose slots take that room
 
 constexpr size_t refit_sub_lds(int64_t C) { return static_cast<size_t>(C) * 49 + 16; }
 constexpr size_t refit_top_lds(int64_t T) { return static_cast<size_t>(T) * 49 + 16; }
 // LDS of the plain refit kernel: a subtree's slots, and room for kTopCap top
 // nodes in the workgroup that refits the top.
+constexpr int refit_top_cap(int kThreads) { return kThreads > 512 ? 2 * kTopCap : kTopCap; }
 constexpr size_t refit_lds_bytes(int chunk_log2) {
     return refit_sub_lds(int64_t(1) << chunk_log2) > refit_top_lds(kTopCap) ? refit_sub_lds(int64_t(1) << chunk_log2)
                                                                             : refit_top_lds(kTopCap);
 }
+static_assert(refit_lds_bytes(11) >= refit_top_lds(2 * kTopCap), "1024-thread workgroups keep 2 kTopCap top nodes");
 
 // ------------------------------------------------------------- normal slabs
 // An internal child slot of a triangle BVH stores, besides its box, a unit

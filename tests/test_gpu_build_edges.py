@@ -2,10 +2,13 @@
 and search-window edges of the hierarchy, every tile shape of the sort, and skewed codes
 (few long ranges, or all of them), bitwise against the oracle's tree."""
 
+import ctypes
+
 import numpy as np
 import pytest
 
 from gpu_helpers import need_gpu, dev
+from paper_2606_00444_amd._lib import LbvhHeader
 from test_gpu_lbvh import _check_build
 
 pytestmark = pytest.mark.gpu
@@ -56,3 +59,19 @@ def test_build_one_workgroup_sort(device, n, dist, faces):
     P = _points(dist, n + 2 if faces else n, rng)
     F = np.stack([np.arange(n), np.arange(n) + 1, np.arange(n) + 2]).astype(np.int32) if faces else None
     _check_build(mg.lbvh_build(dev(P, device), None if F is None else dev(F, device)), P, F)
+
+
+@pytest.mark.parametrize("n,faces", [(524289, True), (1400000, False)])
+def test_refit_of_2048_leaf_subtrees(device, n, faces):
+    """1024-thread workgroups, with up to 1024 top nodes (one a thread) and more (two)."""
+    import paper_2606_00444_amd as mg
+    rng = np.random.default_rng(n)
+    P = (rng.normal(size=(3, n + 2 if faces else n)) ** 3).astype(np.float32)
+    F = np.stack([np.arange(n), np.arange(n) + 1, np.arange(n) + 2]).astype(np.int32) if faces else None
+    print(f"refit: {n}, faces {faces}", flush=True)
+    Pd = dev(P, device)
+    bvh = mg.lbvh_build(Pd, None if F is None else dev(F, device))
+    mg.lbvh_refit(bvh, Pd)
+    _check_build(bvh, P, F)
+    hdr = LbvhHeader.from_buffer_copy(bvh.buf[:ctypes.sizeof(LbvhHeader)].cpu().numpy().tobytes())
+    assert (hdr.n_top > 1024) == (n > 1000000)
