@@ -297,7 +297,9 @@ mg_status mg_frame_update(const float *frames, int32_t n_frames, int32_t n_verts
  *   MG_QUERY_BATCH  one wave per `batch` queries (1, 2, 4, 8, 16 or 32) sharing
  *                   an LDS work stack, 32 node expansions per step (64 on points); suits
  *                   few queries or queries with many near-equidistant faces
- *   MG_QUERY_AUTO   BATCH with the default batch and seed on
+ *   MG_QUERY_AUTO   BATCH with the default batch and seed on; a scan of every
+ *                   leaf for up to 4,096 queries on up to 1,280 triangles or
+ *                   3,072 points (if no batch, order, counters, queue or waves is given)
  * batch == 0 means the default: the largest of 16, 8, 4, 2, 1 with
  * n_queries >= 2048 batch (at least 512 workgroups of four waves), on triangles
  * without hints with n_queries >= 1024 batch.  NULL options also turn the seed

@@ -12,7 +12,8 @@
 // each leaf child) in every traversal.  Leaf children hold their triangle, so a
 // leaf is tested with the data of the record that referenced it.
 //
-// Two traversals (chosen per call, see mg_query_options):
+// Small sets on small trees are scanned (scan_kernel).  Otherwise, two traversals
+// (chosen per call, see mg_query_options):
 //  * lane:  one query per lane, depth-first, nearer child first; stack in LDS
 //           for the first 32 entries and in a private array beyond (Karras trees
 //           over 30-bit codes with index tie-break are at most 62 levels deep).
@@ -186,6 +187,103 @@ inline const T *cat(const void *base, int64_t off) {
     return reinterpret_cast<const T *>(static_cast<const char *>(base) + off);
 }
 
+// ---------------------------------------------------------------- scan kernel
+// Few queries on a small tree: a wave per query tests every leaf, the lanes 64 of
+// them at a time and four such groups' records in flight.  A traversal is bound
+// there by its chain, a round of about 1 us for every level of the tree and the
+// hint's four dependent reads before it; the scan has no chain beyond a read of
+// the leaves' places and one of their records.  Triangles whose box lies beyond
+// the best of the groups before are not tested.  Same leaf arithmetic, and the
+// least (d^2, id) of all leaves, so the same result; a hint cannot change it and is
+// not read.  257 queries on 500 faces: 17.0 us hinted and 19.7 cold, 8.0 so; 2,000
+// nearest of 2,080 points 18.0, 11.0.
+template <bool kTri>
+__global__ __launch_bounds__(64 * kBatchWaves) void scan_kernel(QueryArgs a) {
+    constexpr int kGroups = 4;
+    check_vertex_count(a);
+    const int lane = threadIdx.x % 64;
+    const int64_t q = static_cast<int64_t>(blockIdx.x) * kBatchWaves + threadIdx.x / 64;
+    if (q >= a.nq) return;
+    const f3 p = load3(a.queries, a.nq, q);
+    const float qm = qnorm1(p);
+    const int32_t n = static_cast<int32_t>(a.n), slots = 2 * (n - 1);
+    unsigned long long best = pack_best(a.maxd2, INT_MAX);
+    const unsigned long long none = best;
+    float pb = prune_bound(a.maxd2, qm);
+    int32_t at = -1;
+    for (int32_t base = 0; base < n; base += 64 * kGroups) {
+        int32_t code[kGroups];
+        bool ok[kGroups];
+#pragma unroll
+        for (int u = 0; u < kGroups; ++u) {
+            const int32_t leaf = base + 64 * u + lane;
+            code[u] = a.leaf_parent[leaf < n ? leaf : 0];
+            ok[u] = leaf < n && code[u] >= 0 && code[u] < slots;
+            if (leaf < n && !ok[u]) atomicOr(a.status, 16);
+        }
+        float4 f0[kGroups], f1[kGroups], f2[kGroups];
+#pragma unroll
+        for (int u = 0; u < kGroups; ++u) {
+            const float4 *rec = a.nodes + 3 * (ok[u] ? code[u] : 0);
+            f1[u] = rec[1];
+            if (kTri) { f0[u] = rec[0]; f2[u] = rec[2]; }
+        }
+#pragma unroll
+        for (int u = 0; u < kGroups; ++u) {
+            bool act = ok[u];
+            if (kTri) act = act && leaf_box_dist2<kTri>(p, f0[u], f1[u], f2[u]) <= pb;
+            if (act) {
+                const float d2 = kTri ? leaf_dist2<kTri>(p, f0[u], f1[u], f2[u]) : leaf_dist2<kTri>(p, f1[u], f1[u], f1[u]);
+                const unsigned long long cand = pack_best(d2, __float_as_int(f1[u].w));
+                if (cand < best) {
+                    best = cand;
+                    at = code[u];
+                }
+            }
+        }
+        if (kTri && base + 64 * kGroups < n) {
+            float d2 = __uint_as_float(static_cast<uint32_t>(best >> 32));
+#pragma unroll
+            for (int o = 32; o >= 1; o >>= 1) d2 = fminf(d2, __shfl_xor(d2, o));
+            pb = prune_bound(d2, qm);
+        }
+    }
+    unsigned long long m = best;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const unsigned long long x = __shfl_xor(m, o);
+        if (x < m) m = x;
+    }
+    const uint64_t winners = __ballot(m < none && best == m);
+    if (winners == 0) {
+        if (lane == 0) write_result<kTri>(a, q, p, -1, -1, 0.0f);
+        return;
+    }
+    if ((winners & lanemask_lt()) != 0 || best != m) return;
+    const int32_t id = static_cast<int32_t>(m & 0xffffffffull);
+    if (id < 0 || id >= n) {
+        atomicOr(a.status, 16);
+        write_result<kTri>(a, q, p, -1, -1, 0.0f);
+    } else if (kTri) {
+        const float4 *rec = a.nodes + 3 * at;
+        write_face(a, q, p, id, xyz(rec[0]), xyz(rec[1]), xyz(rec[2]));
+    } else {
+        store_face(a, q, id);
+        if (a.dist2) a.dist2[q] = __uint_as_float(static_cast<uint32_t>(m >> 32));
+    }
+}
+
+// Whether the automatic choice is the scan: it reads every leaf for every query, so
+// it pays up to about the size at which that fills the card (us by the batch kernel
+// hinted, and by the scan):
+//   triangles  1,088 faces: 1,000 queries 18.1 / 13.4, 4,000 23.3 / 18.9, 8,000 23.9 / 31.3;  2,080: 2,000 20.0 / 22.9
+//   points     2,080: 4,000 queries 21.5 / 13.3, 8,000 22.0 / 26.3;  4,100: 4,000 22.6 / 24.1
+template <bool kTri>
+inline bool scans(const mg_query_options *o, int64_t n, int64_t nq) {
+    if (o && (o->kernel != MG_QUERY_AUTO || o->batch || o->order || o->counters || o->queue || o->waves)) return false;
+    return n >= 2 && n <= (kTri ? 1280 : 3072) && nq <= 4096;
+}
+
 // Default traversal when the caller gives no options: the batch kernel with a
 // seed descent and the largest batch (16, 8, 4, 2 or 1 queries per wave) that
 // leaves enough workgroups of four waves: 512 where the queries start from hints
@@ -265,6 +363,10 @@ mg_status launch_traverse(QueryArgs a, const mg_query_options *opts, hipStream_t
     a.counters = opts ? reinterpret_cast<unsigned long long *>(opts->counters) : nullptr;
     a.queue = opts ? opts->queue : nullptr;
     a.hint = opts ? opts->hint : nullptr;
+    if (scans<kTri>(opts, a.n, a.nq)) {
+        hipLaunchKernelGGL(scan_kernel<kTri>, dim3(blocks_for(a.nq, kBatchWaves)), dim3(64 * kBatchWaves), 0, s, a);
+        return launch_status();
+    }
     if (kernel == MG_QUERY_LANE) {
         hipLaunchKernelGGL(traverse_lane_kernel<kTri>, dim3(blocks_for(a.nq, kLaneBlock)), dim3(kLaneBlock), 0, s, a);
         return launch_status();

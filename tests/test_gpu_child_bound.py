@@ -110,3 +110,52 @@ def test_cold_queries_on_deep_trees(device, nf, kind):
     if kind == "doubling":
         for k in (2, 4):
             check_knn_result(mg.knn_surface_query(bvh, Vd, Qd, k=k, eps=1e-6), V, F, Q, k, 1e-6, float("inf"))
+
+
+@pytest.mark.parametrize("n", [2, 63, 65, 255, 256, 257, 1279, 1280])
+@pytest.mark.parametrize("max_dist2", [float("inf"), 0.02])
+def test_scan_matches_all_faces(device, n, max_dist2):
+    """Every leaf scanned, in groups of 64 and fours of them: one, a full set and a remainder;
+    ties of coincident faces, points that are no numbers or overflow, hints of no use."""
+    import paper_2606_00444_amd as mg
+    rng = np.random.default_rng(n)
+    V = (rng.uniform(-1, 1, size=(n, 1, 3)) + 0.2 * rng.normal(size=(n, 3, 3))).astype(np.float32)
+    V[n // 2:n // 2 + 9] = V[0]                               # faces in one place
+    V = np.ascontiguousarray(V.reshape(-1, 3).T)
+    F = np.arange(3 * n, dtype=np.int32).reshape(n, 3).T.copy()
+    Q = rng.uniform(-1.5, 1.5, size=(3, 301)).astype(np.float32)
+    Q[:, 0], Q[:, 1], Q[:, 2], Q[0, 3] = np.nan, 1e25, V[:, 0], np.inf
+    Vd, Fd, Qd = dev(V, device), dev(F, device), dev(Q, device)
+    bvh = mg.lbvh_build(Vd, Fd)
+    walk = mg.closest_point_query(bvh, Vd, Qd, max_dist2, normal=True, kernel="batch", batch=4)
+    ref = mg.closest_point_bruteforce(Vd, Fd, Qd, max_dist2, normal=True)
+    hint = torch.randint(-1, n + 1, (301,), dtype=torch.int32, device=device)
+    for h in (None, hint):
+        r = mg.closest_point_query(bvh, Vd, Qd, max_dist2, normal=True, hint=h)
+        for key in r:
+            assert torch.equal(r[key].nan_to_num(7.0), walk[key].nan_to_num(7.0)), key
+            assert torch.equal(r[key][..., 4:], ref[key][..., 4:]), key
+    P = np.ascontiguousarray(V[:, ::3])
+    pts = mg.lbvh_build(dev(P, device))
+    i, d = mg.nearest_point_query(pts, dev(P, device), Qd, max_dist2)
+    j, e = mg.nearest_point_query(pts, dev(P, device), Qd, max_dist2, kernel="batch", batch=4)
+    assert torch.equal(i, j) and torch.equal(d, e)
+
+
+@pytest.mark.parametrize("faces,n,nq", [(True, 1280, 4096), (True, 1281, 4096), (True, 1280, 4097),
+                                        (False, 3072, 4096), (False, 3073, 4096), (False, 3072, 4097)])
+def test_scan_rule_edges(device, faces, n, nq):
+    import paper_2606_00444_amd as mg
+    rng = np.random.default_rng(n + nq)
+    P = dev(rng.uniform(-1, 1, size=(3, n + 2 if faces else n)).astype(np.float32), device)
+    Q = dev(rng.uniform(-1.2, 1.2, size=(3, nq)).astype(np.float32), device)
+    if faces:
+        F = dev(np.stack([np.arange(n) + s for s in range(3)]).astype(np.int32), device)
+        bvh = mg.lbvh_build(P, F)
+        r = mg.closest_point_query(bvh, P, Q, normal=True)
+        w = mg.closest_point_query(bvh, P, Q, normal=True, kernel="batch", batch=4)
+        assert all(torch.equal(r[key], w[key]) for key in r)
+    else:
+        bvh = mg.lbvh_build(P)
+        r, w = mg.nearest_point_query(bvh, P, Q), mg.nearest_point_query(bvh, P, Q, kernel="batch", batch=4)
+        assert torch.equal(r[0], w[0]) and torch.equal(r[1], w[1])
