@@ -568,8 +568,7 @@ typedef struct mg_batch_scene {
     const float *log_scale;     /* [3][n_gauss] */
     const float *queries;       /* [3][n_queries] */
     int32_t n_queries;
-    int32_t batch;              /* this scene's queries per wave at least (1, 2, 4, 8, 16; raised while
-                                   a tile still gives each of four waves a batch); 0: the plan's */
+    int32_t batch;              /* this scene's queries per wave (1, 2, 4, 8, 16); 0: the plan's */
     int32_t seed;               /* this scene's seed descent: 0 off, 1 on, -1: the plan's */
     int32_t query_tile;         /* this scene's queries per work item, a multiple of 4 * its
                                    batch; 0: the plan's */
@@ -591,12 +590,18 @@ typedef struct mg_batch_scene {
 /* Plan-wide defaults; a scene's own batch / seed / query_tile fields override
  * them (the autotuner picks the traversal per scene). */
 typedef struct mg_batch_options {
-    int32_t batch;              /* least queries per wave of the batch traversal: 1, 2, 4, 8, 16 (0: 4) */
+    int32_t batch;              /* queries per wave of the batch traversal: 1, 2, 4, 8, 16; 0: for each
+                                   scene the most of 4, 8, 16 that gives each of four waves a batch of
+                                   the queries that a tile holds */
     int32_t seed;               /* seed descent: 0 off, otherwise on */
     int32_t gauss_tile;         /* Gaussians per work item, multiple of 256 (0: 2048) */
-    int32_t query_tile;         /* queries per work item, multiple of 4 * batch (0: 256) */
+    int32_t query_tile;         /* queries per work item, multiple of 4 * batch, of 16 for batch 0 (0: 256) */
     int32_t reserved[4];        /* must be 0 */
 } mg_batch_options;
+
+/* Host-only: *batch <- the queries per wave that mg_batch_plan_init takes for this
+ * scene (only its n_queries, batch and query_tile are read) under opts (or NULL). */
+mg_status mg_batch_queries_per_wave(const mg_batch_scene *scene, const mg_batch_options *opts, int32_t *batch);
 
 /* Bytes of the device plan for these scenes (scenes: host array).  Reads each
  * scene BVH's top-node count from its device header (a synchronous copy):

@@ -100,6 +100,7 @@ PROTOTYPES = {
     "mg_point_mesh_backward_ordered": (I32, [P, I32, P, I32, P, I32, P, P, P, F32, P, P, P, P]),
     "mg_chamfer_backward_ordered": (I32, [P, I32, P, I32, P, P, F32, F32, P, P, P, P]),
     "mg_adam_step": (I32, [P, P, P, P, I64, I32, F32, F32, F32, F32, P]),
+    "mg_batch_queries_per_wave": (I32, [P, P, P]),
     "mg_batch_plan_size": (I32, [P, I32, P]),
     "mg_batch_plan_init": (I32, [P, I32, P, P, SZ, P]),
     "mg_batch_run": (I32, [P, SZ, P]),

@@ -20,12 +20,13 @@ class BatchPlan:
       q_local [4][G], log_scale [3][G], queries [3][Q] float32,
       and optionally bvh (a triangle LBVH over the faces; built from frame 0 if absent)
       and this scene's traversal: batch (queries per wave), seed, query_tile.
-    Options: the plan-wide defaults of batch, seed and query_tile, and
-    gauss_tile.  autotune.tune_batch chooses all of them.  After run(), out[i]
+    Options: the plan-wide defaults of batch (0: what fills the waves of a
+    scene's tiles, up to 16), seed and query_tile, and gauss_tile.
+    autotune.tune_batch chooses all of them.  After run(), out[i]
     holds scene i's per-frame outputs.
     """
 
-    def __init__(self, scenes, *, batch=4, seed=True, gauss_tile=2048, query_tile=256, normals=True):
+    def __init__(self, scenes, *, batch=0, seed=True, gauss_tile=2048, query_tile=256, normals=True):
         self.scenes = scenes
         self.out = []
         arr = (_lib.BatchScene * len(scenes))()
@@ -65,7 +66,7 @@ class BatchPlan:
         _call("mg_batch_status_word", _ptr(self.plan), ctypes.byref(st))
         self._status_off = st.value - self.plan.data_ptr()
 
-    def configure(self, *, batch=4, seed=True, gauss_tile=2048, query_tile=256, per_scene=None):
+    def configure(self, *, batch=0, seed=True, gauss_tile=2048, query_tile=256, per_scene=None):
         """(Re)write the device plan with new plan-wide defaults and, optionally,
         per-scene traversal overrides per_scene[i] = {batch, seed, query_tile}
         (synchronises the stream; outputs and plan buffer are reused)."""

@@ -395,6 +395,29 @@ inline mg_status scratch_words(const mg_batch_scene *scenes, int32_t n_scenes, i
     return MG_OK;
 }
 
+// Queries per wave where neither the scene nor the plan names a number.  A tile is one
+// workgroup's whatever the batch, so smaller batches only run it in more, emptier
+// rounds: 24 scene-frames of 60,000 queries in tiles of 256 took 1,545 us at 4 queries
+// per wave, 1,113 at 8 and 925 at 16.  The most, from 4 up, that gives each of the four
+// waves a batch of the queries that a tile holds is taken.
+inline int default_batch(int64_t query_tile, int64_t n_queries) {
+    const int64_t held = std::min(query_tile, n_queries);
+    int batch = 4;
+    while (batch < 16 && 8 * batch <= held) batch *= 2;
+    return batch;
+}
+
+extern "C" mg_status mg_batch_queries_per_wave(const mg_batch_scene *scene, const mg_batch_options *opts, int32_t *batch) {
+    if (!scene || !batch || bad_count(scene->n_queries)) return MG_ERR_INVALID_ARGUMENT;
+    const int named = scene->batch != 0 ? scene->batch : opts ? opts->batch : 0;
+    const int tile = scene->query_tile != 0 ? scene->query_tile : opts && opts->query_tile != 0 ? opts->query_tile : 256;
+    const int per = named == 0 ? 4 : named;
+    if (!(per == 1 || per == 2 || per == 4 || per == 8 || per == 16) || tile <= 0 || tile % (4 * per) != 0)
+        return MG_ERR_INVALID_ARGUMENT;
+    *batch = named == 0 ? default_batch(tile, scene->n_queries) : named;
+    return MG_OK;
+}
+
 extern "C" mg_status mg_batch_plan_size(const mg_batch_scene *scenes, int32_t n_scenes, size_t *plan_bytes) {
     if (!scenes || !plan_bytes || n_scenes < 1 || n_scenes > kMaxScenes) return MG_ERR_INVALID_ARGUMENT;
     for (int i = 0; i < n_scenes; ++i)
@@ -448,17 +471,10 @@ extern "C" mg_status mg_batch_plan_init(const mg_batch_scene *scenes, int32_t n_
         if (s.bvh_bytes < static_cast<size_t>(L.total_bytes)) return MG_ERR_WORKSPACE_TOO_SMALL;
         PlanScene &P = h.scenes[i];
         P.s = s;
-        P.batch = s.batch == 0 ? batch : s.batch;
         P.seed = s.seed < 0 ? (o.seed != 0) : (s.seed != 0);
         P.query_tile = s.query_tile == 0 ? qtile : s.query_tile;
-        if (!(P.batch == 1 || P.batch == 2 || P.batch == 4 || P.batch == 8 || P.batch == 16) || s.seed < -1 ||
-            s.seed > 1 || P.query_tile <= 0 || P.query_tile % (4 * P.batch) != 0)
+        if (mg_batch_queries_per_wave(&s, &o, &P.batch) != MG_OK || s.seed < -1 || s.seed > 1)
             return MG_ERR_INVALID_ARGUMENT;
-        // A tile is one workgroup's whatever the batch, so smaller batches only run it in
-        // more, emptier rounds: 24 scene-frames of 60,000 queries in tiles of 256 took
-        // 1,545 us at 4 queries per wave, 1,113 at 8 and 925 at 16.  The most that gives
-        // each of the four waves a batch is taken.
-        while (P.batch < 16 && 8 * P.batch <= P.query_tile) P.batch *= 2;
         const char *b = static_cast<const char *>(s.bvh);
         P.leaf_faces = reinterpret_cast<const int32_t *>(b + L.off_leaf_faces);
         P.prim = reinterpret_cast<const int32_t *>(b + L.off_prim);
