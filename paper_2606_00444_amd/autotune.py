@@ -1,8 +1,9 @@
 """Autotuner for the closest-point / nearest-point traversal.
 
-For a given BVH and query set it times every candidate traversal (one query per
-lane, or one wave per batch of 1-16 queries with or without the greedy seed
-descent, with batches dealt statically or taken from a work counter; in the
+For a given BVH and query set it times the call left to the library (which may
+scan the leaves or order the queries itself) and every traversal that a caller can
+name (one query per lane, or one wave per batch of 1-16 queries with or without the
+seed descent, with batches dealt statically or taken from a work counter; in the
 given query order or a supplied one such as Morton order), each
 as a HIP graph of back-to-back launches bracketed by HIP events
 on the launch stream, and keeps the fastest.  Choices are cached per device,
@@ -18,8 +19,12 @@ import torch
 
 from . import api
 
-CANDIDATES = ([("lane", 0, False, False)] + [("batch", b, s, False) for b in (1, 2, 4, 8, 16) for s in (False, True)]
+CANDIDATES = ([("auto", 0, True, False), ("lane", 0, False, False)] + [("batch", b, s, False) for b in (1, 2, 4, 8, 16) for s in (False, True)]
               + [("batch", b, True, True) for b in (2, 4, 8, 16)])
+
+
+# Of the cache's keys: raised when the candidates or what they run change.
+FORMAT = "2"
 
 
 def _cache_path():
@@ -68,7 +73,7 @@ def _graph_time(fn, reps):
 def _key(kind, bvh, queries, ordered, extra=""):
     dev = torch.cuda.get_device_properties(queries.device)
     arch = getattr(dev, "gcnArchName", dev.name)
-    return f"{arch}|{kind}|n={bvh.n}|q={queries.shape[1]}|ordered={int(ordered)}{extra}"
+    return f"{FORMAT}|{arch}|{kind}|n={bvh.n}|q={queries.shape[1]}|ordered={int(ordered)}{extra}"
 
 
 def _tune(key, run, orders, candidates, reps, use_cache):
@@ -82,8 +87,9 @@ def _tune(key, run, orders, candidates, reps, use_cache):
                 lambda: run(kernel=kernel, batch=batch, seed=seed, dynamic=dyn, order=order), reps)
     best = min(timings, key=timings.get)
     k, b, s, d, o = best.split("/")
-    res = {"kernel": k, "batch": int(b), "seed": bool(int(s)), "dynamic": bool(int(d)), "order": o,
-           "ms": timings[best], "timings": timings}
+    auto = k == "auto"
+    res = {"kernel": "batch" if auto else k, "auto": auto, "batch": int(b), "seed": bool(int(s)), "dynamic": bool(int(d)),
+           "order": o, "ms": timings[best], "timings": timings}
     if use_cache:
         cache = _load_cache()
         cache[key] = res
@@ -97,7 +103,8 @@ def tune_closest(bvh, verts, queries, *, order=None, normal=False, reps=5, use_c
 
     order: an optional processing order to consider besides the given one (e.g.
     query_order(queries)); the result's "order" is "given" or "order".  Returns
-    {"kernel", "batch", "seed", "order", "ms", "timings"}; options(res, order)
+    {"kernel", "auto", "batch", "seed", "order", "ms", "timings"}, with "auto" where
+    the call is best left to the library; options(res, order)
     gives the keyword arguments for closest_point_query.  waves: the batch
     kernel's register allocation to time (0: by launch size, as the plain call).
     """
@@ -118,7 +125,7 @@ def tune_nearest(bvh, points, queries, *, order=None, reps=5, use_cache=True, ca
 
 def options(res, order=None):
     """Keyword arguments of a tuning result for the query calls (order: the candidate order tensor)."""
-    kw = {"kernel": res["kernel"], "batch": res["batch"], "seed": res["seed"], "dynamic": res.get("dynamic", False)}
+    kw = {"kernel": "auto" if res.get("auto") else res["kernel"], "batch": res["batch"], "seed": res["seed"], "dynamic": res.get("dynamic", False)}
     if res.get("order") == "order":
         kw["order"] = order
     return kw
@@ -148,7 +155,7 @@ def tune_batch(plan, reps=3, use_cache=True):
                      for s in plan.scenes)
     picks = ",".join(f"{p['batch']}{int(p['seed'])}" for p in per_scene)
     dev = torch.cuda.get_device_properties(plan.plan.device)
-    key = f"{getattr(dev, 'gcnArchName', dev.name)}|batchplan|{sizes}|{picks}"
+    key = f"{FORMAT}|{getattr(dev, 'gcnArchName', dev.name)}|batchplan|{sizes}|{picks}"
     cache = _load_cache() if use_cache else {}
     if key in cache:
         res = cache[key]

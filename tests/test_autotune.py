@@ -1,0 +1,59 @@
+"""What the autotuner times, on the host: the library's own choice is among the
+candidates, so that a tuned call is not slower than one that names nothing."""
+
+import pytest
+import torch
+
+from paper_2606_00444_amd import api, autotune
+
+
+class _Bvh:
+    n = 500
+
+
+@pytest.fixture
+def timed(monkeypatch):
+    """Calls of the query functions instead of launches; their times by `cost`."""
+    calls = []
+    monkeypatch.setattr(autotune, "_key", lambda *a, **k: "key")
+    monkeypatch.setattr(api, "closest_point_query", lambda *a, **kw: calls.append(kw))
+    monkeypatch.setattr(api, "nearest_point_query", lambda *a, **kw: calls.append(kw))
+    return calls
+
+
+def _own_choice(kw):
+    """Whether these arguments leave the traversal to the library: what rules out its scan
+    and its order is a kernel, batch, work counter, wave count or order asked for."""
+    return (kw.get("kernel") in (None, "auto") and not any(kw.get(k) for k in ("batch", "dynamic", "waves"))
+            and kw.get("order") is None and kw.get("counters") is None)
+
+
+@pytest.mark.parametrize("tune", [autotune.tune_closest, autotune.tune_nearest])
+@pytest.mark.parametrize("order", [None, torch.arange(4, dtype=torch.int32)])
+def test_the_default_call_is_timed_and_can_win(tune, order, timed, monkeypatch):
+    def cost(run, reps):
+        run()
+        return 1.0 if _own_choice(timed[-1]) else 2.0
+    monkeypatch.setattr(autotune, "_graph_time", cost)
+    res = tune(_Bvh(), None, torch.zeros(3, 4), order=order, use_cache=False)
+    assert sum(_own_choice(kw) for kw in timed) >= 1
+    assert res["ms"] == 1.0 and res["order"] == "given"
+    assert _own_choice(autotune.options(res, order))
+
+
+def test_a_named_traversal_that_wins_is_returned(timed, monkeypatch):
+    def cost(run, reps):
+        run()
+        return 1.0 if timed[-1]["kernel"] == "batch" and timed[-1]["batch"] == 8 and timed[-1]["dynamic"] else 2.0
+    monkeypatch.setattr(autotune, "_graph_time", cost)
+    res = autotune.tune_closest(_Bvh(), None, torch.zeros(3, 4), use_cache=False)
+    assert autotune.options(res) == {"kernel": "batch", "batch": 8, "seed": True, "dynamic": True}
+
+
+def test_choices_of_earlier_candidates_are_not_reused(tmp_path, monkeypatch):
+    """A stored choice is found by a key that names the candidates' format."""
+    class Props:
+        name = gcnArchName = "gfx950"
+    monkeypatch.setattr(torch.cuda, "get_device_properties", lambda d: Props)
+    key = autotune._key("closest", _Bvh(), torch.zeros(3, 4), False)
+    assert key.startswith(autotune.FORMAT + "|") and key != "gfx950|closest|n=500|q=4|ordered=0"
