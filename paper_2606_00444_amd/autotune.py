@@ -132,17 +132,21 @@ def options(res, order=None):
 
 
 BATCH_CANDIDATES = [("batch", b, s, False) for b in (1, 2, 4, 8, 16) for s in (False, True)]
-BATCH_TILES = [(g, q) for g in (1024, 2048, 4096) for q in (128, 256, 512, 1024)]
+# Gaussian tile, query tile, and whether the scenes take the queries per wave and seed
+# that were fastest alone or the launch's own (a tile's waves filled, seed on).
+BATCH_TILES = [(g, q, own) for g in (1024, 2048, 4096) for q in (128, 256, 512, 1024) for own in ("alone", "filled")]
 
 
 def tune_batch(plan, reps=3, use_cache=True):
     """Choose the batched launch's options and apply them to plan (a BatchPlan).
 
     Per scene: queries per wave and seed descent, by timing the plain
-    closest-point traversal (the same device code, with the four-wave register
-    allocation of the batched kernel) of the scene's queries on its frame 0.  Plan-wide: the Gaussian and query tile sizes, by timing whole
-    runs of the plan.  Returns {"per_scene", "gauss_tile", "query_tile", "ms",
-    "timings"} and leaves the plan configured with the best choice.
+    closest-point traversal (the same device code) of the scene's queries on its
+    frame 0.  Plan-wide, by timing whole runs of the plan: the Gaussian and query
+    tile sizes, each with the scenes' picks and with the launch's own choice (a
+    plain launch spreads small batches over the card, a tile runs them one after
+    another in four waves).  Returns {"per_scene", "gauss_tile", "query_tile",
+    "ms", "timings"} and leaves the plan configured with the best choice.
     """
     per_scene = []
     for sc in plan.scenes:
@@ -161,12 +165,14 @@ def tune_batch(plan, reps=3, use_cache=True):
         res = cache[key]
     else:
         timings = {}
-        for g, q in BATCH_TILES:
-            plan.configure(gauss_tile=g, query_tile=q, per_scene=per_scene)
-            timings[f"{g}/{q}"] = _graph_time(plan.run, reps)
+        scenes = {"alone": per_scene, "filled": [{"batch": 0, "seed": True} for _ in per_scene]}
+        for g, q, own in BATCH_TILES:
+            plan.configure(gauss_tile=g, query_tile=q, per_scene=scenes[own])
+            timings[f"{g}/{q}/{own}"] = _graph_time(plan.run, reps)
         best = min(timings, key=timings.get)
-        g, q = (int(x) for x in best.split("/"))
-        res = {"per_scene": per_scene, "gauss_tile": g, "query_tile": q, "ms": timings[best], "timings": timings}
+        g, q, own = best.split("/")
+        res = {"per_scene": scenes[own], "gauss_tile": int(g), "query_tile": int(q), "ms": timings[best],
+               "timings": timings}
         if use_cache:
             cache = _load_cache()
             cache[key] = res

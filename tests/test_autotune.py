@@ -57,3 +57,38 @@ def test_choices_of_earlier_candidates_are_not_reused(tmp_path, monkeypatch):
     monkeypatch.setattr(torch.cuda, "get_device_properties", lambda d: Props)
     key = autotune._key("closest", _Bvh(), torch.zeros(3, 4), False)
     assert key.startswith(autotune.FORMAT + "|") and key != "gfx950|closest|n=500|q=4|ordered=0"
+
+
+def test_the_untuned_plan_is_timed_and_can_win(monkeypatch):
+    """tune_batch times the plan as BatchPlan configures it by default, whatever the scenes'
+    picks, and applies it if it is the fastest."""
+    class Plan:
+        plan = torch.zeros(1)
+        scenes = [{"frames": torch.zeros(1, 3, 9), "faces": torch.zeros(3, n, dtype=torch.int32),
+                   "gface": torch.zeros(5), "queries": torch.zeros(3, 40)} for n in (7, 8)]
+        tried = []
+
+        def configure(self, *, batch=0, seed=True, gauss_tile=2048, query_tile=256, per_scene=None):
+            own = [(p.get("batch") or batch, seed if p.get("seed") is None else p["seed"])
+                   for p in per_scene or [{}] * len(self.scenes)]
+            self.now = (gauss_tile, query_tile, own)
+
+        def run(self):
+            self.tried.append(self.now)
+
+    class Props:
+        name = gcnArchName = "gfx950"
+
+    untuned = (2048, 256, [(0, True), (0, True)])
+    plan = Plan()
+
+    def cost(run, reps):
+        run()
+        return 1.0 if plan.now == untuned else 2.0
+    monkeypatch.setattr(torch.cuda, "get_device_properties", lambda d: Props)
+    monkeypatch.setattr(api, "lbvh_build", lambda v, f: None)
+    monkeypatch.setattr(autotune, "tune_closest", lambda *a, **kw: {"batch": 4, "seed": False})
+    monkeypatch.setattr(autotune, "_graph_time", cost)
+    res = autotune.tune_batch(plan, use_cache=False)
+    assert untuned in plan.tried and (2048, 256, [(4, False), (4, False)]) in plan.tried
+    assert plan.now == untuned and res["ms"] == 1.0
