@@ -486,7 +486,8 @@ __device__ void run_stack(const QueryArgs &a, BatchLds<kTri, M, K> &L, int self,
     WaveStack<kTri, M, K> &S = L.st[self];
     WaveStack<kTri, M, K> &O = L.st[owner];
     WaveMail &mail = L.mail;
-    // the stack never exceeds kCap + 62: a round of width k pushes at most
+    // the stack never exceeds kCap + 62: it starts with at most kCap entries (a
+    // chunk of 64, or what start_batch leaves), a round of width k pushes at most
     // 2k entries (nodes and leaves together), widths are cut to half the room
     // left, the leaves are tested whenever room runs out, and width-1 rounds are
     // a plain depth-first walk whose growth is bounded by the tree depth; each
@@ -632,7 +633,7 @@ __device__ __forceinline__ unsigned long long quad_xor64(unsigned long long v) {
 // that the rounds go on from them instead of walking from the root again.
 struct Kept {
     StackEntry *e;
-    int cap, alloc;                     // of the stack
+    int cap, alloc;                     // entries that may be kept, and the stack's
     int nodes, leaves;
     bool full;                          // they did not fit, or the walk ended early: start from the root
 };
@@ -726,7 +727,8 @@ __device__ __forceinline__ unsigned long long seed_descent(const QueryArgs &a, f
 // Starts a wave's batch [qb, qb + nb): points, starting bests (a hint's
 // distance, else the seed descent's, else max_dist2) and, on the stack, the root
 // or what the descent passed by.  Returns the stack's size, and the number of
-// waiting leaves in lc.
+// waiting leaves in lc: at most kCap together (run_stack's bound rests on it), so a
+// descent leaves room for the roots of the batch's hinted queries.
 //
 // Going on from the descents' paths took 50,000 cold queries on 40,000 faces from
 // 98 to 81 us, 20,002 on 46,000 faces from 43 to 39.
@@ -805,6 +807,7 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<kTri, M
         const bool need = a.seed && own && !hinted;
         if (__ballot(need)) {
             uint32_t at;
+            kept.cap -= __popcll(__ballot(lead && !need));   // the other queries' roots go on top
             const unsigned long long c = seed_descent<kTri, kLanes, kKeep>(a, p, need, at, kept, stats);
             walked = need;
             if (need && c < best) {
