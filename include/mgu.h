@@ -443,6 +443,10 @@ mg_status mg_sdf_update_records(const float *verts, int32_t n_verts, const int32
                                 int32_t nx, int32_t ny, int32_t nz, float *sdf, int32_t *face,
                                 void *records, size_t records_bytes, void *stream);
 
+/* Host-only: *bytes <- the records that mg_sdf_update_records makes use of for this grid
+ * (48 n_faces, or 0 where it takes the plain way). */
+mg_status mg_sdf_records_bytes(int32_t n_faces, int32_t k, int32_t nx, int32_t ny, int32_t nz, size_t *bytes);
+
 /* out [n_queries] (device) <- trilinear interpolation of the node values sdf at
  * queries [3][n_queries]; +inf for a query outside the grid's box. */
 mg_status mg_sdf_sample(const float *sdf, float lo_x, float lo_y, float lo_z, float h, int32_t nx, int32_t ny,

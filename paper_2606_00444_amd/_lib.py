@@ -90,6 +90,7 @@ PROTOTYPES = {
     "mg_grid_points": (I32, [F32, F32, F32, F32, I32, I32, I32, P, P]),
     "mg_sdf_update": (I32, [P, I32, P, I32, P, I32, F32, F32, F32, F32, I32, I32, I32, P, P, P]),
     "mg_sdf_update_records": (I32, [P, I32, P, I32, P, I32, F32, F32, F32, F32, I32, I32, I32, P, P, P, SZ, P]),
+    "mg_sdf_records_bytes": (I32, [I32, I32, I32, I32, I32, P]),
     "mg_sdf_sample": (I32, [P, F32, F32, F32, F32, I32, I32, I32, P, I32, P, P]),
     "mg_knn_surface_query": (I32, [P, SZ, I32, P, I32, P, I32, I32, F32, F32, P, P, P, P, P]),
     "mg_reduce_workspace_size": (I32, [I64, P]),

@@ -215,9 +215,16 @@ extern "C" mg_status mg_grid_points(float lo_x, float lo_y, float lo_z, float h,
 // many as the faces (us without and with records):
 //   40,000 faces: 64^3 nodes, k = 1 6.2 / 7.9; 48^3, k = 4 9.6 / 10.0; 64^3, k = 2 9.8 / 9.5; k = 4 17.1 / 12.1
 //   500,000 faces: 64^3, k = 1 13.4 / 19.0; k = 2 21.3 / 21.9; k = 4 36.0 / 26.7; k = 8 67.5 / 37.1
-static bool packs(int64_t n, int32_t k, int64_t nf, const void *records, size_t records_bytes) {
-    return records && records_bytes >= kRecord * sizeof(float4) * static_cast<size_t>(nf) && nf > 0 &&
-           (k == 1 || k == 2 || k == 4 || k == 8) && n * k >= (1 << 19) && n * k >= nf;
+static size_t record_bytes(int64_t n, int32_t k, int64_t nf) {
+    const bool pays = nf > 0 && (k == 1 || k == 2 || k == 4 || k == 8) && n * k >= (1 << 19) && n * k >= nf;
+    return pays ? kRecord * sizeof(float4) * static_cast<size_t>(nf) : 0;
+}
+
+extern "C" mg_status mg_sdf_records_bytes(int32_t n_faces, int32_t k, int32_t nx, int32_t ny, int32_t nz, size_t *bytes) {
+    int64_t n = 0;
+    if (bad_grid(1.0f, nx, ny, nz, n) || bad_count(n_faces) || k < 1 || k > 64 || !bytes) return MG_ERR_INVALID_ARGUMENT;
+    *bytes = record_bytes(n, k, n_faces);
+    return MG_OK;
 }
 
 extern "C" mg_status mg_sdf_update_records(const float *verts, int32_t n_verts, const int32_t *faces, int32_t n_faces,
@@ -232,7 +239,8 @@ extern "C" mg_status mg_sdf_update_records(const float *verts, int32_t n_verts, 
     const int grid = static_cast<int>(std::min<int64_t>(blocks_for(n, 256), 8192));
     hipStream_t st = as_stream(stream);
     const int64_t nv = n_verts, nf = n_faces;
-    float4 *rec = packs(n, k, nf, records, records_bytes) ? static_cast<float4 *>(records) : nullptr;
+    const size_t need = record_bytes(n, k, nf);
+    float4 *rec = records && need > 0 && records_bytes >= need ? static_cast<float4 *>(records) : nullptr;
     if (rec)
         hipLaunchKernelGGL(face_record_kernel, dim3(blocks_for(nf, 256)), dim3(256), 0, st, verts, nv, faces, nf, rec);
     if (n_faces > 0 && k == 1)

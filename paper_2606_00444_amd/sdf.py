@@ -9,10 +9,19 @@ one pass over the grid (mg_sdf_update), and sample(queries) interpolates it
 trilinearly (mg_sdf_sample).  See include/mgu.h for the exact definition.
 """
 
+import ctypes
+
 import torch
 
 from . import api
 from .api import _call, _ptr, _f32, _i32, _stream
+
+
+def records_bytes(n_faces, k, dims):
+    """Bytes of face records that an update of this grid uses; 0 where it reads the mesh itself."""
+    b = ctypes.c_size_t()
+    _call("mg_sdf_records_bytes", n_faces, k, *dims, ctypes.byref(b))
+    return b.value
 
 
 class IndexSDF:
@@ -35,7 +44,7 @@ class IndexSDF:
         self.face_k = r["face"]                   # [k][n] int32: the indices kept across frames
         self.sdf = torch.empty(n, device=dev)
         self.face = torch.empty(n, dtype=torch.int32, device=dev)
-        self.records = torch.empty(12 * self.faces.shape[1], device=dev)   # the faces' corners during an update
+        self.records = torch.empty(records_bytes(faces.shape[1], self.k, self.dims) // 4, device=dev)   # the faces' corners during an update
 
     def update(self, verts):
         """Signed distances of every node for the vertex positions verts [3][V] (into self.sdf)."""
