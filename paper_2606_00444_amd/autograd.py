@@ -106,7 +106,10 @@ class ChamferLoss(torch.autograd.Function):
         if bvh_b is None:
             bvh_b = api.lbvh_build(b_, None)
         o = api.chamfer(a_, bvh_a, b_, bvh_b, **(query or {}))
-        ctx.save_for_backward(a_, b_, o["nn_ab"], o["nn_ba"], api.scatter_order(bvh_a), api.scatter_order(bvh_b))
+        # each gradient scatters over the other set's points
+        order_a = api.scatter_order(bvh_a) if ctx.needs_input_grad[1] else None
+        order_b = api.scatter_order(bvh_b) if ctx.needs_input_grad[0] else None
+        ctx.save_for_backward(a_, b_, o["nn_ab"], o["nn_ba"], order_a, order_b)
         return o["total"].reshape(())
 
     @staticmethod
@@ -146,8 +149,9 @@ class TemplateProjectionLoss(torch.autograd.Function):
         bvh_mu = api.lbvh_build(mu, None)
         bvh_y = targets_bvh if targets_bvh is not None else api.lbvh_build(targets, None)
         o = api.chamfer(mu, bvh_mu, targets, bvh_y, add=P, **(nn_query or {}))
+        order_y = api.scatter_order(bvh_y) if ctx.needs_input_grad[0] else None
         ctx.save_for_backward(v, faces, gface, bary, q_local, log_scale, offset, targets, rec["face"],
-                              rec["point"], rec["bary"], mu, o["nn_ab"], o["nn_ba"], api.scatter_order(bvh_y))
+                              rec["point"], rec["bary"], mu, o["nn_ab"], o["nn_ba"], order_y)
         return o["total"].reshape(())
 
     @staticmethod
