@@ -383,6 +383,10 @@ def closest_point_query(bvh, verts, queries, max_dist2=math.inf, *, point=True, 
     be the very array this call overwrites) - see mg_query_options; waves: the
     batch kernel's register allocation (0: by launch size, 4 or 5).  out: a dict
     of output tensors to fill (face, and point, bary, dist2, normal or None each).
+    A large query set on a large tree left to the automatic choice takes 4 bytes a
+    query from torch's allocator for the call, on its current stream, also with out
+    given (none where a kernel, batch or order is named); a graph must be captured
+    through torch for that.
     """
     if bvh.kind != MG_PRIM_TRIANGLES:
         raise ValueError("closest_point_query needs a triangle BVH")
@@ -392,8 +396,11 @@ def closest_point_query(bvh, verts, queries, max_dist2=math.inf, *, point=True, 
     tree, count = _SPREAD_COLD if hint is None else _SPREAD_HINTED
     if (nq >= count and 96 * bvh.n >= tree and order is None and counters is None and kernel in (None, "auto")
             and not batch and not waves and not dynamic):
-        order = _spread(bvh, queries, nq)
-        seed = True                           # as the automatic choice without an order
+        try:
+            order = _spread(bvh, queries, nq)
+            seed = True                       # as the automatic choice without an order
+        except torch.OutOfMemoryError:        # no 4 bytes a query left: in the order given
+            pass
     _call("mg_closest_point_query", _ptr(bvh.buf), bvh.nbytes, bvh.n, _ptr(verts), verts.shape[1],
           _ptr(queries), nq, float(max_dist2), _ptr(o["face"]), _ptr(o.get("point")), _ptr(o.get("bary")),
           _ptr(o.get("dist2")), _ptr(o.get("normal")),
