@@ -291,7 +291,7 @@ struct WaveStack {
     StackEntry e[kAlloc];
     float4 q[M];                        // per query of the batch: the point, and prune_bound of its best
     unsigned long long best[M][K];      // the nearest faces, sorted: (d^2 bits, original id)
-    uint32_t code[M];                   // where the best face lies (a record slot); only a guess, see leaf_of
+    uint32_t code[M];                   // where the best face lies (a record slot); only a guess, see finish_query
 };
 
 struct WaveMail {
@@ -804,7 +804,12 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<kTri, M
                 }
             }
         }
-        const bool need = a.seed && own && !hinted;
+        rd = box_dist2(p, f3{a.root[0], a.root[1], a.root[2]}, f3{a.root[4], a.root[5], a.root[6]});
+        // On triangles also without `seed`, unless max_dist2 ends the query at the root: a
+        // round's leaves wait, so a query with no face to start from prunes nothing for
+        // many rounds (65,536 queries on 40,000 faces, batches of 4: 760 us, with the
+        // walk 152; leaves tested at once 665).
+        const bool need = own && !hinted && (a.seed || (kTri && rd <= prune_bound(a.maxd2, qnorm1(p))));
         if (__ballot(need)) {
             uint32_t at;
             kept.cap -= __popcll(__ballot(lead && !need));   // the other queries' roots go on top
@@ -815,7 +820,6 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<kTri, M
                 code = at;
             }
         }
-        rd = box_dist2(p, f3{a.root[0], a.root[1], a.root[2]}, f3{a.root[4], a.root[5], a.root[6]});
         pb = prune_bound(best < none ? __uint_as_float(static_cast<uint32_t>(best >> 32)) : a.maxd2, qnorm1(p));
         push = lead && rd <= pb;
     }
