@@ -304,11 +304,11 @@ mg_status mg_frame_update(const float *frames, int32_t n_frames, int32_t n_verts
  * n_queries >= 2048 batch (at least 512 workgroups of four waves), on triangles
  * without hints with n_queries >= 1024 batch.  NULL options also turn the seed
  * on; with options given, seed is as set.  seed != 0 (BATCH only): each query
- * first walks down the two nearest nodes of a level to a few leaves, for a tight
- * bound, and on triangles (batches up to 16) the wide expansion goes on from what
- * the walk passed by; seed == 0 leaves out the walks of queries that max_dist2
- * ends at the root, and on points all of them.  order (device int32 [n_queries] permutation, or NULL):
- * queries are processed in the order order[0], order[1], ... - e.g. the prim
+ * first walks down to a few leaves, for a tight bound: by the nearest node of a
+ * level, or on triangles (batches up to 16) the two nearest, where the wide
+ * expansion goes on from what the walk passed by; seed == 0 leaves out the walks
+ * of queries that max_dist2 ends at the root, and on points all of them.
+ * order (device int32 [n_queries] permutation, or NULL): queries are processed in the order order[0], order[1], ... - e.g. the prim
  * section of a MG_PRIM_POINTS BVH built over the queries, i.e. Morton order -
  * or mg_query_spread's, and every result is still written at the query's own
  * index.  counters (device uint64 [4], or NULL): += node expansions, leaves met,
