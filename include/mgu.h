@@ -300,9 +300,7 @@ mg_status mg_frame_update(const float *frames, int32_t n_frames, int32_t n_verts
  *   MG_QUERY_AUTO   BATCH with the default batch and seed on; a scan of every
  *                   leaf for up to 4,096 queries on up to 1,280 triangles or
  *                   3,072 points (if no batch, order, counters, queue or waves is given)
- * batch == 0 means the default: the largest of 16, 8, 4, 2, 1 with
- * n_queries >= 2048 batch (at least 512 workgroups of four waves), on triangles
- * without hints with n_queries >= 1024 batch.  NULL options also turn the seed
+ * batch == 0 means the default (mg_query_default_batch).  NULL options also turn the seed
  * on; with options given, seed is as set.  seed != 0 (BATCH only): each query
  * first walks down to a few leaves, for a tight bound: by the nearest node of a
  * level, or on triangles (batches up to 16) the two nearest, where the wide
@@ -393,6 +391,11 @@ mg_status mg_knn_surface_query(const void *bvh, size_t bvh_bytes, int32_t n_prim
                                int32_t n_verts, const float *queries, int32_t n_queries, int32_t k,
                                float eps, float max_dist2, int32_t *face_k, float *dist2_k, float *point,
                                uint64_t *counters, void *stream);
+
+/* Host-only: *batch <- the queries per wave of the batch traversal where none are
+ * named: the largest of 16, 8, 4, 2, 1 with n_queries >= 2048 batch (at least 512
+ * workgroups of four waves), on triangles 16 only from 40,961 queries. */
+mg_status mg_query_default_batch(int32_t prim_kind, int32_t n_queries, int32_t *batch);
 
 /* order [n_queries] (device) <- a permutation for mg_query_options.order that keeps
  * each XCD of the card on one part of the tree and each batch's queries apart, by
