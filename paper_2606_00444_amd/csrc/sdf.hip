@@ -211,12 +211,22 @@ extern "C" mg_status mg_grid_points(float lo_x, float lo_y, float lo_z, float h,
     return launch_status();
 }
 
-// The records pay from about half a million stored ids on, if they are at least as
-// many as the faces (us without and with records):
-//   40,000 faces: 64^3 nodes, k = 1 6.2 / 7.9; 48^3, k = 4 9.6 / 10.0; 64^3, k = 2 9.8 / 9.5; k = 4 17.1 / 12.1
-//   500,000 faces: 64^3, k = 1 13.4 / 19.0; k = 2 21.3 / 21.9; k = 4 36.0 / 26.7; k = 8 67.5 / 37.1
+// From how many nodes on the records pay, by k (one face a node saves few gathers, and a
+// mesh that stays in the first-level cache none), if the stored ids are at least as many
+// as the faces.  us without and with records:
+//   k = 1  128^3 nodes: 500 faces 16.4 / 17.4, 4,100 19.2 / 17.4, 40,000 23.3 / 19.8;  112^3: 40,000 17.3 / 15.8,
+//          500 12.1 / 13.3, 100,800 19.5 / 19.3;  96^3: 500,000 26.3 / 27.4
+//   k = 2  96^3: 500 12.0 / 11.8, 40,000 21.6 / 15.0, 500,000 41.9 / 33.8;  81^3: 100,800 17.5 / 18.2;  64^3: 500,000
+//          18.8 / 22.5
+//   k = 4  64^3: 500 9.7 / 8.5, 40,000 17.2 / 12.2, 500,000 31.0 / 26.0;  52^3: 40,000 11.7 / 10.6, 100,800 13.1 / 15.0
+//   k = 8  52^3: 500 13.0 / 10.5, 100,800 24.2 / 21.7;  48^3: 40,000 16.9 / 14.2, 500,000 38.5 / 28.2
 static size_t record_bytes(int64_t n, int32_t k, int64_t nf) {
-    const bool pays = nf > 0 && (k == 1 || k == 2 || k == 4 || k == 8) && n * k >= (1 << 19) && n * k >= nf;
+    const int64_t least = k == 1 && nf >= 4096 ? int64_t(1) << 21
+                          : k == 2             ? int64_t(3) << 18
+                          : k == 4             ? int64_t(1) << 18
+                          : k == 8             ? int64_t(1) << 16
+                                               : INT64_MAX;
+    const bool pays = nf > 0 && n >= least && n * k >= nf;
     return pays ? kRecord * sizeof(float4) * static_cast<size_t>(nf) : 0;
 }
 
