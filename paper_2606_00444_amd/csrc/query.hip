@@ -34,7 +34,7 @@ namespace mgu {
 namespace {
 
 // ---------------------------------------------------------------- lane kernel
-template <bool kTri>
+template <bool kTri, bool kBall>
 __global__ __launch_bounds__(kLaneBlock) void traverse_lane_kernel(QueryArgs a) {
     __shared__ int32_t s_stack[kLdsStack][kLaneBlock];
     int32_t deep[kMaxStack - kLdsStack];
@@ -89,8 +89,8 @@ __global__ __launch_bounds__(kLaneBlock) void traverse_lane_kernel(QueryArgs a) 
             if (rref < 0 && leaf_box_dist2<kTri>(p, r0, r1, r2) <= prune_bound(best, qm))
                 consider(leaf_dist2<kTri>(p, r0, r1, r2), __float_as_int(r1.w), ~rref);
             const float bound = prune_bound(best, qm);
-            const float dl = lref >= 0 ? child_bound<kTri>(p, dq, l0, l1, l2) : INFINITY;
-            const float dr = rref >= 0 ? child_bound<kTri>(p, dq, r0, r1, r2) : INFINITY;
+            const float dl = lref >= 0 ? child_bound<kTri, kBall>(p, dq, l0, l1, l2) : INFINITY;
+            const float dr = rref >= 0 ? child_bound<kTri, kBall>(p, dq, r0, r1, r2) : INFINITY;
             const bool gl = lref >= 0 && dl <= bound, gr = rref >= 0 && dr <= bound;
             if (gl && gr) {
                 const bool left_first = dl <= dr;
@@ -377,7 +377,18 @@ mg_status launch_traverse(QueryArgs a, const mg_query_options *opts, hipStream_t
         return launch_status();
     }
     if (kernel == MG_QUERY_LANE) {
-        hipLaunchKernelGGL(traverse_lane_kernel<kTri>, dim3(blocks_for(a.nq, kLaneBlock)), dim3(kLaneBlock), 0, s, a);
+        // On small trees the ball's part of the bound costs a lane more than what it prunes
+        // saves (us without and with it: 65,536 queries near 4,100 faces 96 / 106, uniform ones
+        // on 1,088 faces 281 / 323; near 40,000 faces 132 / 137, uniform on 100,800 1,510 / 1,332,
+        // 4,097 of them 1,196 / 520).
+        const dim3 grid(static_cast<unsigned>(blocks_for(a.nq, kLaneBlock)));
+        if constexpr (kTri) {
+            if (a.n > 8192) {
+                hipLaunchKernelGGL((traverse_lane_kernel<kTri, true>), grid, dim3(kLaneBlock), 0, s, a);
+                return launch_status();
+            }
+        }
+        hipLaunchKernelGGL((traverse_lane_kernel<kTri, false>), grid, dim3(kLaneBlock), 0, s, a);
         return launch_status();
     }
     switch (batch) {

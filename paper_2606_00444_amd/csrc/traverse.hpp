@@ -151,7 +151,9 @@ __device__ __forceinline__ float slab_query_margin(f3 q) { return 0x1p-20f * qno
 // raising the bound.  dq is also the query's slab margin, and the last factor
 // 1 - 2^-19 allows for |d| and the sums.  The box offset is p - median(p, lo, hi):
 // one instruction less per axis than two differences and a maximum.
-template <bool kTri>
+//
+// kBall false: the larger of the box and the slab distance alone, a third of the work.
+template <bool kTri, bool kBall = true>
 __device__ __forceinline__ float child_bound(f3 q, float dq, float4 c0, float4 c1, float4 c2) {
     const float dx = q.x - __builtin_amdgcn_fmed3f(q.x, c0.x, c1.x);
     const float dy = q.y - __builtin_amdgcn_fmed3f(q.y, c0.y, c1.y);
@@ -160,6 +162,7 @@ __device__ __forceinline__ float child_bound(f3 q, float dq, float4 c0, float4 c
     if (!kTri) return bd;
     const float s = c2.x * q.x + c2.y * q.y + c2.z * q.z;
     const float g = fmaxf(fmaxf(c1.w - s, s - c2.w) - dq, 0.0f);
+    if (!kBall) return fmaxf(bd, (g * g) * (1.0f - 0x1p-19f));
     const f3 w = f3{fmaf(-0.5f, c0.x + c1.x, q.x), fmaf(-0.5f, c0.y + c1.y, q.y), fmaf(-0.5f, c0.z + c1.z, q.z)};
     const f3 h = f3{c1.x - c0.x, c1.y - c0.y, c1.z - c0.z};
     const float m = fdot(f3{c2.x, c2.y, c2.z}, w);
