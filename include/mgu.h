@@ -305,7 +305,7 @@ mg_status mg_frame_update(const float *frames, int32_t n_frames, int32_t n_verts
  * first walks down to a few leaves, for a tight bound: by the nearest node of a
  * level, or on triangles (batches up to 16) the two nearest, where the wide
  * expansion goes on from what the walk passed by; seed == 0 leaves out the walks
- * of queries that max_dist2 ends at the root, and on points all of them.
+ * of queries that max_dist2 ends at the root.
  * order (device int32 [n_queries] permutation, or NULL): queries are processed in the order order[0], order[1], ... - e.g. the prim
  * section of a MG_PRIM_POINTS BVH built over the queries, i.e. Morton order -
  * or mg_query_spread's, and every result is still written at the query's own

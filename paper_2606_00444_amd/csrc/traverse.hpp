@@ -811,11 +811,11 @@ __device__ __forceinline__ int start_batch(const QueryArgs &a, WaveStack<kTri, M
             }
         }
         rd = box_dist2(p, f3{a.root[0], a.root[1], a.root[2]}, f3{a.root[4], a.root[5], a.root[6]});
-        // On triangles also without `seed`, unless max_dist2 ends the query at the root: a
-        // round's leaves wait, so a query with no face to start from prunes nothing for
-        // many rounds (65,536 queries on 40,000 faces, batches of 4: 760 us, with the
-        // walk 152; leaves tested at once 665).
-        const bool need = own && !hinted && (a.seed || (kTri && rd <= prune_bound(a.maxd2, qnorm1(p))));
+        // Also without `seed`, unless max_dist2 ends the query at the root: a round's leaves
+        // wait, so a query with no face to start from prunes nothing for many rounds (65,536
+        // queries on 40,000 faces, batches of 4: 760 us, with the walk 152, leaves tested at
+        // once 665; 10,000 on 100,000 points, batches of 8: 595, 25).
+        const bool need = own && !hinted && (a.seed || rd <= prune_bound(a.maxd2, qnorm1(p)));
         if (__ballot(need)) {
             uint32_t at;
             kept.cap -= __popcll(__ballot(lead && !need));   // the other queries' roots go on top

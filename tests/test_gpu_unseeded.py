@@ -46,3 +46,19 @@ def test_queries_out_of_reach_expand_nothing(device):
     c = torch.zeros(4, dtype=torch.int64, device=device)
     r = mg.closest_point_query(bvh, V, Q, 0.01, kernel="batch", batch=8, seed=False, counters=c)
     assert (r["face"] == -1).all() and c.cpu().tolist() == [0, 0, 0, 1000]
+
+
+@pytest.mark.parametrize("batch", [1, 8, 32])
+def test_unseeded_point_batches_search_no_more(device, batch):
+    import paper_2606_00444_amd as mg
+    g = torch.Generator(device=device).manual_seed(6)
+    P = torch.rand(3, 20000, device=device, generator=g)
+    Q = torch.rand(3, 3000, device=device, generator=g)
+    bvh = mg.lbvh_build(P)
+    res, counts = [], []
+    for seed in (True, False):
+        c = torch.zeros(4, dtype=torch.int64, device=device)
+        res.append(mg.nearest_point_query(bvh, P, Q, kernel="batch", batch=batch, seed=seed, counters=c))
+        counts.append(c.cpu().tolist())
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][1], res[1][1])
+    assert counts[1][0] <= 1.05 * counts[0][0], counts
