@@ -599,8 +599,8 @@ typedef struct mg_batch_scene {
  * them (the autotuner picks the traversal per scene). */
 typedef struct mg_batch_options {
     int32_t batch;              /* queries per wave of the batch traversal: 1, 2, 4, 8, 16; 0: for each
-                                   scene the most of 4, 8, 16 that gives each of four waves a batch of
-                                   the queries that a tile holds */
+                                   scene the least of 4, 8, 16 that runs the queries of a tile at once in
+                                   its four waves, or 16 */
     int32_t seed;               /* seed descent: 0 off, otherwise on */
     int32_t gauss_tile;         /* Gaussians per work item, multiple of 256 (0: 2048) */
     int32_t query_tile;         /* queries per work item, multiple of 4 * batch, of 16 for batch 0 (0: 256) */

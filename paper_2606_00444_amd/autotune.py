@@ -133,7 +133,7 @@ def options(res, order=None):
 
 BATCH_CANDIDATES = [("batch", b, s, False) for b in (1, 2, 4, 8, 16) for s in (False, True)]
 # Gaussian tile, query tile, and whether the scenes take the queries per wave and seed
-# that were fastest alone or the launch's own (a tile's waves filled, seed on).
+# that were fastest alone or the launch's own (a tile run at once, seed on).
 BATCH_TILES = [(g, q, own) for g in (1024, 2048, 4096) for q in (128, 256, 512, 1024) for own in ("alone", "filled")]
 
 

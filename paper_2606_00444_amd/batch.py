@@ -20,8 +20,8 @@ class BatchPlan:
       q_local [4][G], log_scale [3][G], queries [3][Q] float32,
       and optionally bvh (a triangle LBVH over the faces; built from frame 0 if absent)
       and this scene's traversal: batch (queries per wave), seed, query_tile.
-    Options: the plan-wide defaults of batch (0: what fills the waves of a
-    scene's tiles, up to 16), seed and query_tile, and gauss_tile.
+    Options: the plan-wide defaults of batch (0: what runs a scene's tiles at
+    once, up to 16 queries per wave), seed and query_tile, and gauss_tile.
     autotune.tune_batch chooses all of them.  After run(), out[i]
     holds scene i's per-frame outputs.
     """

@@ -398,12 +398,13 @@ inline mg_status scratch_words(const mg_batch_scene *scenes, int32_t n_scenes, i
 // Queries per wave where neither the scene nor the plan names a number.  A tile is one
 // workgroup's whatever the batch, so smaller batches only run it in more, emptier
 // rounds: 24 scene-frames of 60,000 queries in tiles of 256 took 1,545 us at 4 queries
-// per wave, 1,113 at 8 and 925 at 16.  The most, from 4 up, that gives each of the four
-// waves a batch of the queries that a tile holds is taken.
+// per wave, 1,113 at 8 and 925 at 16; six of 20 queries on 500 faces 82.8 at 4, 69.6 at 8
+// and 70.2 at 16.
+// The least, from 4 up, that runs the queries of a tile at once is taken, or 16.
 inline int default_batch(int64_t query_tile, int64_t n_queries) {
     const int64_t held = std::min(query_tile, n_queries);
     int batch = 4;
-    while (batch < 16 && 8 * batch <= held) batch *= 2;
+    while (batch < 16 && 4 * batch < held) batch *= 2;
     return batch;
 }
 

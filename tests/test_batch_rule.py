@@ -24,9 +24,10 @@ def test_a_named_number_is_taken(batch, tile):
     assert _per_wave(60000, batch=batch, plan_batch=16, plan_tile=tile) == (0, batch)      # the scene's before the plan's
 
 
-@pytest.mark.parametrize("n,tile,want", [(60000, 0, 16), (60000, 16, 4), (60000, 32, 8), (60000, 48, 8), (60000, 64, 16),
-                                         (64, 256, 16), (63, 256, 8), (32, 256, 8), (31, 256, 4), (1, 256, 4), (0, 256, 4)])
-def test_the_default_gives_every_wave_a_batch(n, tile, want):
+@pytest.mark.parametrize("n,tile,want", [(60000, 0, 16), (60000, 16, 4), (60000, 32, 8), (60000, 48, 16), (60000, 64, 16),
+                                         (64, 256, 16), (33, 256, 16), (32, 256, 8), (17, 256, 8), (16, 256, 4),
+                                         (1, 256, 4), (0, 256, 4)])
+def test_the_default_runs_a_tile_at_once(n, tile, want):
     assert _per_wave(n, tile=tile) == (0, want)
     assert _per_wave(n, plan_tile=tile) == (0, want)
     if tile == 0:
