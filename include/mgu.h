@@ -394,8 +394,9 @@ mg_status mg_knn_surface_query(const void *bvh, size_t bvh_bytes, int32_t n_prim
 
 /* Host-only: *batch <- the queries per wave of the batch traversal where none are
  * named: the largest of 16, 8, 4, 2, 1 with n_queries >= 2048 batch (at least 512
- * workgroups of four waves), on triangles 16 only from 40,961 queries. */
-mg_status mg_query_default_batch(int32_t prim_kind, int32_t n_queries, int32_t *batch);
+ * workgroups of four waves; 1024 batch without hints on up to 2,048 triangles); on
+ * triangles 16 only from 40,961 queries (not so without hints on up to 16,384). */
+mg_status mg_query_default_batch(int32_t prim_kind, int32_t n_prims, int32_t n_queries, int32_t hinted, int32_t *batch);
 
 /* order [n_queries] (device) <- a permutation for mg_query_options.order that keeps
  * each XCD of the card on one part of the tree and each batch's queries apart, by

@@ -83,7 +83,7 @@ PROTOTYPES = {
     "mg_lbvh_refit": (I32, [P, I32, P, SZ, I32, I32, P]),
     "mg_closest_point_query": (I32, [P, SZ, I32, P, I32, P, I32, F32, P, P, P, P, P, P, P]),
     "mg_closest_point_bruteforce": (I32, [P, I32, P, I32, P, I32, F32, P, P, P, P, P, P]),
-    "mg_query_default_batch": (I32, [I32, I32, P]),
+    "mg_query_default_batch": (I32, [I32, I32, I32, I32, P]),
     "mg_query_spread": (I32, [P, SZ, I32, I32, P, I32, P, P, SZ, P]),
     "mg_nearest_point_query": (I32, [P, SZ, I32, P, P, I32, F32, P, P, P, P]),
     "mg_particles_integrate": (I32, [P, P, I32, F32, F32, F32, F32, P]),

@@ -287,27 +287,31 @@ inline bool scans(const mg_query_options *o, int64_t n, int64_t nq) {
 // Queries per wave by default: the largest of 16, 8, 4, 2, 1 that leaves at least 512
 // workgroups of four waves; on triangles 16 only for more queries than batches of 8 are
 // resident at once (five waves on each of 1,024 SIMDs: 40,960), where a second round of
-// waves costs more than the fuller batch.  us in batches of 8 and 16, queries near the
-// surface:
+// waves costs more than the fuller batch.  Cold searches of small trees, whose walks are
+// most of their work and fill a wave only with 16, differ: 256 workgroups are enough up
+// to 2,048 faces, and 16 is not held back up to 16,384.  us in batches of 8 and 16,
+// queries near the surface:
 //   hinted  4,100 faces: 32,768 queries 27.0 / 27.0, 50,000 42.3 / 32.7;  40,000: 28,000 32.7 / 33.4,
 //           40,000 37.2 / 37.3, 50,000 54.0 / 39.6;  500,000: 32,768 55.2 / 60.9, 65,536 94.6 / 74.7
-//   cold    4,100 faces: 16,384 29.3 / 30.5, 32,768 34.9 / 31.6, 50,000 57.2 / 39.1;  40,000: 24,000 36.6 / 38.5,
-//           50,000 69.0 / 46.9;  500,000: 16,384 58.7 / 82.8, 32,768 68.4 / 94.1, 50,000 109 / 102
+//   cold    500 faces: 32,768 28.3 / 23.9;  4,100: 16,384 29.3 / 30.5, 40,000 42.0 / 35.4;  10,200: 40,000 42.2 / 36.6;
+//           40,000: 24,000 36.6 / 38.5, 50,000 69.0 / 46.9;  500,000: 16,384 58.7 / 82.8, 32,768 68.4 / 94.1,
+//           50,000 109 / 102
 //   k = 4   20,002 queries: 4,100 faces 35.2 / 42.2, 46,460 49.2 / 55.9, 500,000 70.6 / 133
-inline int default_batch(bool tri, int64_t nq) {
+inline int default_batch(bool tri, bool cold, int64_t n, int64_t nq) {
+    const int64_t least = tri && cold && n <= 2048 ? 1024 : 2048;
     int batch = 16;
-    while (batch > 1 && nq < static_cast<int64_t>(2048) * batch) batch >>= 1;
-    return tri && batch == 16 && nq <= 5 * 1024 * 8 ? 8 : batch;
+    while (batch > 1 && nq < least * batch) batch >>= 1;
+    return tri && !(cold && n <= 16384) && batch == 16 && nq <= 5 * 1024 * 8 ? 8 : batch;
 }
 
 // Default traversal when the caller gives no options: the batch kernel with a
 // seed descent and the default batch.
-inline void resolve(const mg_query_options *o, bool tri, int64_t nq, int &kernel, int &batch, int &seed) {
+inline void resolve(const mg_query_options *o, bool tri, int64_t n, int64_t nq, int &kernel, int &batch, int &seed) {
     kernel = o ? o->kernel : MG_QUERY_AUTO;
     batch = o ? o->batch : 0;
     seed = o ? (o->seed != 0) : 1;
     if (kernel == MG_QUERY_AUTO) kernel = MG_QUERY_BATCH;
-    if (batch <= 0) batch = default_batch(tri, nq);
+    if (batch <= 0) batch = default_batch(tri, !(o && o->hint), n, nq);
 }
 
 __global__ void zero_word_kernel(uint32_t *w) { *w = 0u; }
@@ -366,7 +370,7 @@ mg_status launch_batch(const QueryArgs &a, int waves, hipStream_t s) {
 template <bool kTri>
 mg_status launch_traverse(QueryArgs a, const mg_query_options *opts, hipStream_t s) {
     int kernel, batch;
-    resolve(opts, kTri, a.nq, kernel, batch, a.seed);
+    resolve(opts, kTri, a.n, a.nq, kernel, batch, a.seed);
     const int waves = opts ? opts->waves : 0;
     a.order = opts ? opts->order : nullptr;
     a.counters = opts ? reinterpret_cast<unsigned long long *>(opts->counters) : nullptr;
@@ -410,10 +414,12 @@ mg_status launch_knn(const QueryArgs &a, hipStream_t s) {
     return launch_status();
 }
 
-// Queries per wave as for the single closest point, at most 64 / K.
+// Queries per wave as for the single closest point on large trees (lists make small ones
+// dearer too: k = 4 of 20,002 queries on 500 faces 30.2 us in batches of 8, 36.3 of 16),
+// at most 64 / K.
 template <int K>
 mg_status launch_knn_k(const QueryArgs &a, hipStream_t s) {
-    const int batch = default_batch(true, a.nq);
+    const int batch = default_batch(true, true, INT32_MAX, a.nq);
     if constexpr (K <= 4)
         if (batch >= 16) return launch_knn<16, K>(a, s);
     if (batch >= 8) return launch_knn<8, K>(a, s);
@@ -550,10 +556,12 @@ extern "C" mg_status mg_closest_point_query(const void *bvh, size_t bvh_bytes, i
     return launch_traverse<true>(a, opts, as_stream(stream));
 }
 
-extern "C" mg_status mg_query_default_batch(int32_t prim_kind, int32_t n_queries, int32_t *batch) {
-    if ((prim_kind != MG_PRIM_TRIANGLES && prim_kind != MG_PRIM_POINTS) || bad_count(n_queries) || !batch)
+extern "C" mg_status mg_query_default_batch(int32_t prim_kind, int32_t n_prims, int32_t n_queries, int32_t hinted,
+                                            int32_t *batch) {
+    if ((prim_kind != MG_PRIM_TRIANGLES && prim_kind != MG_PRIM_POINTS) || bad_count(n_prims) || bad_count(n_queries) ||
+        !batch)
         return MG_ERR_INVALID_ARGUMENT;
-    *batch = default_batch(prim_kind == MG_PRIM_TRIANGLES, n_queries);
+    *batch = default_batch(prim_kind == MG_PRIM_TRIANGLES, !hinted, n_prims, n_queries);
     return MG_OK;
 }
 

@@ -7,18 +7,25 @@ import pytest
 from paper_2606_00444_amd import MG_PRIM_POINTS, MG_PRIM_TRIANGLES, _lib
 
 
-def _default(kind, n):
+def _default(kind, n, nq, hinted):
     b = ctypes.c_int32(-1)
-    return _lib.load().mg_query_default_batch(kind, n, ctypes.byref(b)), b.value
+    return _lib.load().mg_query_default_batch(kind, n, nq, hinted, ctypes.byref(b)), b.value
 
 
-@pytest.mark.parametrize("n,tri,points", [(0, 1, 1), (1, 1, 1), (4095, 1, 1), (4096, 2, 2), (8191, 2, 2), (8192, 4, 4),
-                                          (16383, 4, 4), (16384, 8, 8), (32767, 8, 8), (32768, 8, 16), (40960, 8, 16),
-                                          (40961, 16, 16), (1000000, 16, 16)])
-def test_rule(n, tri, points):
-    assert _default(MG_PRIM_TRIANGLES, n) == (0, tri)
-    assert _default(MG_PRIM_POINTS, n) == (0, points)
+# queries, then batches for triangles hinted and cold on 2,048, 16,384 and 16,385 faces, and for points
+@pytest.mark.parametrize("nq,hinted,small,mid,large,points", [
+    (0, 1, 1, 1, 1, 1), (2047, 1, 1, 1, 1, 1), (2048, 1, 2, 1, 1, 1), (4095, 1, 2, 1, 1, 1), (4096, 2, 4, 2, 2, 2),
+    (8191, 2, 4, 2, 2, 2), (8192, 4, 8, 4, 4, 4), (16383, 4, 8, 4, 4, 4), (16384, 8, 16, 8, 8, 8),
+    (32767, 8, 16, 8, 8, 8), (32768, 8, 16, 16, 8, 16), (40960, 8, 16, 16, 8, 16), (40961, 16, 16, 16, 16, 16),
+    (1000000, 16, 16, 16, 16, 16)])
+def test_rule(nq, hinted, small, mid, large, points):
+    for n in (1, 2048, 2049, 16384, 16385, 1000000):
+        assert _default(MG_PRIM_TRIANGLES, n, nq, 1) == (0, hinted)
+        assert _default(MG_PRIM_TRIANGLES, n, nq, 0) == (0, small if n <= 2048 else mid if n <= 16384 else large)
+        for h in (0, 1):
+            assert _default(MG_PRIM_POINTS, n, nq, h) == (0, points)
 
 
 def test_bad_arguments():
-    assert _default(7, 10)[0] == 1 and _default(MG_PRIM_POINTS, -1)[0] == 1
+    assert _default(7, 10, 10, 0)[0] == 1 and _default(MG_PRIM_POINTS, 10, -1, 0)[0] == 1
+    assert _default(MG_PRIM_TRIANGLES, -1, 10, 0)[0] == 1
