@@ -81,8 +81,9 @@ inline mg_lbvh_layout make_layout(int64_t n, int kind) {
 // with n <= 512 C (a few hundred subtrees, so the top tree stays small),
 // capped at 2048 (the phase-1 LDS state is 52 B per leaf).  A tree of 257 to 512
 // leaves is one subtree: a level more in it is less than a phase for the one
-// or two nodes above subtrees of 256 (refit of 500 faces: 15.2 us
-// in subtrees of 256, 13.8 of 512; of 1,120 16.2 and 17.7).
+// or two nodes above subtrees of 256 (refits in subtrees of 256 and of 512: 257 faces
+// 14.0, 13.0 us; 320 15.7, 13.3; 450 15.7, 13.2; 512 16.6, 14.8; 320 points 9.5, 7.8; but
+// 1,120 faces 16.2, 17.7).
 inline int chunk_log2_for(int64_t n) {
     int c = n > 256 && n <= 512 ? 9 : 8;
     while ((int64_t(512) << c) < n && c < 11) ++c;
@@ -772,7 +773,7 @@ __global__ __launch_bounds__(kHierThreads) void hierarchy_kernel(const uint32_t 
 
 // Subtrees largest first.  Phase 1 of the refit gives subtree k to workgroup k
 // (then k + grid, ...), and workgroups start in index order as compute units free
-// up; when more subtrees than resident workgroups exist (LDS allows two per CU at
+// up; when more subtrees than resident workgroups exist (LDS allows three per CU at
 // 1024-leaf chunks, one at 2048), the late starters should be the small subtrees
 // (longest-first list scheduling).  One workgroup deals them by size, a counting
 // sort in LDS (the bitonic sort it replaces took 16 us); equal sizes in any order,
@@ -1209,10 +1210,10 @@ extern "C" mg_status mg_frame_update(const float *frames, int32_t n_frames, int3
     w.in = Inputs{src, n_verts, faces, n_faces, gface, bary, q_local, log_scale, offset, n_gauss};
     w.mean = mean; w.quat = quat; w.cov = cov; w.rot = rot;
     w.sub_blocks = 2 * ((n_faces + C - 1) / C);
-    const int threads = 512;                 // as the plain refit (launch_refit_k)
-    w.copy_tile = 16 * static_cast<int64_t>(threads);
+    const int64_t tile = 512;                // items of a round, whatever the workgroup's size
+    w.copy_tile = 16 * tile;
     w.copy_blocks = (n3 + w.copy_tile - 1) / w.copy_tile;
-    w.gauss_tile = 2 * static_cast<int64_t>(threads);
+    w.gauss_tile = 2 * tile;
     const int64_t gauss_blocks = (static_cast<int64_t>(n_gauss) + w.gauss_tile - 1) / w.gauss_tile;
     const int64_t grid = w.sub_blocks + w.copy_blocks + gauss_blocks;
     if (grid > 0x7fffffff) return MG_ERR_INVALID_ARGUMENT;

@@ -116,10 +116,9 @@ __global__ __launch_bounds__(kLaneBlock) void traverse_lane_kernel(QueryArgs a) 
     if (a.counters) add_counters(a, n_exp, n_lbox, n_lex, 1);
 }
 
-// kMinWaves: the fewest waves per SIMD the register allocation must allow (4:
-// at most 128 VGPRs, what the triangle kernel needs without spills; 5 trades a
-// few spills outside the round loop for a fifth resident wave, which pays only
-// when the launch has more waves than four per SIMD hold).
+// kMinWaves: the fewest waves per SIMD the register allocation must allow.  The
+// triangle kernel takes 94 or 95 VGPRs and no scratch with 4 as with 5, so that five
+// waves are resident either way and only the compiler's schedule differs.
 template <bool kTri, int M, int kMinWaves>
 __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_eu(kMinWaves))) void traverse_batch_kernel(QueryArgs a) {
     __shared__ BatchLds<kTri, M> lds;
@@ -131,7 +130,7 @@ __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_e
 
 // ----------------------------------------------------------------- k nearest
 // The batch kernel with the K best per query (k <= K kept), the children pruned
-// against the k-th.  20,002 queries, k = 4, on 46,000 faces: 268 -> 84 us
+// against the k-th.  20,002 queries, k = 4, on 46,000 faces: 268 -> 51 us
 // against one query per lane, depth-first, where a wave waits for its longest walk.
 template <int M, int K>
 __global__ __launch_bounds__(64 * kBatchWaves) __attribute__((amdgpu_waves_per_eu(4))) void knn_batch_kernel(QueryArgs a) {
@@ -351,12 +350,12 @@ int device_cus() {
     return v;
 }
 
-// The triangle kernel takes the five-wave allocation when its batches outnumber
-// four waves on every SIMD (CUs x 4 SIMDs x 4 waves; 4,096 on a whole MI355X):
-// 1M queries in batches of 16 ran 7% faster, while launches that fit in four
-// waves per SIMD ran up to 2% slower with it.
-// waves: 0 by that rule, 4 or 5 forced (the batched launch's tuner times the
-// plain traversal with the four-wave allocation its own kernel has).
+// The five-wave form of the triangle kernel is launched when its batches outnumber
+// four waves on every SIMD (CUs x 4 SIMDs x 4 waves; 4,096 on a whole MI355X).  The
+// forms differed when four waves took 109 VGPRs (1M queries ran 7% faster with five);
+// now both fit five waves and take the same time (1M hinted queries on 500,000 faces
+// 1,342 and 1,342 us, 100,000 near it 131 and 131).
+// waves: 0 by that rule, 4 or 5 forced.
 template <bool kTri, int M>
 mg_status launch_batch(const QueryArgs &a, int waves, hipStream_t s) {
     if constexpr (kTri) {
