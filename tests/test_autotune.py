@@ -50,6 +50,19 @@ def test_a_named_traversal_that_wins_is_returned(timed, monkeypatch):
     assert autotune.options(res) == {"kernel": "batch", "batch": 8, "seed": True, "dynamic": True}
 
 
+@pytest.mark.parametrize("own,kept", [(1.02, True), (1.05, False)])
+def test_the_default_call_is_kept_unless_clearly_slower(own, kept, timed, monkeypatch):
+    """Tuned on cold queries, a choice is used with hints too: a named batch that wins by less
+    than two runs differ would fix what the default follows."""
+    def cost(run, reps):
+        run()
+        kw = timed[-1]
+        return own if _own_choice(kw) else 1.0 if kw["kernel"] == "batch" and kw["batch"] == 8 and not kw["dynamic"] else 2.0
+    monkeypatch.setattr(autotune, "_graph_time", cost)
+    res = autotune.tune_closest(_Bvh(), None, torch.zeros(3, 4), use_cache=False)
+    assert res["auto"] is kept and res["ms"] == (own if kept else 1.0)
+
+
 def test_choices_of_earlier_candidates_are_not_reused(tmp_path, monkeypatch):
     """A stored choice is found by a key that names the candidates' format."""
     class Props:
