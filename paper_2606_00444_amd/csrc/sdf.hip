@@ -211,22 +211,24 @@ extern "C" mg_status mg_grid_points(float lo_x, float lo_y, float lo_z, float h,
     return launch_status();
 }
 
-// From how many nodes on the records pay, by k (one face a node saves few gathers, and a
-// mesh that stays in the first-level cache none), if the stored ids are at least as many
-// as the faces.  us without and with records:
-//   k = 1  128^3 nodes: 500 faces 16.4 / 17.4, 4,100 19.2 / 17.4, 40,000 23.3 / 19.8;  112^3: 40,000 17.3 / 15.8,
-//          500 12.1 / 13.3, 100,800 19.5 / 19.3;  96^3: 500,000 26.3 / 27.4
-//   k = 2  96^3: 500 12.0 / 11.8, 40,000 21.6 / 15.0, 500,000 41.9 / 33.8;  81^3: 100,800 17.5 / 18.2;  64^3: 500,000
-//          18.8 / 22.5
-//   k = 4  64^3: 500 9.7 / 8.5, 40,000 17.2 / 12.2, 500,000 31.0 / 26.0;  52^3: 40,000 11.7 / 10.6, 100,800 13.1 / 15.0
+// From how many stored ids on the records pay, in units of 2^16, for k = 1, 2, 4, 8 and
+// meshes of under 2,048, up to 65,536, up to 262,144 and more faces, if the ids are at
+// least as many as the faces: they save a gather-bound update some 4 (k = 4 on 4,100
+// faces), 6 (40,000), 7 (100,800) and 10 us (500,000) a million ids, less with fewer faces
+// a node (k = 2: 0.7 on 500 faces, 3, 5, 7 and 10; k = 1 on 4,100 faces 1), and the pass
+// that writes them takes 1, 2, 6 and 5 us.  us without and with records:
+//   k = 1  4,100 faces: 96^3 nodes 10.1 / 10.1, 128^3 19.2 / 17.4;  40,000: 81^3 9.5 / 10.4, 96^3 12.7 / 12.1;
+//          100,800: 112^3 19.5 / 19.3;  500,000: 96^3 26.3 / 27.4, 112^3 34.9 / 31.6;  500: 128^3 16.4 / 17.4
+//   k = 2  500 faces: 81^3 9.1 / 9.2, 96^3 12.0 / 11.8;  4,100: 64^3 8.1 / 7.0;  40,000: 64^3 10.0 / 9.6;  100,800:
+//          81^3 17.5 / 18.2, 96^3 24.3 / 20.2;  500,000: 72^3 24.3 / 25.7, 81^3 39.8 / 29.2
+//   k = 4  500 faces: 52^3 7.9 / 7.8;  40,000: 52^3 11.7 / 10.6, 64^3 17.2 / 12.2;  100,800: 52^3 13.1 / 15.0,
+//          62^3 18.2 / 18.3, 64^3 19.2 / 16.0;  500,000: 52^3 25.1 / 24.5, 64^3 31.0 / 26.0
 //   k = 8  52^3: 500 13.0 / 10.5, 100,800 24.2 / 21.7;  48^3: 40,000 16.9 / 14.2, 500,000 38.5 / 28.2
 static size_t record_bytes(int64_t n, int32_t k, int64_t nf) {
-    const int64_t least = k == 1 && nf >= 4096 ? int64_t(1) << 21
-                          : k == 2             ? int64_t(3) << 18
-                          : k == 4             ? int64_t(1) << 18
-                          : k == 8             ? int64_t(1) << 16
-                                               : INT64_MAX;
-    const bool pays = nf > 0 && n >= least && n * k >= nf;
+    constexpr int64_t kLeast[4][4] = {{INT32_MAX, 13, 24, 16}, {24, 8, 18, 16}, {8, 8, 14, 8}, {8, 8, 8, 8}};
+    const int row = k == 1 ? 0 : k == 2 ? 1 : k == 4 ? 2 : k == 8 ? 3 : -1;
+    const int mesh = nf < 2048 ? 0 : nf <= 65536 ? 1 : nf <= 262144 ? 2 : 3;
+    const bool pays = row >= 0 && nf > 0 && n * k >= kLeast[row][mesh] << 16 && n * k >= nf;
     return pays ? kRecord * sizeof(float4) * static_cast<size_t>(nf) : 0;
 }
 

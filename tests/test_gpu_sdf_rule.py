@@ -16,7 +16,7 @@ def device():
     return need_gpu()
 
 
-@pytest.mark.parametrize("k,least", [(1, 1 << 21), (2, 3 << 18), (4, 1 << 18), (8, 1 << 16)])
+@pytest.mark.parametrize("k,least", [(1, 13 << 16), (2, 1 << 18), (4, 1 << 17), (8, 1 << 16)])
 def test_records_change_nothing_at_the_rule(device, k, least):
     """Just below and just above (grids of 1,023 nodes a layer, no whole number of
     workgroups): the values and faces of the plain update, ids outside the mesh ignored, and
