@@ -301,15 +301,15 @@ mg_status mg_frame_update(const float *frames, int32_t n_frames, int32_t n_verts
  *                   leaf for up to 4,096 queries on up to 1,280 triangles or
  *                   3,072 points (if no batch, order, counters, queue or waves is given)
  * batch == 0 means the default (mg_query_default_batch).  NULL options also turn
- * the seed on; with options given, seed is as set.  seed != 0 (BATCH only): each query
- * first walks down to a few leaves, for a tight bound: by the nearest node of a
+ * the seed on; with options given, seed is as set.  seed != 0 (BATCH only): each
+ * query first walks down to a few leaves, for a tight bound: by the nearest node of a
  * level, or on triangles (batches up to 16) the two nearest, where the wide
  * expansion goes on from what the walk passed by; seed == 0 leaves out the walks
  * of queries that max_dist2 ends at the root.
  * order (device int32 [n_queries] permutation, or NULL): queries are processed
- * in the order order[0], order[1], ... - e.g. the prim section of a MG_PRIM_POINTS BVH built over the queries, i.e. Morton order -
- * or mg_query_spread's, and every result is still written at the query's own
- * index.  counters (device uint64 [4], or NULL): += node expansions, leaves met,
+ * in the order order[0], order[1], ... - e.g. the prim section of a
+ * MG_PRIM_POINTS BVH built over the queries, i.e. Morton order - or
+ * mg_query_spread's, and every result is still written at the query's own index.  counters (device uint64 [4], or NULL): += node expansions, leaves met,
  * exact leaf tests, queries.  queue (device uint32 [1], or NULL; BATCH only): the
  * waves stay resident and take query batches one at a time from this counter,
  * which the call zeroes on its stream before the traversal (no initial value
@@ -325,9 +325,9 @@ mg_status mg_frame_update(const float *frames, int32_t n_frames, int32_t n_verts
  * of their directions.  waves (BATCH on triangles): the waves per SIMD that
  * the batch kernel is compiled for; 0 picks 5 when the batches outnumber four
  * waves on every SIMD (more than 4,096 batches) and 4 otherwise (both forms
- * leave room for five), 4 or 5 forces one; any other value is MG_ERR_INVALID_ARGUMENT.  Results do not
- * depend on any of these choices except among exact ties, which all pick the
- * lowest original id. */
+ * leave room for five), 4 or 5 forces one; any other value is
+ * MG_ERR_INVALID_ARGUMENT.  Results do not depend on any of these choices except
+ * among exact ties, which all pick the lowest original id. */
 #define MG_QUERY_AUTO  0
 #define MG_QUERY_LANE  1
 #define MG_QUERY_BATCH 2
